@@ -196,11 +196,11 @@ WOLF_API int64_t wolf_direct_work_bytes(int32_t n, int32_t dtype);
  * n_fft = 512). Four passes, one per axis. An n_fft that is a power of two (<= 1024) or one of 6, 10,
  * 12, 20, 24, 36, 48, 72, 80, 96, 100, 144, 192, 200 takes zero-padded FFTs of n_fft points per line
  * (the N inputs at the centre, the N central outputs kept; mixed radices 2, 3, 5 for the listed
- * lengths). Any other n_fft takes dense N x N products with the exact centred kernel
- * e^{-+2 pi i (k - N/2)(n - N/2) / n_fft} (32 N real flops per element).
+ * lengths). Any other n_fft takes products with the exact centred kernel
+ * e^{-+2 pi i (k - N/2)(n - N/2) / n_fft}, halved by its mirror symmetry (8 N real flops per element).
  *   n          even, 2..256.   n_fft   N..2048.
  *   w_in, w_out   device N^4 complex; w_in == w_out allowed (partial overlap is not).
- *   work       device N^4 complex of `dtype` (used by the dense passes), overwritten; must not
+ *   work       device N^4 complex of `dtype`, its contents undefined after the call; must not
  *              overlap w_in or w_out.
  *   farfield   0 Fresnel, 1 far field.   kind, dtype, out_pitch_m as wolf_propagate_fresnel.
  * The source builder and the observables accept any even N as well.

@@ -557,17 +557,14 @@ WOLF_API wolf_status wolf_propagate_padded(const void* w_in, void* w_out, int32_
   if (partial_overlap(w_in, w_out, bytes) || intervals_overlap(work, bytes, w_in, bytes) ||
       intervals_overlap(work, bytes, w_out, bytes))
     return fail(WOLF_EINVAL, "%s: buffers overlap", who);
-  // Tables of the dense passes: chirps on the N-point grids, no (-1)^n (the centring is exact in
-  // the kernel index), output pitch lambda z / (n_fft pitch).
+  // Chirps on the N-point grids, output pitch lambda z / (n_fft pitch).
   const double dx = wavelength_m * z_m / ((double)n_fft * pitch_m);
   const double c = kind == WOLF_PRIMARY ? 1.0 / ((4.0 * M_PI * z_m) * (4.0 * M_PI * z_m))
                                         : 1.0 / ((wavelength_m * z_m) * (wavelength_m * z_m));
   const double a_src = farfield ? 0.0 : pitch_m * pitch_m / (wavelength_m * z_m);
   const double a_out = dx * dx / (wavelength_m * z_m);
-  // A power-of-two n_fft takes zero-padded FFTs (the centring as (-1)^n in the tables); any other
-  // n_fft the dense passes (the centring exact in the kernel index, no (-1)^n).
-  const bool fft = wolf::pad_fft_supported(n, n_fft);
-  const int chk = fft ? 1 : 0;
+  // The FFT passes take the centring as (-1)^n in the tables; the dense ones have it exact in the index.
+  const int chk = wolf::pad_fft_supported(n, n_fft) ? 1 : 0;
   wolf::OperatorTables op;
   op.pre2 = wolf::Chirp{a_src, 1.0, +1, chk};
   op.post2 = wolf::Chirp{a_out, 1.0, +1, chk};
@@ -579,16 +576,10 @@ WOLF_API wolf_status wolf_propagate_padded(const void* w_in, void* w_out, int32_
   op.pupil = wolf::Pupil{0, 0};
   if (out_pitch_m) *out_pitch_m = dx;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipError_t e;
-  if (fft)
-    e = dtype == WOLF_C64 ? wolf::launch_operator_padfft<float2>(n, n_fft, (const float2*)w_in, (float2*)w_out, op, st)
-                          : wolf::launch_operator_padfft<double2>(n, n_fft, (const double2*)w_in, (double2*)w_out, op,
-                                                                  st);
-  else
-    e = dtype == WOLF_C64
-            ? wolf::launch_operator_dense<float2>(n, n_fft, (const float2*)w_in, (float2*)w_out, (float2*)work, op, st)
-            : wolf::launch_operator_dense<double2>(n, n_fft, (const double2*)w_in, (double2*)w_out, (double2*)work, op,
-                                                   st);
+  const hipError_t e =
+      dtype == WOLF_C64
+          ? wolf::launch_operator_padded<float2>(n, n_fft, (const float2*)w_in, (float2*)w_out, op, st)
+          : wolf::launch_operator_padded<double2>(n, n_fft, (const double2*)w_in, (double2*)w_out, op, st);
   return launched(e, who);
 }
 

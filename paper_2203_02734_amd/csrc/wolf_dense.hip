@@ -3,16 +3,10 @@
 //
 // Along one axis the operator is
 //   y[k] = post[k] sum_n e^{SIGN 2 pi i (k - N/2)(n - N/2) / N_z} pre[n] x[n],   k, n in [0, N),
-// the N central outputs of the centred N_z-point DFT of the N inputs embedded in N_z - N zeros. The
-// index (k - N/2)(n - N/2) mod N_z is exact in integers, and the table of the N_z roots of unity is
-// built in FP64. There is no FFT here: each axis is a dense product of the N x N matrix (generated
-// from the table, never stored) with the N-point lines of the array, tiled like a GEMM (64 x 64
-// outputs per tile on the matrix cores in the 3M form, 16 inputs per LDS stage) on a persistent grid
-// that builds the tables once per workgroup. The four axes run as four passes that alternate between the
-// output and a work buffer.
-//   COLS: a strided axis (stride S); the lines of one batch o are S contiguous columns:
-//         out[o N S + k S + c] from in[o N S + n S + c], tiles of 64 k x 64 c.
-//   !COLS: the contiguous axis: out[r N + k] from in[r N + n], tiles of 64 r x 64 k.
+// the N central outputs of the centred N_z-point DFT of the N inputs embedded in N_z - N zeros. The four
+// axes run as four passes, each over lines of N points: zero-padded FFTs for the lengths that have a split
+// (k_axis_pad, k_axis_pad_fold), a mirrored dense product on the matrix cores for every other N_z
+// (k_axis_mirror).
 #include "wolf_device.hpp"
 #include "wolf_internal.hpp"
 #include "wolf_mfma.hpp"
@@ -22,179 +16,250 @@ namespace wolf {
 constexpr int kDenseMaxNz = 2048;
 constexpr int kDenseMaxN = 256;
 
-struct DenseAxis {
-  long long S;       // stride of the axis (COLS), columns per batch
-  long long outer;   // batches (COLS)
-  long long rows;    // lines (!COLS)
-  long long ctiles;  // column tiles per batch (COLS)
-  int n, nz;
+// Lines of one pass: `outer` blocks (stride outer_stride) of ncols lines each (stride col_stride);
+// the transformed axis has stride axis_stride. tiles_per_outer and tiles are filled at launch.
+struct PadJob {
+  long long outer, outer_stride, axis_stride, col_stride, ncols;
+  int n, s;
+  Chirp pre, post;
+  long long tiles_per_outer, tiles;
 };
 
-__device__ __forceinline__ int dense_index(int k, int n, int c, int nz) {
-  int m = ((k - c) * (n - c)) % nz;
-  return m < 0 ? m + nz : m;
+// Tiles of a pass in XCD order. The hardware deals consecutive workgroups to the 8 XCDs in turn, and with
+// the plain grid-stride order neighbouring tiles ran on different XCDs: where a line's rows are not
+// 128-byte aligned (N = 200: 1600 B), two neighbouring tiles share the cache lines at their boundary, and
+// each XCD fetched those lines again. Here XCD x takes a contiguous share of the tiles, in proportion to
+// its workgroups (b < G with b mod 8 = x), and its workgroups stride through that share, so neighbouring
+// tiles run at the same time on one XCD and meet in its L2. A partition of [0, tiles) for any grid size.
+struct TileRange {
+  long long first, end, step;
+};
+__device__ __forceinline__ TileRange xcd_tiles(long long tiles) {
+  const long long G = gridDim.x, x = blockIdx.x % 8, r = G % 8;
+  const long long below = (G / 8) * x + (r < x ? r : x);             // workgroups on XCDs 0 .. x-1
+  const long long upto = (G / 8) * (x + 1) + (r < x + 1 ? r : x + 1);  // ... on XCDs 0 .. x
+  return TileRange{tiles * below / G + blockIdx.x / 8, tiles * upto / G, upto - below};
 }
 
-template <class T, bool COLS, int SIGN>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 4 : 2))) void k_dense_axis(
-    const T* __restrict__ in, T* __restrict__ out, DenseAxis d, Chirp pre, Chirp post, double scale) {
+// ---------------------------------------------------------------------------------------------
+// The dense product for the lengths without an FFT split, halved by the mirror symmetry of the kernel. With
+// m = n - N/2, q = k - N/2, z = pre x and c = N/2 (z[c] = 0: the grid ends at c - 1),
+//   E[q] = sum_{m=0}^{c} cos(2 pi q m / N_z) (z[m] + z[-m])   (m = 0: z[0]),
+//   O[q] = sum_{m=1}^{c} SIGN sin(2 pi q m / N_z) (z[m] - z[-m]),
+//   y[q] = post (E[q] + i O[q]),   y[-q] = post (E[q] - i O[q]),   q = 0 .. c.
+// Real matrices of half the size on complex data: 2 N real flops per element and axis on the matrix cores,
+// against 6 N for the whole complex matrix in the 3M form (and shorter sums).
+// A wavefront owns 16 lines. The lane layout of the MFMA operand of the data (line l % 16, contraction index
+// 4 j + l / 16) is the layout of the loads: a lane loads z[m] and z[-m] of its line for m = 4 j + l / 16,
+// forms the sum and the difference in place and keeps them for every output tile, so there is no exchange
+// between lanes, no staging and no barrier in the loop; the wavefronts of a CU run out of step, one on its
+// loads while another is on the matrix cores. The matrix operand is read from an LDS table of the N_z roots
+// (FP64-built), whose index q m mod N_z is exact and steps by 4 q mod N_z. All of a line's loads are consumed
+// before its first store, so dst may be src.
+//   !CONTIG (strided axis): the data is the B operand (16 neighbouring lines across the lanes), so the loads and
+//           the stores of a row are runs of 16 elements.
+//   CONTIG: the data is the A operand: a store is a run of 16 outputs along the line.
+// Bound: memory at N <= 128 or so, the FP32 matrix cores above. N = 150 unpadded, complex64: 29.9 -> 9.2 ms (4 passes,
+// 3.5 TB/s moved), error against FP64 5.0e-7 -> 3.2e-7; before, a 64 x 64-tiled complex product generated its
+// matrix tile by tile into LDS behind two barriers per 16 steps.
+// KJ: contraction steps of four (c + 1 <= 4 KJ), at compile time since the data sits in registers. The wavefronts
+// per SIMD that the registers allow are given to the compiler (data: 4 KJ words per lane in complex64, 8 KJ in
+// complex128).
+// ---------------------------------------------------------------------------------------------
+template <class T, int KJ> constexpr int mirror_waves() {
+  const int need = (int)(sizeof(T) / 2) * KJ + (sizeof(T) == 8 ? 56 : 74);
+  const int w = 512 / need;
+  return w < 1 ? 1 : (w > 6 ? 6 : w);
+}
+
+// Complex elements of global memory as plain vectors, so that a pointer made opaque keeps its address space.
+template <class T> struct GlobalElem;
+template <> struct GlobalElem<float2> { typedef float V __attribute__((ext_vector_type(2))); };
+template <> struct GlobalElem<double2> { typedef double V __attribute__((ext_vector_type(2))); };
+template <class T> using GlobalPtr = __attribute__((address_space(1))) typename GlobalElem<T>::V*;
+using GlobalBytes = __attribute__((address_space(1))) char*;
+
+// Hides how a wavefront-uniform pointer was formed, so that the steps of an unrolled chain of rows stay one scalar
+// addition each (folded, they were kept as loop-invariant offsets across tiles: 60-170 spilled registers).
+template <class P> __device__ __forceinline__ void opaque(P& p) { asm("" : "+s"(p)); }
+
+// The element `off` bytes past a pointer (a wavefront-uniform one and 32 bits per lane: one addressing mode).
+template <class T> __device__ __forceinline__ GlobalPtr<T> byte_at(GlobalPtr<T> p, unsigned off) {
+  return (GlobalPtr<T>)((GlobalBytes)p + off);
+}
+template <class T> __device__ __forceinline__ T load_elem(GlobalPtr<T> p) {
+  const auto v = *p;
+  return T{v.x, v.y};
+}
+template <class T> __device__ __forceinline__ void store_elem(GlobalPtr<T> p, const T& v) {
+  *p = typename GlobalElem<T>::V{v.x, v.y};
+}
+
+template <class T, int KJ, bool CONTIG>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mirror_waves<T, KJ>()))) void k_axis_mirror(
+    const T* src, T* dst, PadJob j, int nz, int sign, double scale) {
   using R = typename real_of<T>::type;
-  using G = MTile<64>;
-  constexpr int TM = 64, TN = 64, TK = 16;
-  __shared__ T tw[kDenseMaxNz];
-  __shared__ T tpre[kDenseMaxN], tpost[kDenseMaxN];
-  __shared__ R ar[TK][G::LDA], ai[TK][G::LDA], br[TK][G::LDB], bi[TK][G::LDB];
-  const int tid = threadIdx.x, lane = tid % 64;
-  const int wv = __builtin_amdgcn_readfirstlane(tid / 64);  // wavefront-uniform
-  const int row0 = (wv / G::WC) * 32, col0 = (wv % G::WC) * 32;
-  const int n = d.n, nz = d.nz, c0 = n / 2;
-  for (int i = tid; i < nz; i += 256) tw[i] = twiddle_entry<T, SIGN>(i, nz);
-  for (int i = tid; i < n; i += 256) {
-    tpre[i] = chirp_entry<T>(pre, i, n);
-    tpost[i] = chirp_entry<T>(post, i, n);
+  using V = typename Mfma<T>::V;
+  constexpr unsigned EB = sizeof(T);
+  constexpr int kSure = KJ == 5 ? 0 : KJ - 4;  // steps whose rows lie inside the data for every N of the bucket
+  constexpr int RG = sizeof(T) == 8 ? 4 : 1, RI = sizeof(T) == 8 ? 1 : 4;  // Mfma<T>::row = RG (l / 16) + RI i
+  extern __shared__ char mirror_lds[];
+  T* tw = reinterpret_cast<T*>(mirror_lds);  // (cos, SIGN sin) of the N_z roots
+  T* tpre = tw + nz;          // pre at middle + m, m in [-4 KJ, 4 KJ), zero outside the data
+  T* tpost = tpre + 8 * KJ;
+  const int n = j.n, c = n / 2;
+  for (int i = threadIdx.x; i < nz; i += 256) {
+    double s, co;
+    sincospi(2.0 * (double)i / (double)nz, &s, &co);
+    tw[i] = T{(R)co, (R)(sign * s)};
   }
+  for (int i = threadIdx.x; i < 8 * KJ; i += 256) {
+    const int m = i - 4 * KJ;
+    tpre[i] = m >= -c && m < c ? chirp_entry<T>(j.pre, c + m, n) : T{(R)0, (R)0};
+  }
+  for (int i = threadIdx.x; i < n; i += 256) tpost[i] = chirp_entry<T>(j.post, i, n);
   __syncthreads();
-  const T zero{(R)0, (R)0};
-  const long long ktiles = (n + TM - 1) / TM;
-  const long long tiles = COLS ? d.outer * d.ctiles * ktiles : ((d.rows + TM - 1) / TM) * ktiles;
-  // Persistent grid: the tables above are built once per workgroup, then it takes every
-  // gridDim-th tile.
-  for (long long t = blockIdx.x; t < tiles; t += gridDim.x) {
-    long long o = 0, i0, j0;
-    if constexpr (COLS) {
-      const long long kt = t % ktiles, rest = t / ktiles;
-      o = rest / d.ctiles;
-      j0 = (rest - o * d.ctiles) * TN;  // columns c
-      i0 = kt * TM;                      // outputs k
-    } else {
-      i0 = (t / ktiles) * TM;            // lines r
-      j0 = (t % ktiles) * TN;            // outputs k
+  const int lane = threadIdx.x % 64, l16 = lane % 16, g = lane / 16;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int lines = (int)(j.outer * j.ncols), ncols = (int)j.ncols;  // at most N^3 lines
+  const int kj = c / 4 + 1, rts = c / 16 + 1;  // steps and output tiles in use
+  const unsigned unz = (unsigned)nz;
+  const long long as = j.axis_stride;
+  const R rscale = (R)scale;
+  const TileRange tr = xcd_tiles(j.tiles);
+  for (long long u = tr.first; u < tr.end; u += tr.step) {
+    const int line0 = ((int)u * 4 + wv) * 16;
+    if (line0 >= lines) continue;  // no barrier in the loop
+    // Addresses: a uniform base (the wavefront's first line, at its middle row) and a 32-bit byte offset per lane.
+    // The lines of a wavefront may run into the next block; their offsets stay below outer_stride + 16 elements.
+    const int o0 = line0 / ncols, col0 = line0 - o0 * ncols;
+    const long long base0 = (long long)o0 * j.outer_stride + (long long)col0 * j.col_stride + (long long)c * as;
+    const bool line_ok = line0 + l16 < lines;
+    unsigned lofs = 0;  // this lane's line; lanes past the last line work on the first (not stored)
+    if (line_ok) {
+      const int ln = line0 + l16, o = ln / ncols;
+      lofs = (unsigned)((long long)(o - o0) * j.outer_stride + (long long)(ln - o * ncols - col0) * j.col_stride) * EB;
     }
-    const long long base = o * (long long)n * d.S;
-    CTile<T> acc;
-    ctile_zero(acc);
-    for (int n0 = 0; n0 < n; n0 += TK) {
-      T raw[4];  // this thread's four elements of the array tile, all loads issued first
+    T zp[KJ], zm[KJ];  // z[m], z[-m], then their sum and difference
+    {
+      const unsigned gofs = (unsigned)g * (unsigned)(as * EB);
+      GlobalPtr<T> mid = (GlobalPtr<T>)const_cast<T*>(src) + base0;
+      GlobalPtr<T> up = mid, down = mid - 3 * as;  // rows c + 4 t and c - 4 t - 3
+      const unsigned vu = lofs + gofs, vd = lofs + (3u * (unsigned)(as * EB) - gofs);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int e = tid + 256 * q;
-        if constexpr (COLS) {
-          const int kk = e / TN, jj = e % TN;
-          const long long gc = j0 + jj;
-          const int gn = n0 + kk;
-          raw[q] = load_or_first(in, gc < d.S && gn < n, base + (long long)gn * d.S + gc);
-        } else {
-          const int ii = e / TK, kk = e % TK;
-          const long long gi = i0 + ii;
-          const int gn = n0 + kk;
-          raw[q] = load_or_first(in, gi < d.rows && gn < n, gi * n + gn);
+      for (int t = 0; t < KJ; ++t) {
+        const int m = 4 * t + g;
+        if (t < kSure) {
+          zp[t] = load_elem<T>(byte_at<T>(up, vu));
+          zm[t] = load_elem<T>(byte_at<T>(down, vd));
+        } else {  // rows outside the data read the middle row; their entries of tpre are zero
+          zp[t] = load_elem<T>(m < c ? byte_at<T>(up, vu) : byte_at<T>(mid, lofs));
+          zm[t] = load_elem<T>(m <= c ? byte_at<T>(down, vd) : byte_at<T>(mid, lofs));
         }
+        up += 4 * as;
+        down -= 4 * as;
+        opaque(up);
+        opaque(down);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      // A (TM x TK): the DFT matrix (COLS) or the pre-multiplied lines (!COLS); B (TK x TN): the
-      // pre-multiplied columns (COLS) or the DFT matrix (!COLS). Staged as re / im planes.
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int e = tid + 256 * q;
-        const int ii = e / TK, kk = e % TK;
-        const long long gi = i0 + ii;
-        const int gn = n0 + kk;
-        T v = zero;
-        if constexpr (COLS) {
-          if (gi < n && gn < n) v = tw[dense_index((int)gi, gn, c0, nz)];
-        } else {
-          const T x = cmul(raw[q], tpre[gn < n ? gn : 0]);
-          v = keep_or_zero(gi < d.rows && gn < n, x);
-        }
-        ar[kk][ii] = v.x;
-        ai[kk][ii] = v.y;
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int e = tid + 256 * q;
-        T v = zero;
-        int kk, jj;
-        if constexpr (COLS) {
-          kk = e / TN;
-          jj = e % TN;
-          const long long gc = j0 + jj;
-          const int gn = n0 + kk;
-          const T x = cmul(raw[q], tpre[gn < n ? gn : 0]);
-          v = keep_or_zero(gc < d.S && gn < n, x);
-        } else {
-          jj = e / TK;
-          kk = e % TK;
-          const long long gk = j0 + jj;
-          const int gn = n0 + kk;
-          if (gk < n && gn < n) v = tw[dense_index((int)gk, gn, c0, nz)];
-        }
-        br[kk][jj] = v.x;
-        bi[kk][jj] = v.y;
-      }
-      __syncthreads();
-      ctile_mfma16<T, G::LDA, G::LDB>(acc, ar, ai, br, bi, row0, col0, lane);
-      __syncthreads();
     }
+    const T* const pup = tpre + 4 * KJ + g;
+    const T* const pdn = tpre + 4 - g;  // middle - g - 4 (KJ - 1)
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
+    for (int t = 0; t < KJ; ++t) {
+      const T a = cmul(zp[t], pup[4 * t]);
+      T b = cmul(zm[t], pdn[4 * (KJ - 1 - t)]);
+      if (t == 0) b = keep_or_zero(g > 0, b);  // m = 0 is one row
+      zp[t] = cadd(a, b);
+      zm[t] = csub(a, b);
+      if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    // The loads above are consumed here: the stores below may overwrite src.
+    // Store addresses: the lanes' positions within an output tile, rows upwards and downwards from the middle.
+    GlobalPtr<T> dup = (GlobalPtr<T>)dst + base0, ddn = dup - (CONTIG ? 15 : 15 * as);
+    unsigned su, sd;
+    if constexpr (CONTIG) {  // line RG g + RI i, output l16
+      su = ((unsigned)(RG * g) * (unsigned)j.col_stride + (unsigned)l16) * EB;
+      sd = ((unsigned)(RG * g) * (unsigned)j.col_stride + (unsigned)(15 - l16)) * EB;
+    } else {  // output RG g + RI i, line l16
+      su = lofs + (unsigned)(RG * g) * (unsigned)(as * EB);
+      sd = lofs + (unsigned)(15 - RI * 3 - RG * g) * (unsigned)(as * EB);
+    }
+    int rt = 0;
+    do {  // at least one tile: the sums above stay ahead of the loop
+      const unsigned q = (unsigned)(16 * rt + l16);
+      unsigned idx = (q * (unsigned)g) % unz;
+      const unsigned step = (4u * q) % unz;
+      V er{0, 0, 0, 0}, ei{0, 0, 0, 0}, orr{0, 0, 0, 0}, oi{0, 0, 0, 0};
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const long long gi = i0 + row0 + 16 * r + Mfma<T>::row(lane, i), gj = j0 + col0 + 16 * q + lane % 16;
-          const T a{acc.re(r, q, i), acc.im(r, q, i)};
-          if constexpr (COLS) {
-            if (gi < n && gj < d.S) {
-              const T v = cmul(a, tpost[gi]);
-              out[base + gi * d.S + gj] = T{(R)(scale * v.x), (R)(scale * v.y)};
-            }
+      for (int t = 0; t < KJ; ++t) {
+        if (t + 4 <= KJ || t < kj) {  // the last steps of a bucket may lie past the data
+          const T w = tw[idx];
+          if constexpr (CONTIG) {
+            er = Mfma<T>::mac(zp[t].x, w.x, er);
+            ei = Mfma<T>::mac(zp[t].y, w.x, ei);
+            orr = Mfma<T>::mac(zm[t].x, w.y, orr);
+            oi = Mfma<T>::mac(zm[t].y, w.y, oi);
           } else {
-            if (gi < d.rows && gj < n) {
-              const T v = cmul(a, tpost[gj]);
-              out[gi * n + gj] = T{(R)(scale * v.x), (R)(scale * v.y)};
-            }
+            er = Mfma<T>::mac(w.x, zp[t].x, er);
+            ei = Mfma<T>::mac(w.x, zp[t].y, ei);
+            orr = Mfma<T>::mac(w.y, zm[t].x, orr);
+            oi = Mfma<T>::mac(w.y, zm[t].y, oi);
           }
+          idx += step;
+          idx = min(idx, idx - unz);  // idx mod N_z (the difference wraps to a large value below N_z)
         }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int k = 16 * rt + (CONTIG ? l16 : RG * g + RI * i);
+        const bool ok = k <= c && (CONTIG ? line0 + RG * g + RI * i < lines : line_ok);
+        const T yp{er[i] - oi[i], ei[i] + orr[i]}, ym{er[i] + oi[i], ei[i] - orr[i]};
+        // Downwards the row (or element) 15 - RG g - RI i counts from the tile's last one.
+        const GlobalPtr<T> pu = dup + (long long)(RI * i) * (CONTIG ? j.col_stride : as);
+        const GlobalPtr<T> pd = ddn + (CONTIG ? (long long)(RI * i) * j.col_stride : (long long)(RI * (3 - i)) * as);
+        if (ok && k < c) store_elem<T>(byte_at<T>(pu, su), cscale(cmul(yp, tpost[c + k]), rscale));
+        if (ok && k > 0) store_elem<T>(byte_at<T>(pd, sd), cscale(cmul(ym, tpost[c - k]), rscale));
+      }
+      dup += CONTIG ? 16 : 16 * as;
+      ddn -= CONTIG ? 16 : 16 * as;
+      opaque(dup);
+      opaque(ddn);
+    } while (++rt < rts);
   }
 }
 
-template <class T, bool COLS>
-static hipError_t launch_dense_axis(const T* in, T* out, const DenseAxis& d, int sign, const Chirp& pre,
-                                    const Chirp& post, double scale, hipStream_t st) {
-  const long long ktiles = (d.n + 63) / 64;
-  const long long tiles = COLS ? d.outer * d.ctiles * ktiles : ((d.rows + 63) / 64) * ktiles;
-  const long long grid = tiles < 2048 ? tiles : 2048;  // a few resident workgroups per CU
-  if (grid < 1) return hipSuccess;
-  if (sign < 0)
-    hipLaunchKernelGGL((k_dense_axis<T, COLS, -1>), dim3((unsigned)grid), dim3(256), 0, st, in, out, d, pre, post,
-                       scale);
+template <class T, int KJ>
+static hipError_t launch_mirror_kj(const T* src, T* dst, const PadJob& j, int nz, int sign, double scale,
+                                   hipStream_t st) {
+  // A persistent grid of a few workgroups per CU, which build their tables once.
+  const unsigned grid = (unsigned)(j.tiles < 2048 ? j.tiles : 2048);
+  const size_t lds = (size_t)(nz + 8 * KJ + j.n) * sizeof(T);
+  if (j.axis_stride == 1)
+    hipLaunchKernelGGL((k_axis_mirror<T, KJ, true>), dim3(grid), dim3(256), lds, st, src, dst, j, nz, sign, scale);
   else
-    hipLaunchKernelGGL((k_dense_axis<T, COLS, +1>), dim3((unsigned)grid), dim3(256), 0, st, in, out, d, pre, post,
-                       scale);
+    hipLaunchKernelGGL((k_axis_mirror<T, KJ, false>), dim3(grid), dim3(256), lds, st, src, dst, j, nz, sign, scale);
   return hipGetLastError();
 }
 
-bool dense_supported(int n, int nz) { return n >= 2 && n <= kDenseMaxN && n % 2 == 0 && nz >= n && nz <= kDenseMaxNz; }
-
-// in -> (j2) work -> (i2) out -> (j1) work -> (i1) out. in == out is allowed (the first pass reads in
-// completely before the second writes out); work must not overlap either.
+// The smallest instantiated KJ that holds the N/8 + 1 steps of the axis.
 template <class T>
-hipError_t launch_operator_dense(int n, int nz, const T* in, T* out, T* work, const OperatorTables& op,
-                                 hipStream_t st) {
-  if (!dense_supported(n, nz)) return hipErrorInvalidValue;
-  const long long N = n, NN = N * N, NNN = NN * N;
-  hipError_t e;
-  DenseAxis d{};
-  d.n = n;
-  d.nz = nz;
-  d.rows = NNN;
-  if ((e = launch_dense_axis<T, false>(in, work, d, op.sign2, op.pre2, op.post2, 1.0, st)) != hipSuccess) return e;
-  d = DenseAxis{N, NN, 0, (N + 63) / 64, n, nz};  // i2: stride N, N^2 batches
-  if ((e = launch_dense_axis<T, true>(work, out, d, op.sign2, op.pre2, op.post2, 1.0, st)) != hipSuccess) return e;
-  d = DenseAxis{NN, N, 0, (NN + 63) / 64, n, nz};  // j1: stride N^2, N batches
-  if ((e = launch_dense_axis<T, true>(out, work, d, op.sign1, op.pre1, op.post1, 1.0, st)) != hipSuccess) return e;
-  d = DenseAxis{NNN, 1, 0, (NNN + 63) / 64, n, nz};  // i1: stride N^3, one batch
-  return launch_dense_axis<T, true>(work, out, d, op.sign1, op.pre1, op.post1, op.scale, st);
+static hipError_t launch_mirror_axis(int nz, const T* src, T* dst, PadJob j, int sign, double scale, hipStream_t st) {
+  j.tiles_per_outer = 0;
+  j.tiles = (j.outer * j.ncols + 63) / 64;  // units of four wavefronts of 16 lines
+  if (j.tiles < 1) return hipSuccess;
+  const int kj = j.n / 8 + 1;
+  if (kj <= 5) return launch_mirror_kj<T, 5>(src, dst, j, nz, sign, scale, st);
+  if (kj <= 9) return launch_mirror_kj<T, 9>(src, dst, j, nz, sign, scale, st);
+  if (kj <= 13) return launch_mirror_kj<T, 13>(src, dst, j, nz, sign, scale, st);
+  if (kj <= 17) return launch_mirror_kj<T, 17>(src, dst, j, nz, sign, scale, st);
+  if (kj <= 21) return launch_mirror_kj<T, 21>(src, dst, j, nz, sign, scale, st);
+  if (kj <= 25) return launch_mirror_kj<T, 25>(src, dst, j, nz, sign, scale, st);
+  if (kj <= 29) return launch_mirror_kj<T, 29>(src, dst, j, nz, sign, scale, st);
+  return launch_mirror_kj<T, 33>(src, dst, j, nz, sign, scale, st);
 }
+
+bool dense_supported(int n, int nz) { return n >= 2 && n <= kDenseMaxN && n % 2 == 0 && nz >= n && nz <= kDenseMaxNz; }
 
 // ---------------------------------------------------------------------------------------------
 // The same operator with a zero-padded FFT when N_z is a power of two (<= 1024). Per line, the N
@@ -206,15 +271,6 @@ hipError_t launch_operator_dense(int n, int nz, const T* in, T* out, T* work, co
 // N_z = N1 N2 of the slab and axis passes. A workgroup owns C lines (one LDS exchange) and loops
 // over tiles of lines; it reads its lines before a barrier and writes them after, so dst may be src.
 // ---------------------------------------------------------------------------------------------
-// Lines of one pass: `outer` blocks (stride outer_stride) of ncols lines each (stride col_stride);
-// the transformed axis has stride axis_stride. tiles_per_outer and tiles are filled at launch.
-struct PadJob {
-  long long outer, outer_stride, axis_stride, col_stride, ncols;
-  int n, s;
-  Chirp pre, post;
-  long long tiles_per_outer, tiles;
-};
-
 // Split of an N_z-point line transform over L2 threads that hold L1 = Q L2 elements each
 // (N_z = Q L2^2), and the C lines of a workgroup (L2 C <= 256 threads, at most one wavefront per
 // SIMD). Powers of two take the split of the slab and axis passes and C = 256 / L2. Other lengths
@@ -270,22 +326,6 @@ template <class T, int NZ> constexpr int pad_groups() {
   using S = LineCfg<T, NZ>;
   constexpr bool phases_fit_more = kMaxLds / pad_lds_bytes<T, NZ, S::Q>() < kMaxLds / pad_lds_bytes<T, NZ, 1>();
   return (sizeof(T) == 16 && S::L1 <= 16 && phases_fit_more) ? 1 : S::Q;
-}
-
-// Tiles of a pass in XCD order. The hardware deals consecutive workgroups to the 8 XCDs in turn, and with
-// the plain grid-stride order neighbouring tiles ran on different XCDs: where a line's rows are not
-// 128-byte aligned (N = 200: 1600 B), two neighbouring tiles share the cache lines at their boundary, and
-// each XCD fetched those lines again. Here XCD x takes a contiguous share of the tiles, in proportion to
-// its workgroups (b < G with b mod 8 = x), and its workgroups stride through that share, so neighbouring
-// tiles run at the same time on one XCD and meet in its L2. A partition of [0, tiles) for any grid size.
-struct TileRange {
-  long long first, end, step;
-};
-__device__ __forceinline__ TileRange xcd_tiles(long long tiles) {
-  const long long G = gridDim.x, x = blockIdx.x % 8, r = G % 8;
-  const long long below = (G / 8) * x + (r < x ? r : x);             // workgroups on XCDs 0 .. x-1
-  const long long upto = (G / 8) * (x + 1) + (r < x + 1 ? r : x + 1);  // ... on XCDs 0 .. x
-  return TileRange{tiles * below / G + blockIdx.x / 8, tiles * upto / G, upto - below};
 }
 
 template <class T, int NZ, int SIGN, bool CONTIG>
@@ -599,54 +639,50 @@ bool pad_fft_supported(int n, int nz) {
   return n >= 2 && n <= kDenseMaxN && n % 2 == 0 && nz >= n && line_length_supported(nz);
 }
 
-// Four passes: j2 (lines along the contiguous axis, line stride N), i2, j1, i1. The first reads `in`
-// and writes `out`; the others work in place on `out`. The tables carry the (-1)^n centring.
+// One pass over the lines of `j`: an FFT where N_z has a split, else the mirrored dense product. The last
+// pass of the operator also applies the scale: in the FFT's output chirp, or in the product's store.
 template <class T>
-hipError_t launch_operator_padfft(int n, int nz, const T* in, T* out, const OperatorTables& op, hipStream_t st) {
-  if (!pad_fft_supported(n, nz)) return hipErrorInvalidValue;
+static hipError_t launch_line_axis(int nz, bool fft, const T* src, T* dst, PadJob j, int sign, double scale,
+                                   hipStream_t st) {
+  if (!fft) return launch_mirror_axis<T>(nz, src, dst, j, sign, scale, st);
+  j.post.scale = scale;
+  return launch_pad_axis<T>(nz, src, dst, j, sign, st);
+}
+
+// Four passes: j2 (lines along the contiguous axis, line stride N), i2, j1, i1. The first reads `in`
+// and writes `out`; the others work in place on `out`. The FFT passes' tables carry the (-1)^n centring, the
+// dense ones' do not (the centring is exact in the index).
+template <class T>
+hipError_t launch_operator_padded(int n, int nz, const T* in, T* out, const OperatorTables& op, hipStream_t st) {
+  if (!dense_supported(n, nz)) return hipErrorInvalidValue;
+  const bool fft = pad_fft_supported(n, nz);
   const long long N = n, NN = N * N, NNN = NN * N;
   const int sft = (nz - n) / 2;
-  Chirp post1 = op.post1;
-  post1.scale = op.scale;
   hipError_t e;
   // PadJob{outer, outer_stride, axis_stride, col_stride, ncols, n, s, pre, post}
-  const PadJob j2{1, 0, 1, N, NNN, n, sft, op.pre2, op.post2, 0, 0};     // contiguous axis: lines of N
-  const PadJob i2{NN, NN, N, 1, N, n, sft, op.pre2, op.post2, 0, 0};    // stride N, N^2 blocks of N lines
-  const PadJob j1{N, NNN, NN, 1, NN, n, sft, op.pre1, op.post1, 0, 0};  // stride N^2, N blocks of N^2 lines
-  const PadJob i1{1, 0, NNN, 1, NNN, n, sft, op.pre1, post1, 0, 0};     // stride N^3, N^3 lines
+  const PadJob i1{1, 0, NNN, 1, NNN, n, sft, op.pre1, op.post1, 0, 0};  // stride N^3, N^3 lines
   // The j2, i2 and j1 passes run over groups of whole i1 planes of at most 256 MB, one group after the other,
   // so that each group's second and third passes find it in the memory-side cache; the i1 pass then runs over
   // the whole array. N = 200 padded to 512: 24.7 -> 23.1 ms in complex64 (groups of 4 planes); N = 256 to 512:
   // 66.4 -> 58.3 ms (1 plane); N = 200 to 512 in complex128: 47.5 -> 44.6 ms; N = 200 unpadded (with the tiles
   // in XCD order): 22.29 -> 22.03 ms.
   const long long P = (256ll << 20) / (NNN * (long long)sizeof(T));  // planes per group
-  if (P < N) {
-    const long long pg = P < 1 ? 1 : P;
-    for (long long i0 = 0; i0 < N; i0 += pg) {
-      const long long pp = i0 + pg <= N ? pg : N - i0, off = i0 * NNN;
-      const PadJob gj2{1, 0, 1, N, pp * NN, n, sft, op.pre2, op.post2, 0, 0};    // the group's lines of N
-      const PadJob gi2{pp * N, NN, N, 1, N, n, sft, op.pre2, op.post2, 0, 0};   // pp N blocks of N lines
-      const PadJob gj1{pp, NNN, NN, 1, NN, n, sft, op.pre1, op.post1, 0, 0};    // pp blocks of N^2 lines
-      if ((e = launch_pad_axis<T>(nz, in + off, out + off, gj2, op.sign2, st)) != hipSuccess) return e;
-      if ((e = launch_pad_axis<T>(nz, out + off, out + off, gi2, op.sign2, st)) != hipSuccess) return e;
-      if ((e = launch_pad_axis<T>(nz, out + off, out + off, gj1, op.sign1, st)) != hipSuccess) return e;
-    }
-    return launch_pad_axis<T>(nz, out, out, i1, op.sign1, st);
+  const long long pg = P < 1 ? 1 : (P < N ? P : N);
+  for (long long i0 = 0; i0 < N; i0 += pg) {
+    const long long pp = i0 + pg <= N ? pg : N - i0, off = i0 * NNN;
+    const PadJob j2{1, 0, 1, N, pp * NN, n, sft, op.pre2, op.post2, 0, 0};    // contiguous axis: lines of N
+    const PadJob i2{pp * N, NN, N, 1, N, n, sft, op.pre2, op.post2, 0, 0};   // stride N, blocks of N lines
+    const PadJob j1{pp, NNN, NN, 1, NN, n, sft, op.pre1, op.post1, 0, 0};    // stride N^2, blocks of N^2 lines
+    if ((e = launch_line_axis<T>(nz, fft, in + off, out + off, j2, op.sign2, 1.0, st)) != hipSuccess) return e;
+    if ((e = launch_line_axis<T>(nz, fft, out + off, out + off, i2, op.sign2, 1.0, st)) != hipSuccess) return e;
+    if ((e = launch_line_axis<T>(nz, fft, out + off, out + off, j1, op.sign1, 1.0, st)) != hipSuccess) return e;
   }
-  if ((e = launch_pad_axis<T>(nz, in, out, j2, op.sign2, st)) != hipSuccess) return e;
-  if ((e = launch_pad_axis<T>(nz, out, out, i2, op.sign2, st)) != hipSuccess) return e;
-  if ((e = launch_pad_axis<T>(nz, out, out, j1, op.sign1, st)) != hipSuccess) return e;
-  return launch_pad_axis<T>(nz, out, out, i1, op.sign1, st);
+  return launch_line_axis<T>(nz, fft, out, out, i1, op.sign1, op.scale, st);
 }
 
-template hipError_t launch_operator_padfft<float2>(int, int, const float2*, float2*, const OperatorTables&,
+template hipError_t launch_operator_padded<float2>(int, int, const float2*, float2*, const OperatorTables&,
                                                    hipStream_t);
-template hipError_t launch_operator_padfft<double2>(int, int, const double2*, double2*, const OperatorTables&,
+template hipError_t launch_operator_padded<double2>(int, int, const double2*, double2*, const OperatorTables&,
                                                     hipStream_t);
-
-template hipError_t launch_operator_dense<float2>(int, int, const float2*, float2*, float2*, const OperatorTables&,
-                                                  hipStream_t);
-template hipError_t launch_operator_dense<double2>(int, int, const double2*, double2*, double2*,
-                                                   const OperatorTables&, hipStream_t);
 
 }  // namespace wolf

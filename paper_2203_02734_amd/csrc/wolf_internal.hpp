@@ -120,17 +120,13 @@ hipError_t launch_dft2_batch(int n, T* data, long long count, int sign, hipStrea
 int axis_tile_cols(int n, int elem_bytes);  // columns of an axis-pass tile
 int row_pass_rows(int n);  // rows per workgroup of the row pass
 
-// The operator for any even N and transform length N_z >= N (zero padding and crop), as four dense
-// axis passes (wolf_dense.hip). work: N^4 elements. Tables without the (-1)^n centring factor.
+// The operator for any even N and transform length N_z >= N (zero padding and crop), four passes over lines
+// (wolf_dense.hip): zero-padded FFTs for the lengths pad_fft_supported accepts (tables with the (-1)^n
+// centring factor), a mirrored dense product for any other (tables without it). in -> out, then in place.
 bool dense_supported(int n, int nz);
-// The same operator with zero-padded FFTs, for a power-of-two N_z <= 1024 (in -> out, then in place).
-// Tables with the (-1)^n centring factor.
 bool pad_fft_supported(int n, int nz);
 template <class T>
-hipError_t launch_operator_padfft(int n, int nz, const T* in, T* out, const OperatorTables& op, hipStream_t st);
-template <class T>
-hipError_t launch_operator_dense(int n, int nz, const T* in, T* out, T* work, const OperatorTables& op,
-                                 hipStream_t st);
+hipError_t launch_operator_padded(int n, int nz, const T* in, T* out, const OperatorTables& op, hipStream_t st);
 
 // Direct sum with the exact free-space kernel (wolf_direct.hip). work: direct_work_bytes(n, elem).
 template <class T>
