@@ -59,9 +59,12 @@ __device__ __forceinline__ TileRange xcd_tiles(long long tiles) {
 //   !CONTIG (strided axis): the data is the B operand (16 neighbouring lines across the lanes), so the loads and
 //           the stores of a row are runs of 16 elements.
 //   CONTIG: the data is the A operand: a store is a run of 16 outputs along the line.
-// Bound: memory at N <= 128 or so, the FP32 matrix cores above. N = 150 unpadded, complex64: 29.9 -> 9.2 ms (4 passes,
-// 3.5 TB/s moved), error against FP64 5.0e-7 -> 3.2e-7; before, a 64 x 64-tiled complex product generated its
-// matrix tile by tile into LDS behind two barriers per 16 steps.
+// Bound: memory up to N of about 150 (without its products the N = 150 pass takes 2.2 ms, without its loads and stores
+// 1.4 ms), the FP32 matrix cores above. N = 150 unpadded, complex64: 29.9 -> 8.5 ms (3.8 TB/s moved), N = 200 to
+// 210: 126 -> 29.9 ms; error against FP64 5.0e-7 -> 3.2e-7 at N = 150. Before, a 64 x 64-tiled complex product
+// generated its matrix tile by tile into LDS behind two barriers per 16 steps. Measured and not kept: the next
+// tile's loads issued ahead of the products (9.1 ms, half the wavefronts), 32 lines per wavefront with 16-byte
+// accesses (9.0 ms).
 // KJ: contraction steps of four (c + 1 <= 4 KJ), at compile time since the data sits in registers. The wavefronts
 // per SIMD that the registers allow are given to the compiler (data: 4 KJ words per lane in complex64, 8 KJ in
 // complex128).
@@ -185,11 +188,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mirror_wave
       su = lofs + (unsigned)(RG * g) * (unsigned)(as * EB);
       sd = lofs + (unsigned)(15 - RI * 3 - RG * g) * (unsigned)(as * EB);
     }
+    // Index of the root at step 0 and its increment per step, for output q = l16; both advance with the output tile.
+    unsigned idx0 = ((unsigned)l16 * (unsigned)g) % unz, step = (4u * (unsigned)l16) % unz;
+    const unsigned didx = (16u * (unsigned)g) % unz, dstep = 64u % unz;
+    auto wrap = [&](unsigned x) { return min(x, x - unz); };  // x mod N_z for x < 2 N_z (the difference wraps)
     int rt = 0;
     do {  // at least one tile: the sums above stay ahead of the loop
-      const unsigned q = (unsigned)(16 * rt + l16);
-      unsigned idx = (q * (unsigned)g) % unz;
-      const unsigned step = (4u * q) % unz;
+      unsigned idx = idx0;
       V er{0, 0, 0, 0}, ei{0, 0, 0, 0}, orr{0, 0, 0, 0}, oi{0, 0, 0, 0};
 #pragma unroll
       for (int t = 0; t < KJ; ++t) {
@@ -206,10 +211,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mirror_wave
             orr = Mfma<T>::mac(w.y, zm[t].x, orr);
             oi = Mfma<T>::mac(w.y, zm[t].y, oi);
           }
-          idx += step;
-          idx = min(idx, idx - unz);  // idx mod N_z (the difference wraps to a large value below N_z)
+          idx = wrap(idx + step);
         }
       }
+      idx0 = wrap(idx0 + didx);
+      step = wrap(step + dstep);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int k = 16 * rt + (CONTIG ? l16 : RG * g + RI * i);
@@ -232,8 +238,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mirror_wave
 template <class T, int KJ>
 static hipError_t launch_mirror_kj(const T* src, T* dst, const PadJob& j, int nz, int sign, double scale,
                                    hipStream_t st) {
-  // A persistent grid of a few workgroups per CU, which build their tables once.
-  const unsigned grid = (unsigned)(j.tiles < 2048 ? j.tiles : 2048);
+  // More workgroups than are resident (the last ones even out the CUs), each over several units, so that the tables
+  // are few: grids of 2048, 4096 and 16384 took 9.15, 9.07 and 8.90 ms at N = 150 in complex64, 2.00, 1.96 and
+  // 1.89 ms at N = 90 in complex128 (before the indices advanced by additions).
+  const unsigned grid = (unsigned)(j.tiles < 16384 ? j.tiles : 16384);
   const size_t lds = (size_t)(nz + 8 * KJ + j.n) * sizeof(T);
   if (j.axis_stride == 1)
     hipLaunchKernelGGL((k_axis_mirror<T, KJ, true>), dim3(grid), dim3(256), lds, st, src, dst, j, nz, sign, scale);
@@ -666,7 +674,9 @@ hipError_t launch_operator_padded(int n, int nz, const T* in, T* out, const Oper
   // the whole array. N = 200 padded to 512: 24.7 -> 23.1 ms in complex64 (groups of 4 planes); N = 256 to 512:
   // 66.4 -> 58.3 ms (1 plane); N = 200 to 512 in complex128: 47.5 -> 44.6 ms; N = 200 unpadded (with the tiles
   // in XCD order): 22.29 -> 22.03 ms.
-  const long long P = (256ll << 20) / (NNN * (long long)sizeof(T));  // planes per group
+  // The dense passes run over the whole array: their launches over a group end in a ragged last round of tiles
+  // (N = 200: 36.1 ms grouped, 32.0 ms whole; N = 150: 9.2 and 9.1 ms; N = 90 in complex128: 1.90 ms either way).
+  const long long P = fft ? (256ll << 20) / (NNN * (long long)sizeof(T)) : N;  // planes per group
   const long long pg = P < 1 ? 1 : (P < N ? P : N);
   for (long long i0 = 0; i0 < N; i0 += pg) {
     const long long pp = i0 + pg <= N ? pg : N - i0, off = i0 * NNN;
