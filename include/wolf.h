@@ -173,7 +173,8 @@ WOLF_API wolf_status wolf_propagate_lens(const void* w_in, void* w_out, int32_t 
  * the same arguments (pitch lambda z / (N pitch_m)), so the two results compare element by element;
  * their difference is the error of the Fresnel approximation for this source and distance.
  * The kernel does not separate into x and y: the cost is two dense complex products of size N^2
- * (2 N^6 complex multiply-adds), meant for N <= 64 (N = 128 is accepted).
+ * (2 N^6 complex multiply-adds, about a quarter of them from N = 16 on, where the mirror symmetry of the grids
+ * splits each product), meant for N <= 64 (N = 128 is accepted).
  *   w_in, w_out   device N^4 complex of `dtype`; w_in == w_out is allowed (partial overlap is not).
  *   work          device scratch of wolf_direct_work_bytes(n, dtype) bytes (two N^4 arrays),
  *                 overwritten, not overlapping w_in or w_out.
