@@ -193,10 +193,12 @@ __global__ __launch_bounds__(256) void k_rs_fold(const T* in, T* out, T* extra, 
 // On the matrix cores (FP32 for complex64, FP64 for complex128) in the 3M form: 64 x 64 outputs per
 // workgroup of four wavefronts (32 x 32 blocks), kk staged through double-buffered LDS 16 at a time, the
 // loads of step s + 1 issued before the products of step s. Out-of-range elements load as zero and are not stored.
-// Workgroups: each XCD takes a contiguous share of the 64-wide panels of F (or T1) and streams the matrices through its
-// L2 once for them; consecutive workgroups of an XCD share a matrix tile.
-// Bound: the matrix cores. N = 64: 1.22 and 1.39 ms in complex64 (90 and 81 TFLOP/s executed of 154), 3.45 and 3.18 ms in
-// complex128 (32 and 36 TFLOP/s of 72); the plain products took 4.2 and 10.7 ms each.
+// Workgroups: the pairs of a 64-wide panel of F (or T1) and a matrix tile are listed by groups of an eighth of the panels,
+// each group tile by tile, and each XCD takes an equal contiguous share of the list: it streams the matrices through its
+// L2 about once, and its consecutive workgroups share a matrix tile.
+// Bound: the matrix cores. N = 64: 1.13 and 1.24 ms in complex64 (97 and 91 TFLOP/s executed of 154), 2.04 and 2.28 ms in
+// complex128 (54 and 50 of 72); the plain products took 4.2 and 10.7 ms each. Stores of the operands that run along kk
+// are swizzled over the LDS banks (before: 3.45 and 3.18 ms in complex128).
 template <class T, bool FIRST>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 2))) void k_rs_gemm(
     const T* __restrict__ x, const T* __restrict__ h, T* __restrict__ y, T* __restrict__ extra, RsClasses cs,
@@ -208,9 +210,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
   const int tid = threadIdx.x, lane = tid % 64;
   const int wv = __builtin_amdgcn_readfirstlane(tid / 64);  // wavefront-uniform
   const int row0 = (wv / G::WC) * 32, col0 = (wv % G::WC) * 32;
-  const int xcd = (int)blockIdx.x % 8, at = (int)blockIdx.x / 8;
-  const int panel = xcd * per_xcd + at % per_xcd, tile = at / per_xcd;
-  if (panel >= panels) return;
+  const int xcd = (int)blockIdx.x % 8, total = panels * cs.tiles;
+  const int unit = (int)((long long)total * xcd / 8) + (int)blockIdx.x / 8;
+  if (unit >= (int)((long long)total * (xcd + 1) / 8)) return;
+  const int group = unit / (per_xcd * cs.tiles), first = group * per_xcd, in_group = unit - first * cs.tiles;
+  const int width = panels - first < per_xcd ? panels - first : per_xcd;
+  const int panel = first + in_group % width, tile = in_group / width;
   RsClass cl = cs.c[0];
 #pragma unroll
   for (int q = 1; q < 4; ++q)
@@ -269,19 +274,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     const int kk = tid % TK;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int ii = tid / TK + 16 * q;
+      const int ii = tid / TK + 16 * q, at = swizzled(kk, ii);
       const T v = keep_or_zero(o0 + ii < kk_n && k0 + kk < kk_n, rh[q]);
       if constexpr (FIRST) {
         const T u = keep_or_zero(p0 + ii < p_n && k0 + kk < kk_n, rx[q]);
-        ar[buf][kk][ii] = u.x;
-        ai[buf][kk][ii] = u.y;
-        br[buf][kk][ii] = v.x;
-        bi[buf][kk][ii] = v.y;
+        ar[buf][kk][at] = u.x;
+        ai[buf][kk][at] = u.y;
+        br[buf][kk][at] = v.x;
+        bi[buf][kk][at] = v.y;
       } else {
         const int kx = wv + 4 * q;
         const T u = keep_or_zero(p0 + lane < p_n && k0 + kx < kk_n, rx[q]);
-        ar[buf][kk][ii] = v.x;
-        ai[buf][kk][ii] = -v.y;
+        ar[buf][kk][at] = v.x;
+        ai[buf][kk][at] = -v.y;
         br[buf][kx][lane] = u.x;
         bi[buf][kx][lane] = u.y;
       }
@@ -296,7 +301,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
   for (int k0 = 0; k0 < kk_n; k0 += TK) {
     const bool more = k0 + TK < kk_n;
     if (more) fetch(k0 + TK);
-    ctile_mfma16<T, G::LDA, G::LDB>(acc, ar[buf], ai[buf], br[buf], bi[buf], row0, col0, lane);
+    ctile_mfma16<T, G::LDA, G::LDB, true, FIRST>(acc, ar[buf], ai[buf], br[buf], bi[buf], row0, col0, lane);
     if (more) stage(buf ^ 1, k0 + TK);
     __syncthreads();
     buf ^= 1;
@@ -327,7 +332,7 @@ static hipError_t launch_rs_gemm(const T* x, const T* h, T* y, T* extra, const R
                                  hipStream_t st) {
   const int lines = FIRST ? cs.n * cs.n : cs.slots * cs.slots;
   const int panels = (lines + 63) / 64, per_xcd = (panels + 7) / 8;
-  hipLaunchKernelGGL((k_rs_gemm<T, FIRST>), dim3((unsigned)(8 * per_xcd * cs.tiles)), dim3(256), 0, st, x, h, y, extra,
+  hipLaunchKernelGGL((k_rs_gemm<T, FIRST>), dim3((unsigned)(8 * ((panels * cs.tiles + 7) / 8))), dim3(256), 0, st, x, h, y, extra,
                      cs, panels, per_xcd, alpha);
   return hipGetLastError();
 }
@@ -344,8 +349,8 @@ hipError_t launch_direct(int n, const T* in, T* out, void* work, double pitch, d
   const long long nn = (long long)n * n, total = nn * nn;
   const double dx = lam * z / ((double)n * pitch);
   const double s = pitch * pitch * pitch * pitch;
-  // The mirrored form wherever it fits the work buffer of two N^4 arrays (N >= 16). N = 64: 8.4 ms plain, 2.56 mirrored
-  // in complex64, 21.4 and 6.9 ms in complex128; below N = 16 the products are a few tiles.
+  // The mirrored form wherever it fits the work buffer of two N^4 arrays (N >= 16). N = 64: 8.4 ms plain, 2.36 mirrored
+  // in complex64, 21.4 and 4.6 ms in complex128; below N = 16 the products are a few tiles.
   const bool mirrored = rs_mirror_elems(n) <= 2 * total;
   const RsClasses cs = rs_classes(n, mirrored);
   T* h = reinterpret_cast<T*>(work);

@@ -61,9 +61,15 @@ template <class T> __device__ __forceinline__ void ctile_zero(CTile<T>& c) {
     for (int q = 0; q < 2; ++q) c.t1[r][q] = c.t2[r][q] = c.t3[r][q] = V{0, 0, 0, 0};
 }
 
-// c += A B over the 16 staged values of the contraction index, for the wavefront block at (row0, col0).
+// Position of row (or column) i in the staged row kk of an operand whose stores run along kk (16 kk of one i per 16
+// lanes): with the plain position those stores hit 4 (FP32) or 2 (FP64) of the banks the wavefront could use; the
+// exchange within blocks of 16 spreads them over all, and leaves the reads (16 consecutive i of a kk) on distinct banks.
+__device__ __forceinline__ int swizzled(int kk, int i) { return i ^ (2 * (kk / 2)); }
+
+// c += A B over the 16 staged values of the contraction index, for the wavefront block at (row0, col0). SWA, SWB:
+// the operand's positions are swizzled.
 // Bit q of `cols` (wavefront-uniform) enables the 16 columns col0 + 16 q; a disabled block is left as is.
-template <class T, int LDA, int LDB>
+template <class T, int LDA, int LDB, bool SWA = false, bool SWB = false>
 __device__ __forceinline__ void ctile_mfma16(CTile<T>& c, const typename real_of<T>::type (*ar)[LDA],
                                              const typename real_of<T>::type (*ai)[LDA],
                                              const typename real_of<T>::type (*br)[LDB],
@@ -73,17 +79,18 @@ __device__ __forceinline__ void ctile_mfma16(CTile<T>& c, const typename real_of
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
     const int kk = ks * 4 + lane / 16, l16 = lane % 16;
+    const int la = SWA ? swizzled(kk, l16) : l16, lb = SWB ? swizzled(kk, l16) : l16;
     R xr[2], xi[2], xs[2], yr[2], yi[2], ys[2];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-      xr[r] = ar[kk][row0 + 16 * r + l16];
-      xi[r] = ai[kk][row0 + 16 * r + l16];
+      xr[r] = ar[kk][row0 + 16 * r + la];
+      xi[r] = ai[kk][row0 + 16 * r + la];
       xs[r] = xr[r] + xi[r];
     }
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      yr[q] = br[kk][col0 + 16 * q + l16];
-      yi[q] = bi[kk][col0 + 16 * q + l16];
+      yr[q] = br[kk][col0 + 16 * q + lb];
+      yi[q] = bi[kk][col0 + 16 * q + lb];
       ys[q] = yr[q] + yi[q];
     }
 #pragma unroll
