@@ -353,6 +353,31 @@ WOLF_API wolf_status wolf_fit_gradient(const void* ga, const float* imap, int32_
 WOLF_API int64_t wolf_fit_work_bytes(int32_t n, int32_t dtype);
 
 /*
+ * wolf_fit_forward -- S_B (Algorithm 4) of the propagated custom-map source W_A of wolf_fit_gradient (secondary source), as
+ * wolf_build_source, wolf_propagate_fresnel (or _farfield) and wolf_spectral_density give it in WOLF_C128, without an
+ * N^4 array: S_B depends on W_A only through sums over the difference of its two points, taken in FP64.
+ *   imap     device N*N float32.   sigma_g_m > 0 (may be +inf).
+ *   work     device scratch of wolf_fit_sums_work_bytes(n) bytes (overwritten).
+ *   corr     device, 16 (N/2 + 1) N bytes, written: the sums that wolf_fit_backward needs for d_sigma.
+ *   s_out    device, N*N float64.
+ */
+WOLF_API wolf_status wolf_fit_forward(const float* imap, int32_t n, double pitch_m, double sigma_g_m,
+                                      double wavelength_m, double z_m, int32_t farfield, void* work, void* corr,
+                                      double* s_out, void* stream);
+
+/*
+ * wolf_fit_backward -- gradients of a loss of S_B with respect to the map and sigma_g, given g_s = dL/dS_B: what
+ * wolf_propagate_adjoint_diag and wolf_fit_gradient give in WOLF_C128, without an N^4 array.
+ *   g_s      device, N*N float64.   corr: as wolf_fit_forward wrote it for the same arguments.
+ *   imap, d_imap, d_sigma   as wolf_fit_gradient.   work: wolf_fit_sums_work_bytes(n) bytes. N <= 128, sigma_g finite.
+ */
+WOLF_API wolf_status wolf_fit_backward(const double* g_s, const float* imap, int32_t n, double pitch_m,
+                                       double sigma_g_m, double wavelength_m, double z_m, int32_t farfield,
+                                       const void* corr, void* work, float* d_imap, double* d_sigma, void* stream);
+/* Bytes of the work buffer of both; -1 if N is not supported. */
+WOLF_API int64_t wolf_fit_sums_work_bytes(int32_t n);
+
+/*
  * wolf_chirp_table -- the FP64-built table of the quadratic-phase propagator q(z, xi) of
  * eq. (q_factor), along one axis: out[i] = exp(i pi (pitch (i - N/2))^2 / (lambda z)), i in [0, N).
  * The 2D propagator is out[i] * out[j]. It is the same table the propagation kernels build, minus

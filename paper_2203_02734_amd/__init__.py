@@ -33,7 +33,8 @@ EXPORTED = ["wolf_build_source", "wolf_propagate_fresnel", "wolf_propagate_farfi
             "wolf_fit_work_bytes", "wolf_coop_error_flag", "wolf_propagate_adjoint_diag", "wolf_batch_work_bytes",
             "wolf_propagate_lens", "wolf_propagate_direct", "wolf_direct_work_bytes",
             "wolf_propagate_padded", "wolf_propagate_polychromatic", "wolf_polychromatic_work_bytes",
-            "wolf_propagate_source", "wolf_memory_ceiling", "wolf_degree_of_coherence_noalloc"]
+            "wolf_propagate_source", "wolf_memory_ceiling", "wolf_degree_of_coherence_noalloc",
+            "wolf_fit_forward", "wolf_fit_backward", "wolf_fit_sums_work_bytes"]
 
 
 class WolfError(RuntimeError):
@@ -86,6 +87,8 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
         "wolf_autotune": [i32, i32, vp, i32, pd, vp],
         "wolf_diag_embed": [vp, i32, i32, vp, vp],
         "wolf_fit_gradient": [vp, vp, i32, f64, f64, i32, vp, vp, vp, vp],
+        "wolf_fit_forward": [vp, i32, f64, f64, f64, f64, i32, vp, vp, vp, vp],
+        "wolf_fit_backward": [vp, vp, i32, f64, f64, f64, f64, i32, vp, vp, vp, vp, vp],
         "wolf_memory_ceiling": [vp, ctypes.c_int64, i32, vp],
     }
     for name, args in sig.items():
@@ -101,6 +104,8 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.wolf_version.restype = i32
     lib.wolf_fit_work_bytes.argtypes = [i32, i32]
     lib.wolf_fit_work_bytes.restype = ctypes.c_int64
+    lib.wolf_fit_sums_work_bytes.argtypes = [i32]
+    lib.wolf_fit_sums_work_bytes.restype = ctypes.c_int64
     lib.wolf_batch_work_bytes.argtypes = [i32, i32]
     lib.wolf_batch_work_bytes.restype = ctypes.c_int64
     lib.wolf_direct_work_bytes.argtypes = [i32, i32]
@@ -539,4 +544,44 @@ def fit_gradient(ga: torch.Tensor, imap: torch.Tensor, pitch: float, sigma_g: fl
     d_sigma = torch.empty((1,), dtype=torch.float64, device=ga.device)
     _check(lib.wolf_fit_gradient(_ptr(ga), _ptr(imap), n, pitch, sigma_g, _code(ga.dtype), _ptr(work), _ptr(d_imap),
                                  _ptr(d_sigma), _stream()), "wolf_fit_gradient")
+    return d_imap, d_sigma
+
+
+def _fit_sums_work(n: int, device) -> torch.Tensor:
+    nbytes = int(load().wolf_fit_sums_work_bytes(n))
+    if nbytes < 0:
+        raise WolfError(EUNSUPPORTED, "wolf_fit_sums_work_bytes", f"N={n} unsupported")
+    return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
+def fit_forward(imap: torch.Tensor, pitch: float, sigma_g: float, wavelength: float, z: float, farfield: bool = False):
+    """(S_B, corr) of the propagated custom-map source in float64; corr is what fit_backward needs of the forward sums."""
+    n = imap.shape[0]
+    if tuple(imap.shape) != (n, n):
+        raise ValueError(f"intensity_map must have shape ({n}, {n}), got {tuple(imap.shape)}")
+    imap = imap.to(torch.float32).contiguous()
+    work = _fit_sums_work(n, imap.device)
+    corr = torch.empty((n // 2 + 1, n), dtype=torch.complex128, device=imap.device)
+    s = torch.empty((n, n), dtype=torch.float64, device=imap.device)
+    _check(load().wolf_fit_forward(_ptr(imap), n, pitch, sigma_g, wavelength, z, int(bool(farfield)), _ptr(work),
+                                   _ptr(corr), _ptr(s), _stream()), "wolf_fit_forward")
+    return s, corr
+
+
+def fit_backward(g_s: torch.Tensor, imap: torch.Tensor, corr: torch.Tensor, pitch: float, sigma_g: float,
+                 wavelength: float, z: float, farfield: bool = False):
+    """(dL/dI, dL/dsigma_g) of the custom-map source from g_s = dL/dS_B (float64) and the forward's corr."""
+    n = imap.shape[0]
+    if imap.shape != (n, n) or imap.dtype != torch.float32 or not imap.is_cuda or not imap.is_contiguous():
+        raise ValueError("imap must be a contiguous CUDA float32 (N, N) tensor")
+    if g_s.shape != (n, n) or g_s.dtype != torch.float64 or not g_s.is_cuda or not g_s.is_contiguous():
+        raise ValueError("g_s must be a contiguous CUDA float64 (N, N) tensor")
+    if corr.shape != (n // 2 + 1, n) or corr.dtype != torch.complex128 or not corr.is_cuda or not corr.is_contiguous():
+        raise ValueError("corr must be the contiguous CUDA complex128 (N/2 + 1, N) tensor of fit_forward")
+    work = _fit_sums_work(n, imap.device)
+    d_imap = torch.empty((n, n), dtype=torch.float32, device=imap.device)
+    d_sigma = torch.empty((1,), dtype=torch.float64, device=imap.device)
+    _check(load().wolf_fit_backward(_ptr(g_s), _ptr(imap), n, pitch, sigma_g, wavelength, z, int(bool(farfield)),
+                                    _ptr(corr), _ptr(work), _ptr(d_imap), _ptr(d_sigma), _stream()),
+           "wolf_fit_backward")
     return d_imap, d_sigma

@@ -901,6 +901,58 @@ WOLF_API wolf_status wolf_fit_gradient(const void* ga, const float* imap, int32_
   return launched(e, who);
 }
 
+// Arguments shared by the two fit passes: validated, and the buffers both use checked.
+static wolf_status fit_args(const float* imap, int32_t n, double pitch_m, double sigma_g_m, double wavelength_m,
+                            double z_m, int32_t farfield, const void* corr, const void* work, const char* who) {
+  if (!supported_n(n)) return fail(WOLF_EUNSUPPORTED, "%s: N=%d is not a power of two in [2, 256]", who, n);
+  if (!pos_finite(pitch_m) || !pos_finite(wavelength_m) || !pos_finite(z_m))
+    return fail(WOLF_EINVAL, "%s: pitch, wavelength and z must be finite and > 0", who);
+  if (!(sigma_g_m > 0)) return fail(WOLF_EINVAL, "%s: sigma_g_m must be > 0 (or +inf)", who);
+  if (farfield != 0 && farfield != 1) return fail(WOLF_EINVAL, "%s: farfield must be 0 or 1", who);
+  wolf_status s;
+  if ((s = check_buf(imap, (size_t)n * n * 4, "imap")) != WOLF_OK) return s;
+  if ((s = check_buf(corr, (size_t)(n / 2 + 1) * n * 16, "corr")) != WOLF_OK) return s;
+  return check_buf(work, wolf::fit_sums_work_bytes(n), "work");
+}
+
+WOLF_API wolf_status wolf_fit_forward(const float* imap, int32_t n, double pitch_m, double sigma_g_m,
+                                      double wavelength_m, double z_m, int32_t farfield, void* work, void* corr,
+                                      double* s_out, void* stream) {
+  const char* who = "wolf_fit_forward";
+  wolf_status s = fit_args(imap, n, pitch_m, sigma_g_m, wavelength_m, z_m, farfield, corr, work, who);
+  if (s != WOLF_OK) return s;
+  if ((s = check_buf(s_out, (size_t)n * n * 8, "s_out")) != WOLF_OK) return s;
+  const wolf::OperatorTables op = make_op(n, pitch_m, wavelength_m, z_m, farfield == 1, WOLF_SECONDARY, false);
+  const double inv2g2_px = std::isinf(sigma_g_m) ? 0.0 : pitch_m * pitch_m / (2.0 * sigma_g_m * sigma_g_m);
+  return launched(wolf::launch_fit_forward(n, imap, op.pre2.alpha, inv2g2_px, op.scale, work, (double2*)corr, s_out,
+                                           static_cast<hipStream_t>(stream)),
+                  who);
+}
+
+WOLF_API wolf_status wolf_fit_backward(const double* g_s, const float* imap, int32_t n, double pitch_m,
+                                       double sigma_g_m, double wavelength_m, double z_m, int32_t farfield,
+                                       const void* corr, void* work, float* d_imap, double* d_sigma, void* stream) {
+  const char* who = "wolf_fit_backward";
+  if (!supported_n(n) || n > 128) return fail(WOLF_EUNSUPPORTED, "%s: N=%d unsupported (N <= 128)", who, n);
+  if (!pos_finite(sigma_g_m)) return fail(WOLF_EINVAL, "%s: sigma_g must be finite and > 0", who);
+  wolf_status s = fit_args(imap, n, pitch_m, sigma_g_m, wavelength_m, z_m, farfield, corr, work, who);
+  if (s != WOLF_OK) return s;
+  if ((s = check_buf(g_s, (size_t)n * n * 8, "g_s")) != WOLF_OK) return s;
+  if ((s = check_buf(d_imap, (size_t)n * n * 4, "d_imap")) != WOLF_OK) return s;
+  if ((s = check_buf(d_sigma, 8, "d_sigma")) != WOLF_OK) return s;
+  const wolf::OperatorTables op = make_op(n, pitch_m, wavelength_m, z_m, farfield == 1, WOLF_SECONDARY, false);
+  const double inv2g2_px = pitch_m * pitch_m / (2.0 * sigma_g_m * sigma_g_m);
+  const double sg_scale = pitch_m * pitch_m / (sigma_g_m * sigma_g_m * sigma_g_m);
+  return launched(wolf::launch_fit_backward(n, g_s, imap, op.pre2.alpha, inv2g2_px, op.scale, sg_scale,
+                                            (const double2*)corr, work, d_imap, d_sigma,
+                                            static_cast<hipStream_t>(stream)),
+                  who);
+}
+
+WOLF_API int64_t wolf_fit_sums_work_bytes(int32_t n) {
+  return supported_n(n) ? (int64_t)wolf::fit_sums_work_bytes(n) : -1;
+}
+
 WOLF_API wolf_status wolf_set_plan(int32_t n, int32_t dtype, int32_t fused_slab, int64_t slab_chunk,
                                    int64_t col_chunk, int32_t coop_cols, int32_t coop_lookahead) {
   if (!supported_n(n)) return fail(WOLF_EUNSUPPORTED, "wolf_set_plan: N=%d unsupported", n);

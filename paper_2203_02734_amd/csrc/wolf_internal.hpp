@@ -175,6 +175,14 @@ hipError_t launch_diag_embed(int n, const typename real_of<T>::type* g, T* out, 
 template <class T>
 hipError_t launch_fit_gradient(int n, const T* ga, const float* imap, double inv2g2_px, double sg_scale, void* work,
                                float* d_imap, double* d_sigma, hipStream_t st);
+// S_B of the custom-map source and its gradients as FP64 sums over point differences (no N^4 array): alpha the source
+// chirp rate, scale = C pitch^4, corr (N/2 + 1) x N complex kept from the forward for dL/dsigma.
+hipError_t launch_fit_forward(int n, const float* imap, double alpha, double inv2g2_px, double scale, void* work,
+                              double2* corr, double* s, hipStream_t st);
+hipError_t launch_fit_backward(int n, const double* g_s, const float* imap, double alpha, double inv2g2_px,
+                               double scale, double sg_scale, const double2* corr, void* work, float* d_imap,
+                               double* d_sigma, hipStream_t st);
+size_t fit_sums_work_bytes(int n);
 int fit_slabs_per_group(int n);
 size_t fit_work_bytes(int n, int real_bytes);
 
