@@ -106,4 +106,30 @@ __device__ __forceinline__ void ctile_mfma16(CTile<T>& c, const typename real_of
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Global memory accesses of the kernels that keep a stream of rows in flight.
+// ---------------------------------------------------------------------------------------------
+// Complex elements of global memory as plain vectors, so that a pointer made opaque keeps its address space.
+template <class T> struct GlobalElem;
+template <> struct GlobalElem<float2> { typedef float V __attribute__((ext_vector_type(2))); };
+template <> struct GlobalElem<double2> { typedef double V __attribute__((ext_vector_type(2))); };
+template <class T> using GlobalPtr = __attribute__((address_space(1))) typename GlobalElem<T>::V*;
+using GlobalBytes = __attribute__((address_space(1))) char*;
+
+// Hides how a wavefront-uniform pointer was formed, so that the steps of an unrolled chain of rows stay one scalar
+// addition each (folded, they were kept as loop-invariant offsets across tiles: 60-170 spilled registers).
+template <class P> __device__ __forceinline__ void opaque(P& p) { asm("" : "+s"(p)); }
+
+// The element `off` bytes past a pointer (a wavefront-uniform one and 32 bits per lane: one addressing mode).
+template <class T> __device__ __forceinline__ GlobalPtr<T> byte_at(GlobalPtr<T> p, unsigned off) {
+  return (GlobalPtr<T>)((GlobalBytes)p + off);
+}
+template <class T> __device__ __forceinline__ T load_elem(GlobalPtr<T> p) {
+  const auto v = *p;
+  return T{v.x, v.y};
+}
+template <class T> __device__ __forceinline__ void store_elem(GlobalPtr<T> p, const T& v) {
+  *p = typename GlobalElem<T>::V{v.x, v.y};
+}
+
 }  // namespace wolf

@@ -303,6 +303,210 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
 }
 
+// Row sums of a Fresnel batch group by the mirror symmetry of the source chirp: with c = N/2, u1[c + m] = u1[c - m] = v[m]
+// for every pair, and the phase e^{2 pi i P a / N} is the same for all pairs, so mirrored rows of W meet before the product:
+//   R[k][p2] = sum_{l, m = 0}^{c} v_k[l] v_k[m] Y_{l,m}[p2],
+//   Y_{l,m}  = sum over the signs of e^{2 pi i (P_i (c +- l) + P_j (c +- m)) / N} W[(c +- l) N + c +- m][p2]
+// (one sign at l or m = 0 and at c: the grid ends at c - 1). A quarter of the matrix-core work of k_pair_rows_ring, for 12
+// vector FMAs per element of W. The stream of W is kept in flight as there: a wavefront owns 16 R pairs and 16 Q columns, a
+// step is four values of m of one l (16 rows of W, 3 Q R MFMAs into G_l = sum_m v[m] Y) and RING steps sit in registers. Y of
+// a step is formed between the products of the step before (a wavefront alone on its SIMD overlaps the two only so). The
+// blocks are l = 0 .. c over m < c, each folded with v[l], and one for m = c, which sums over l < c and is folded with v[c];
+// the corner l = m = c is added at the end. So a block is N / 8 steps, whole turns of the ring, and the fold stands once
+// after them. Loads are unconditional (past the chunk's last block they re-read it). A workgroup takes one tile of 64 Q
+// columns and one of `chunks` ranges of blocks: part[chunk][k][p2].
+// Bound: the read of W (and the matrix cores at 64 pairs). Measured: see rows_fold_parts.
+template <class T, int N, int R, int Q>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_pair_rows_fold(
+    const T* __restrict__ w, const T* __restrict__ u1t, int pi, int pj, int chunks, T* __restrict__ part) {
+  using V = typename Mfma<T>::V;
+  using Rt = typename real_of<T>::type;
+  constexpr int C = N / 2, MS = C / 4, RING = MS < 8 ? MS : 8;
+  constexpr unsigned EB = sizeof(T);
+  constexpr long long NN = (long long)N * N, NNN = NN * N;
+  constexpr int TILES = (int)(NN / (64 * Q));
+  static_assert(MS % RING == 0, "blocks of whole turns");
+  __shared__ T vm[(C + 1) * kPairTile];        // v[m][k] at m 64 + swz(m, k)
+  __shared__ T phj[2][C + 1], phi[2][C + 1];   // the phases of the two signs, zero where a sign has no row
+  const int tid = threadIdx.x, lane = tid % 64, l16 = lane % 16, kq = lane / 16;
+  const int wv = __builtin_amdgcn_readfirstlane(tid / 64);
+  // Two rows of 8-byte entries 512 B apart share their banks: odd rows are exchanged by 16 pairs.
+  auto swz = [](int m, int k) { return sizeof(T) == 8 ? k ^ ((m & 1) << 4) : k; };
+  for (int e = tid; e < (C + 1) * kPairTile; e += 256) {
+    const int m = e / kPairTile, k = e % kPairTile;
+    vm[m * kPairTile + swz(m, k)] = u1t[(C - m) * kPairTile + k];
+  }
+  auto phase = [&](int P, int d, int sgn) {  // e^{2 pi i P (c + sgn d) / N}, zero where that is no row
+    const bool row = !(sgn > 0 && d == C) && !(sgn < 0 && d == 0);
+    double si, co;
+    sincospi(2.0 * (double)((P * (C + sgn * d)) % N) / (double)N, &si, &co);
+    return T{(Rt)(row ? co : 0.0), (Rt)(row ? si : 0.0)};
+  };
+  for (int e = tid; e < 4 * (C + 1); e += 256) {
+    const int which = e / (C + 1), d = e % (C + 1), sgn = which % 2 ? -1 : 1;
+    (which < 2 ? phj[which] : phi[which - 2])[d] = phase(which < 2 ? pj : pi, d, sgn);
+  }
+  __syncthreads();
+  const int tile = (int)blockIdx.x % TILES, chunk = (int)blockIdx.x / TILES;
+  const int b_lo = (C + 2) * chunk / chunks, b_hi = (C + 2) * (chunk + 1) / chunks;  // blocks; C + 1: the rows m = c
+  const int col = tile * 64 * Q + wv * 16 * Q + l16;
+  const GlobalPtr<T> w0 = (GlobalPtr<T>)const_cast<T*>(w);
+  struct Step {
+    T v[4][Q];  // W at (c + l, c + m), (c + l, c - m), (c - l, c + m), (c - l, c - m); block m = c: (c + l, 0), (c - l, 0) twice
+  };
+  // Steps in order (block, ms); the load's position runs RING - 1 steps ahead of the product's.
+  struct Pos {
+    int blk, ms;
+  };
+  auto advance = [&](Pos& p) {
+    const bool last = p.ms == MS - 1;
+    p.ms = last ? 0 : p.ms + 1;
+    p.blk += last ? 1 : 0;
+  };
+  auto load = [&](Step& r, const Pos& p) {
+    const int blk = p.blk < b_hi ? p.blk : b_hi - 1;
+    const bool rim = blk == C + 1;
+    const int l = rim ? 0 : blk;
+    const unsigned st = (unsigned)(rim ? NNN : NN);  // stride of the contraction index
+    const long long at = 4ll * p.ms * st;
+    // Middle rows of the two outer signs (the rim's is row 0 of the second index), the row c + m, and c - m - 3.
+    const long long up = rim ? (long long)C * NNN : (long long)(l < C ? C + l : C - l) * NNN + C * NN;
+    const long long dn = rim ? (long long)C * NNN : (long long)(C - l) * NNN + C * NN;
+    const unsigned op = ((unsigned)kq * st + (unsigned)col) * EB, om = ((unsigned)(3 - kq) * st + (unsigned)col) * EB;
+    const long long back = at + 3ll * st;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      r.v[0][q] = load_elem<T>(byte_at<T>(w0 + up + at + 16 * q, op));
+      r.v[1][q] = load_elem<T>(byte_at<T>(w0 + up - back + 16 * q, om));
+      r.v[2][q] = load_elem<T>(byte_at<T>(w0 + dn + at + 16 * q, op));
+      r.v[3][q] = load_elem<T>(byte_at<T>(w0 + dn - back + 16 * q, om));
+    }
+  };
+  V t1[R][Q], t2[R][Q], t3[R][Q];
+  T f[R][Q][4];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      t1[r][q] = t2[r][q] = t3[r][q] = V{0, 0, 0, 0};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) f[r][q][i] = T{(Rt)0, (Rt)0};
+    }
+  T av[2][R], ph[2][4], y[2][Q];
+  auto read_a = [&](T (&e)[R], const Pos& p) {
+    const int m = 4 * p.ms + kq;
+#pragma unroll
+    for (int r = 0; r < R; ++r) e[r] = vm[m * kPairTile + swz(m, 16 * r + l16)];
+  };
+  // (inner +, inner -, outer +, outer -); the rim's inner index is l and its outer phase that of c - c.
+  auto read_phases = [&](T (&e)[4], const Pos& p) {
+    const int m = 4 * p.ms + kq;
+    const bool rim = p.blk == C + 1;
+    const int l = p.blk <= C ? p.blk : C;
+    e[0] = (rim ? phi[0] : phj[0])[m];
+    e[1] = (rim ? phi[1] : phj[1])[m];
+    e[2] = (rim ? phj[0] : phi[0])[l];
+    e[3] = (rim ? phj[1] : phi[1])[l];
+  };
+  auto form = [&](T (&o)[Q], const Step& b, const T (&e)[4]) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const T xp = cadd(cmul(e[0], b.v[0][q]), cmul(e[1], b.v[1][q]));
+      const T xm = cadd(cmul(e[0], b.v[2][q]), cmul(e[1], b.v[3][q]));
+      o[q] = cadd(cmul(e[2], xp), cmul(e[3], xm));
+    }
+  };
+  Step ring[RING];
+  Pos lp{b_lo, 0}, np{b_lo, 0}, np2{b_lo, 0};  // the load's, the next step's and the one after it
+#pragma unroll
+  for (int u = 0; u < RING - 1; ++u) {
+    load(ring[u], lp);
+    advance(lp);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  read_a(av[0], np);
+  read_phases(ph[0], np);
+  advance(np);
+  read_phases(ph[1], np);
+  form(y[0], ring[0], ph[0]);
+  np2 = np;
+  advance(np2);
+  for (int blk = b_lo; blk < b_hi; ++blk) {
+    for (int t0 = 0; t0 < MS; t0 += RING) {
+#pragma unroll
+      for (int u = 0; u < RING; ++u) {
+        load(ring[(u + RING - 1) % RING], lp);
+        advance(lp);
+        read_a(av[(u + 1) % 2], np);
+        read_phases(ph[u % 2], np2);
+        __builtin_amdgcn_sched_barrier(0);
+        form(y[(u + 1) % 2], ring[(u + 1) % RING], ph[(u + 1) % 2]);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          const T yq = y[u % 2][q];
+          const Rt ys = yq.x + yq.y;
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const T x = av[u % 2][r];
+            t1[r][q] = Mfma<T>::mac(x.x, yq.x, t1[r][q]);
+            t2[r][q] = Mfma<T>::mac(x.y, yq.y, t2[r][q]);
+            t3[r][q] = Mfma<T>::mac(x.x + x.y, ys, t3[r][q]);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 3 * R * Q; ++i) {  // one product, then a few of the vector instructions
+          __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x2, R == 4 ? 3 : R == 2 ? 5 : 10, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q)  // keeps the next Y among the products
+          asm volatile("" : "+v"(y[(u + 1) % 2][q].x), "+v"(y[(u + 1) % 2][q].y));
+        np = np2;
+        advance(np2);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    const int l = blk <= C ? blk : C;  // fold G into the sums with v[l] (v[c] for the rim)
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const T c = vm[l * kPairTile + swz(l, 16 * r + Mfma<T>::row(lane, i))];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          const Rt gr = t1[r][q][i] - t2[r][q][i], gi = t3[r][q][i] - t1[r][q][i] - t2[r][q][i];
+          f[r][q][i].x += c.x * gr - c.y * gi;
+          f[r][q][i].y += c.x * gi + c.y * gr;
+        }
+      }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < Q; ++q) t1[r][q] = t2[r][q] = t3[r][q] = V{0, 0, 0, 0};
+  }
+  if (b_hi == C + 2) {  // the corner l = m = c: row 0 of W
+    const T p0 = cmul(phi[1][C], phj[1][C]);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const T x = cmul(p0, w[col + 16 * q]);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const T c = vm[C * kPairTile + swz(C, 16 * r + Mfma<T>::row(lane, i))];
+          f[r][q][i] = cadd(f[r][q][i], cmul(cmul(c, c), x));
+        }
+    }
+  }
+  T* const out = part + (long long)chunk * kPairTile * NN;
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) out[(16 * r + Mfma<T>::row(lane, i)) * NN + col + 16 * q] = f[r][q][i];
+}
+
 // Difference sums: part[z][k][di N + dj] = sum_{b in chunk z} B_k^{dj}[b] sum_a A_k^{di}[a]
 // W[a, b; a - di, b - dj] (indices mod N), A = u1[a] u2[a - di], B = u1[b] u2[b - dj], for the first TM
 // pairs k. A workgroup owns di, TN values of dj and a chunk of b; for each b the inner sum is a GEMM over
@@ -1331,6 +1535,34 @@ static int rows_ring_parts(int n, int count) {
   return 256 / (n * n / 128);
 }
 
+// The mirrored form of a Fresnel group's row sums (count >= 2): at N = 32, 64, 128 and 256 the number of ranges of blocks it
+// writes, one workgroup per CU where the columns allow it; 0 at smaller N, whose few tiles the LDS-staged kernel covers.
+// Measured at N = 128: complex64, 64 pairs 941 -> 450 us (38 % of the matrix rate), 12 pairs 338 -> 345 us (6.2 TB/s);
+// complex128, 64 pairs 2.2 -> 0.87 ms; N = 64 complex128, 23 pairs 0.13 -> 0.07 ms.
+template <class T> static int rows_fold_parts(int n) {
+  if (n < 32) return 0;
+  const int tiles = n * n / (64 * 16 / (int)sizeof(T));
+  return tiles >= 256 ? 1 : (256 / tiles < kPairSplitK ? 256 / tiles : kPairSplitK);
+}
+
+template <class T>
+static hipError_t launch_rows_fold(int n, int count, const T* w, const T* u1t, int pi, int pj, T* part, hipStream_t st) {
+  constexpr int Q = 16 / (int)sizeof(T);  // 32 columns per wavefront in complex64, 16 in complex128
+  const int parts = rows_fold_parts<T>(n);
+  const unsigned grid = (unsigned)(n * n / (64 * Q) * parts);
+  using Rows = void (*)(const T*, const T*, int, int, int, T*);
+  auto of_n = [&](auto nc) -> Rows {
+    constexpr int N = decltype(nc)::value;
+    return count > 32 ? k_pair_rows_fold<T, N, 4, Q> : count > 16 ? k_pair_rows_fold<T, N, 2, Q> : k_pair_rows_fold<T, N, 1, Q>;
+  };
+  const Rows rows = n == 32    ? of_n(std::integral_constant<int, 32>{})
+                    : n == 64  ? of_n(std::integral_constant<int, 64>{})
+                    : n == 128 ? of_n(std::integral_constant<int, 128>{})
+                               : of_n(std::integral_constant<int, 256>{});
+  hipLaunchKernelGGL(rows, dim3(grid), dim3(256), 0, st, w, u1t, pi, pj, parts, part);
+  return hipGetLastError();
+}
+
 // The ring form of the Fresnel difference sums (complex64, N = 128, any count) writes 256 / N chunks of b.
 static bool diffs_ring_ok(int n, int count) { return n == 128 && count >= 1; }
 
@@ -1440,11 +1672,16 @@ hipError_t launch_pair_sums(int n, const T* w, const double* a_src, int count, i
   }
   const long long chunk = (nn + kPairSplitK - 1) / kPairSplitK;
   const int bchunk = (n + sb - 1) / sb;
-  if ((e = launch_mfma<T>(count, 0, n, w, u1, u2, tr, chunk, bchunk, sb, part_r, st)) != hipSuccess) return e;
+  const int folded = rows_fold_parts<T>(n);
+  if (folded > 0)
+    e = launch_rows_fold<T>(n, count, w, tr, pi, pj, part_r, st);
+  else
+    e = launch_mfma<T>(count, 0, n, w, u1, u2, tr, chunk, bchunk, sb, part_r, st);
+  if (e != hipSuccess) return e;
   e = launch_mfma<T>(count, 1, n, w, u1, u2, tr, chunk, bchunk, sb, part_d, st);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const unsigned sum_blocks = (unsigned)((g + 255) / 256);
-  const int sr = (sizeof(T) == 8 && rows_ring_parts(n, count) > 0) ? rows_ring_parts(n, count) : kPairSplitK;
+  const int sr = folded > 0 ? folded : kPairSplitK;
   hipLaunchKernelGGL(k_pair_sum<T>, dim3(sum_blocks), dim3(256), 0, st, (const T*)part_r, sr, n, kPairTile,
                      (const T*)u2, buf_r);
   if ((e = hipGetLastError()) != hipSuccess) return e;
