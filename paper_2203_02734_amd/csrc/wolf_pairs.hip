@@ -43,10 +43,11 @@ __device__ __forceinline__ void store_tables(T* u1, T* u2, T* ci, T* cj, T* tr, 
 
 template <class T>
 __global__ __launch_bounds__(256) void k_pair_tables(PairGroup g, int n, int pi, int pj, T* u1, T* u2, T* ci, T* cj,
-                                                     T* tr) {
+                                                     T* tr, unsigned long long* key) {
   using R = typename real_of<T>::type;
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= kPairTile * n) return;
+  if (e < g.count) key[e] = 0ull;  // the maxima of this group's s0 (k_pair_s0); kPairTile N >= count
   const int k = e / n, a = e % n;
   if (k >= g.count) {
     const T z{(R)0, (R)0};
@@ -161,7 +162,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
       }
 }
 
-// Row sums of a complex64 group at N = 64 or 128, with the W stream kept deep in flight:
+// Row sums of a complex64 polychromatic group at N = 64 or 128, with the W stream kept deep in flight:
 // part[s][k][p2] = sum_{a} ci[k][a] G_a[k][p2], G_a[k][p2] = sum_b cj[k][b] W[a N + b][p2], over the
 // whole rows a of chunk s, for the first 16 R pairs k (R = 4: groups of more than 32 pairs; 2: 17-32; 1: up
 // to 16; the rows of the other pairs are not written). The tables cj and ci of the group sit in LDS for the
@@ -303,6 +304,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
 }
 
+// Wavefronts of a workgroup of the two streaming contractions below (one workgroup per CU) and blocks of 16 columns per
+// wavefront, for R tiles of 16 pairs. With four tiles complex64 takes two wavefronts per SIMD over one block each, so that
+// one's vector work runs beside the other's products; with fewer the read of W bounds the pass, and one wavefront over two
+// blocks has the longer runs. N = 128 complex64, row and difference sums: 64 pairs 450 and 980 us with one wavefront, 410 and
+// 875 us with two; 12 pairs 350 and 457 us with one, 357 and 580 us with two. complex128 holds one block per wavefront.
+template <class T, int R> constexpr int kStreamWaves = sizeof(T) == 8 && R == 4 ? 8 : 4;
+template <class T, int R> constexpr int kStreamBlocks = sizeof(T) == 8 && R < 4 ? 2 : 1;
+// Columns of a workgroup: 128 in complex64, 64 in complex128.
+template <class T> constexpr int kStreamColumns = 1024 / (int)sizeof(T);
+
 // Row sums of a Fresnel batch group by the mirror symmetry of the source chirp: with c = N/2, u1[c + m] = u1[c - m] = v[m]
 // for every pair, and the phase e^{2 pi i P a / N} is the same for all pairs, so mirrored rows of W meet before the product:
 //   R[k][p2] = sum_{l, m = 0}^{c} v_k[l] v_k[m] Y_{l,m}[p2],
@@ -316,15 +327,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // after them. Loads are unconditional (past the chunk's last block they re-read it). A workgroup takes one tile of 64 Q
 // columns and one of `chunks` ranges of blocks: part[chunk][k][p2].
 // Bound: the read of W (and the matrix cores at 64 pairs). Measured: see rows_fold_parts.
-template <class T, int N, int R, int Q>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_pair_rows_fold(
+template <class T, int N, int R>
+__global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_waves_per_eu((kStreamWaves<T, R> / 4), (kStreamWaves<T, R> / 4)))) void k_pair_rows_fold(
     const T* __restrict__ w, const T* __restrict__ u1t, int pi, int pj, int chunks, T* __restrict__ part) {
   using V = typename Mfma<T>::V;
   using Rt = typename real_of<T>::type;
-  constexpr int C = N / 2, MS = C / 4, RING = MS < 8 ? MS : 8;
+  constexpr int Q = kStreamBlocks<T, R>, W = kStreamWaves<T, R>, C = N / 2, MS = C / 4, RING = MS < 8 ? MS : 8;
   constexpr unsigned EB = sizeof(T);
   constexpr long long NN = (long long)N * N, NNN = NN * N;
-  constexpr int TILES = (int)(NN / (64 * Q));
+  constexpr int TILES = (int)(NN / (16 * Q * W));
   static_assert(MS % RING == 0, "blocks of whole turns");
   __shared__ T vm[(C + 1) * kPairTile];        // v[m][k] at m 64 + swz(m, k)
   __shared__ T phj[2][C + 1], phi[2][C + 1];   // the phases of the two signs, zero where a sign has no row
@@ -332,7 +343,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int wv = __builtin_amdgcn_readfirstlane(tid / 64);
   // Two rows of 8-byte entries 512 B apart share their banks: odd rows are exchanged by 16 pairs.
   auto swz = [](int m, int k) { return sizeof(T) == 8 ? k ^ ((m & 1) << 4) : k; };
-  for (int e = tid; e < (C + 1) * kPairTile; e += 256) {
+  for (int e = tid; e < (C + 1) * kPairTile; e += 64 * W) {
     const int m = e / kPairTile, k = e % kPairTile;
     vm[m * kPairTile + swz(m, k)] = u1t[(C - m) * kPairTile + k];
   }
@@ -342,14 +353,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     sincospi(2.0 * (double)((P * (C + sgn * d)) % N) / (double)N, &si, &co);
     return T{(Rt)(row ? co : 0.0), (Rt)(row ? si : 0.0)};
   };
-  for (int e = tid; e < 4 * (C + 1); e += 256) {
+  for (int e = tid; e < 4 * (C + 1); e += 64 * W) {
     const int which = e / (C + 1), d = e % (C + 1), sgn = which % 2 ? -1 : 1;
     (which < 2 ? phj[which] : phi[which - 2])[d] = phase(which < 2 ? pj : pi, d, sgn);
   }
   __syncthreads();
   const int tile = (int)blockIdx.x % TILES, chunk = (int)blockIdx.x / TILES;
   const int b_lo = (C + 2) * chunk / chunks, b_hi = (C + 2) * (chunk + 1) / chunks;  // blocks; C + 1: the rows m = c
-  const int col = tile * 64 * Q + wv * 16 * Q + l16;
+  const int col = (tile * W + wv) * 16 * Q + l16;
   const GlobalPtr<T> w0 = (GlobalPtr<T>)const_cast<T*>(w);
   struct Step {
     T v[4][Q];  // W at (c + l, c + m), (c + l, c - m), (c - l, c + m), (c - l, c - m); block m = c: (c + l, 0), (c - l, 0) twice
@@ -619,344 +630,284 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
       }
 }
 
-// Difference sums of a complex64 group at N = 128, with the W stream kept deep
-// in flight (the ring of k_pair_rows_ring): part[z][k][di N + dj] = sum_{b in chunk z} B_k^{dj}[b] G_b[k][dj],
-// G_b[k][dj] = sum_a A^{di}[a][k] W[a, b; a - di, b - dj], A^{di}[a][k] = u1[k][a] u2[k][a - di],
-// B_k^{dj}[b] = u1[k][b] u2[k][b - dj] (indices mod N). A workgroup owns one di and 256 / N chunks of b
-// (z = blockIdx.x % (256 / N)), the first 16 R pairs (R = 4, 2, 1 for groups of more than 32, 17-32 and
-// up to 16 pairs; the other pairs' sums are not written) and all N values of dj (a wavefront: 32 of them). A^{di}
-// (formed once) and u2 sit in LDS; u1[k][b] is loaded at the start of each b. Each step is 16 values of a
-// (24 R MFMAs into G); after the N / 16 steps of one b, G is folded into the sums. Only N = 128 fills the
-// four wavefronts' 128 columns; at N = 64 wavefronts 2 and 3 hold no columns and stay idle.
-template <int N, int R>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_pair_diffs_ring(
-    const float2* __restrict__ w, const float2* __restrict__ u1t, const float2* __restrict__ u2t,
-    float2* __restrict__ part) {
-  constexpr long long NN = (long long)N * N;
-  constexpr int SPB = N / 16;  // steps per b
-  constexpr int RING = 8, BSPLIT = 256 / N, BCH = N / BSPLIT;
-  constexpr int NM = N - 1;
-  static_assert(SPB <= RING && RING % SPB == 0, "ring of whole b");
-  static_assert(R >= 1 && 16 * R <= kPairTile, "tiles of 16 pairs");
-  __shared__ float2 as_[N * kPairTile], u2s[N * kPairTile];
-  const int tid = threadIdx.x, lane = tid % 64, l16 = lane % 16, kq = lane / 16;
-  const int wv = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int di = (int)blockIdx.x / BSPLIT, z = (int)blockIdx.x % BSPLIT;
-  const int b_lo = z * BCH;
-  // A^{di}[a][k] at a 64 + (k ^ 16 (a & 1)); u2[m][k] at m 64 + (k ^ 2 (m & 15)) (the fold's 16 lanes of one
-  // k read 16 consecutive m).
-  for (int e = tid; e < N * kPairTile; e += 256) {
-    const int m = e / kPairTile, k = e % kPairTile;
-    as_[m * kPairTile + (k ^ ((m & 1) << 4))] = cmul(u1t[e], u2t[((m - di) & NM) * kPairTile + k]);
-    u2s[m * kPairTile + (k ^ ((m & 15) << 1))] = u2t[e];
-  }
-  __syncthreads();
-  if (wv * 32 >= N) return;  // no columns for this wavefront (N = 64); no barrier follows
-  const int dj0 = 32 * wv;
-  constexpr int total = BCH * SPB;
-  auto load = [&](RingStep& r, int t) {
-    const int tc = t < total ? t : total - 1;
-    const int b = b_lo + tc / SPB, a0 = (tc % SPB) * 16;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int a = a0 + 4 * ks + kq;
-      const float2* row = w + ((long long)a * N + b) * NN + (long long)((a - di) & NM) * N;
-#pragma unroll
-      for (int q = 0; q < 2; ++q) r.v[ks][q] = row[(b - dj0 - 16 * q - l16) & NM];
-    }
-  };
-  v4f t1[R][2], t2[R][2], t3[R][2];
-  float2 f[R][2][4], u1v[R][4];
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      t1[r][q] = t2[r][q] = t3[r][q] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) f[r][q][i] = float2{0.f, 0.f};
-    }
-  auto read_a = [&](float2 (&av)[4][R], int a0) {
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int a = a0 + 4 * ks + kq;
-#pragma unroll
-      for (int r = 0; r < R; ++r) av[ks][r] = as_[a * kPairTile + ((16 * r + l16) ^ ((a & 1) << 4))];
-    }
-  };
-  auto step_mfma = [&](const float2 (&av)[4][R], const RingStep& bw) {
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      float xs[R], ys[2];
-#pragma unroll
-      for (int r = 0; r < R; ++r) xs[r] = av[ks][r].x + av[ks][r].y;
-#pragma unroll
-      for (int q = 0; q < 2; ++q) ys[q] = bw.v[ks][q].x + bw.v[ks][q].y;
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          t1[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks][r].x, bw.v[ks][q].x, t1[r][q], 0, 0, 0);
-          t2[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks][r].y, bw.v[ks][q].y, t2[r][q], 0, 0, 0);
-          t3[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[r], ys[q], t3[r][q], 0, 0, 0);
-        }
-    }
-  };
-  RingStep ring[RING];
-#pragma unroll
-  for (int u = 0; u < RING - 1; ++u) {
-    load(ring[u], u);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  float2 avs[2][4][R];
-  read_a(avs[0], 0);
-  for (int t0 = 0; t0 < total; t0 += RING) {  // t0 is a multiple of SPB
-#pragma unroll
-    for (int u = 0; u < RING; ++u) {
-      const int b = b_lo + (t0 + u) / SPB;
-      load(ring[(u + RING - 1) % RING], t0 + u + RING - 1);
-      if (u % SPB == 0) {  // u1[k][b] of this b, behind the ring's load (it is needed at the fold)
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) u1v[r][i] = u1t[b * kPairTile + 16 * r + Mfma<float2>::row(lane, i)];
-      }
-      read_a(avs[(u + 1) % 2], ((u + 1) % SPB) * 16);  // the next step's operand
-      __builtin_amdgcn_sched_barrier(0);
-      step_mfma(avs[u % 2], ring[u]);
-      if ((u + 1) % SPB == 0) {  // the last step of b: D += u1[k][b] u2[k][b - dj] G
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int k = 16 * r + Mfma<float2>::row(lane, i);
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-              const int m = (b - dj0 - 16 * q - l16) & NM;
-              const float2 c = cmul(u1v[r][i], u2s[m * kPairTile + (k ^ ((m & 15) << 1))]);
-              const float gr = t1[r][q][i] - t2[r][q][i], gi = t3[r][q][i] - t1[r][q][i] - t2[r][q][i];
-              f[r][q][i].x += c.x * gr - c.y * gi;
-              f[r][q][i].y += c.x * gi + c.y * gr;
-            }
-          }
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int q = 0; q < 2; ++q) t1[r][q] = t2[r][q] = t3[r][q] = v4f{0.f, 0.f, 0.f, 0.f};
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  float2* out = part + (long long)z * kPairTile * NN;
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        out[(16 * r + Mfma<float2>::row(lane, i)) * NN + (long long)di * N + dj0 + 16 * q + l16] = f[r][q][i];
-}
+// Difference sums by the mirror symmetry of their weights. For an unfolded offset delta (d_i for a >= d_i, d_i - N for
+// a < d_i) the weight u1[a] u2[a - delta] is a linear phase in a: with s = a - a_mid over the range of a (its middle),
+//   u1[a] u2[a - delta] = kappa e^{-2 pi i alpha delta s},   kappa = +-e^{i pi alpha delta},
+// so mirrored rows W_hi (s) and W_lo (-s) give  kappa (cos(theta) (W_hi + W_lo) - i sin(theta) (W_hi - W_lo)): real weights
+// on complex data, four real products for two rows (the 3M form takes six), and no operand sums. For each range h
+// (delta = d_i, d_i - N) and b,
+//   G[k][dj] = sum over the pairs of rows of the range,   D_h[k][dj] = kappa sum_b u1[b] u2[b - dj] G.
+// A workgroup owns d_i, up to four blocks of 16 Q columns d_j (further waves take their own chunks of b) and a chunk of b; the
+// ranges run one after the other, b inside. A wavefront owns 16 R pairs x 16 Q columns; a step is eight pairs of rows of one
+// b, and RING steps sit in registers (one wavefront per SIMD). cos and sin stand in LDS (FP64-built, one row per pair of
+// rows; zero past a range's last pair, cos = 1/2 for a middle row that is its own mirror). Past the last b the loads re-read
+// it and the weights are zero.
+//   POLY 0 (Fresnel batch): part[2 z + h][k][d_i N + d_j] = D_h: the ranges are two of the parts that are summed.
+//   POLY 1 (unfolded bins): part[z][k][(delta + N) 2N + delta_j + N]: as b rises a lane's column switches from the bin
+//          d_j - N to d_j at b = d_j; each bin is written once per chunk of b.
+// Bound: the matrix cores and the folds at 64 pairs, the read of W at 16. Measured: see diffs_mirror_parts.
+struct DiffRates {
+  double alpha[kPairTile];  // source chirp rate of each pair
+  int count;
+};
 
-// The polychromatic difference sums without wrap (the bins of k_poly_diffs_mfma) on the register ring of
-// k_pair_diffs_ring, for the pairs k0 .. k0 + 16 R - 1 of a complex64 group at N = 128: one tile of 16 pairs
-// with eight steps of the source in flight (R = 1, RING = 8), or two tiles with four steps (R = 2, RING = 4:
-// with eight, the two bins' sums of two tiles exceed the registers of one wavefront per SIMD and spill). A
-// workgroup owns one folded d_i, 256 / N chunks of b (z = blockIdx.x % (256 / N)) and every a: a step of 16
-// values of a adds into the G of bin d_i (a >= d_i) or of bin d_i - N (a < d_i); the one step that holds d_i
-// runs twice, with the A rows of the other bin zeroed. After the N / 16 steps of one b both G are folded into
-// their sums. On the second point a lane's column d_j switches bin once as b rises, so the lane stores its
-// lower bin's sums when b passes d_j - 1 and writes each of its four bins (two of d_i, two of d_j) exactly once
-// per chunk of b, zeros where the chunk holds no term.
-template <int N, int R, int RING>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_poly_diffs_ring(
-    const float2* __restrict__ w, const float2* __restrict__ u1t, const float2* __restrict__ u2t, int k0,
-    float2* __restrict__ part) {
-  constexpr long long NN = (long long)N * N, BINS = 4 * NN;
-  constexpr int SPB = N / 16;  // steps per b
-  constexpr int BSPLIT = 256 / N, BCH = N / BSPLIT;
-  constexpr int NM = N - 1;
-  static_assert((SPB <= RING && RING % SPB == 0) || (RING < SPB && SPB % RING == 0), "ring and steps per b nest");
-  static_assert((R == 1 && RING == 8) || (R == 2 && RING == 4), "the register budgets measured");
-  __shared__ float2 as_[N * kPairTile], u2s[N * kPairTile];
+template <class T, int N, int R, int BCH, bool POLY>
+__global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_waves_per_eu((kStreamWaves<T, R> / 4), (kStreamWaves<T, R> / 4)))) void k_diffs_mirror(
+    const T* __restrict__ w, const T* __restrict__ u1, const T* __restrict__ u2, const T* __restrict__ u1t,
+    const T* __restrict__ u2t, DiffRates rates, T* __restrict__ part) {
+  using V = typename Mfma<T>::V;
+  using Rt = typename real_of<T>::type;
+  constexpr long long NN = (long long)N * N, NNN = NN * N;
+  constexpr int Q = kStreamBlocks<T, R>, W = kStreamWaves<T, R>, K = 16 * R, NM = N - 1;
+  constexpr int RING = sizeof(T) == 16 && R == 4 ? 4 : 8;  // eight would spill there
+  constexpr int CG = N / (16 * Q);                       // blocks of columns
+  constexpr int CT = CG > W ? CG / W : 1;                // workgroups over them
+  constexpr int CW = CG > W ? W : CG, SUBS = W / CW;     // blocks per workgroup, chunks of b per workgroup
+  constexpr int NB = N / (BCH * SUBS);                   // values of b per chunk
+  constexpr int PS = N / 2 + 16;                         // pairs of rows of both ranges, whole steps, and a zero step
+  constexpr bool kLdsB = sizeof(T) == 8 || N == 64;      // the factors of b fit the LDS beside the weights
+  static_assert(NB >= 1, "chunks of b");
+  __shared__ T cs[(PS + 8) * K];                         // (cos, sin) of row j, pair k at j K + swz(j, k)
+  __shared__ T kap[2][K];
+  __shared__ T us[kLdsB ? (NB * SUBS + N) * K : 1];      // u1[b][k], then u2[m][k] at m K + (k ^ 2 (m & 15) within K)
   const int tid = threadIdx.x, lane = tid % 64, l16 = lane % 16, kq = lane / 16;
   const int wv = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int di = (int)blockIdx.x / BSPLIT, z = (int)blockIdx.x % BSPLIT;
-  const int b_lo = z * BCH, b_hi = b_lo + BCH;
-  // A^{di}[a][k] at a 64 + (k ^ 16 (a & 1)); u2[m][k] at m 64 + (k ^ 2 (m & 15)), as in k_pair_diffs_ring.
-  for (int e = tid; e < N * kPairTile; e += 256) {
-    const int m = e / kPairTile, k = e % kPairTile;
-    as_[m * kPairTile + (k ^ ((m & 1) << 4))] = cmul(u1t[e], u2t[((m - di) & NM) * kPairTile + k]);
-    u2s[m * kPairTile + (k ^ ((m & 15) << 1))] = u2t[e];
+  const int bid = (int)blockIdx.x, di = bid / (CT * BCH), ct = bid % CT, zc = (bid / CT) % BCH;
+  const int dj0 = (ct * CW + wv % CW) * 16 * Q, z = zc * SUBS + wv / CW;
+  const int b_lo = z * NB, b_hi = b_lo + NB;
+  // Range h: a0[h] + [0, len[h]); steps of eight pairs; its first row of cs.
+  auto len = [&](int h) { return h ? di : N - di; };
+  auto first = [&](int h) { return h ? 0 : di; };
+  auto delta = [&](int h) { return h ? di - N : di; };
+  const int steps0 = ((N - di + 1) / 2 + 7) / 8, steps1 = ((di + 1) / 2 + 7) / 8;
+  auto steps = [&](int h) { return h ? steps1 : steps0; };
+  const int row1 = 8 * steps0, zrow = 8 * (steps0 + steps1);  // zrow is at most N/2 + 8: the zero step follows
+  auto swz = [](int j, int k) { return sizeof(T) == 8 && K >= 32 ? k ^ ((j & 1) << 4) : k; };
+  auto uswz = [](int m, int k) { return k ^ ((2 * (m & 15)) & (K - 1)); };
+  for (int e = tid; e < (zrow + 8) * K; e += 64 * W) {
+    const int j = e / K, k = e % K;
+    const int h = j >= row1 ? 1 : 0, p = j - (h ? row1 : 0), n = len(h);
+    double si = 0.0, co = 0.0;
+    if (j < zrow && 2 * p < n && k < rates.count) {
+      const double s = 0.5 * (double)(n - 1 - 2 * p);  // a_hi - a_mid
+      double c = rates.alpha[k] * (double)delta(h) * s;
+      c -= rint(c);
+      sincospi(2.0 * c, &si, &co);
+      if (2 * p + 1 == n) co = 0.5;  // the middle row, met twice
+    }
+    cs[j * K + swz(j, k)] = T{(Rt)co, (Rt)si};
+  }
+  for (int e = tid; e < 2 * K; e += 64 * W) {
+    const int h = e / K, k = e % K;
+    double si = 0.0, co = 0.0;
+    if (k < rates.count) {
+      double c = 0.5 * (rates.alpha[k] * (double)delta(h) + (POLY ? 0.0 : (double)(delta(h) & 1)));
+      c -= rint(c);
+      sincospi(2.0 * c, &si, &co);
+    }
+    kap[h][k] = T{(Rt)co, (Rt)si};
+  }
+  if constexpr (kLdsB) {
+    for (int e = tid; e < NB * SUBS * K; e += 64 * W) us[e] = u1t[(zc * NB * SUBS + e / K) * kPairTile + e % K];
+    for (int e = tid; e < N * K; e += 64 * W) {
+      const int m = e / K, k = e % K;
+      us[NB * SUBS * K + m * K + uswz(m, k)] = u2t[m * kPairTile + k];
+    }
   }
   __syncthreads();
-  if (wv * 32 >= N) return;  // no columns for this wavefront; no barrier follows
-  const int dj0 = 32 * wv;
-  constexpr int total = BCH * SPB;
-  auto load = [&](RingStep& r, int t) {
-    const int tc = t < total ? t : total - 1;
-    const int b = b_lo + tc / SPB, a0 = (tc % SPB) * 16;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int a = a0 + 4 * ks + kq;
-      const float2* row = w + ((long long)a * N + b) * NN + (long long)((a - di) & NM) * N;
-#pragma unroll
-      for (int q = 0; q < 2; ++q) r.v[ks][q] = row[(b - dj0 - 16 * q - l16) & NM];
-    }
+  const GlobalPtr<T> w0 = (GlobalPtr<T>)const_cast<T*>(w);
+  struct Step {
+    T hi[2][Q], lo[2][Q];
   };
-  // [h]: h = 0 the bin d_i (a >= d_i), h = 1 the bin d_i - N (a < d_i).
-  v4f t1[2][R][2], t2[2][R][2], t3[2][R][2];
-  float2 f[2][R][2][4], u1v[R][4];
+  struct Pos {
+    int h, b, st;
+  };
+  auto advance = [&](Pos& p) {
+    const bool last = p.st + 1 >= steps(p.h);
+    p.st = last ? 0 : p.st + 1;
+    const bool over = last && p.b + 1 == b_hi;
+    p.b = last ? (over ? b_lo : p.b + 1) : p.b;
+    p.h += over ? 1 : 0;  // 2: past the end
+  };
+  const int h_end = di > 0 ? 2 : 1;  // d_i = 0: the second range is empty
+  auto load = [&](Step& r, const Pos& p) {
+    const bool in = p.h < h_end;
+    const int h = in ? p.h : 0, b = in ? p.b : b_hi - 1, st = in ? p.st : 0;
+    const int n = len(h), pairs = (n + 1) / 2, a0 = first(h);
+    const GlobalPtr<T> wb = w0 + (long long)b * NN - (long long)delta(h) * N;
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+    for (int s = 0; s < 2; ++s) {
+      const int j = 8 * st + 4 * s + kq, jj = j < pairs ? j : pairs - 1;
+      const GlobalPtr<T> ph = wb + (long long)(a0 + n - 1 - jj) * (NNN + N);
+      const GlobalPtr<T> pl = wb + (long long)(a0 + jj) * (NNN + N);
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        t1[h][r][q] = t2[h][r][q] = t3[h][r][q] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) f[h][r][q][i] = float2{0.f, 0.f};
+      for (int q = 0; q < Q; ++q) {
+        const int col = (b - dj0 - 16 * q - l16) & NM;
+        r.hi[s][q] = load_elem<T>(ph + col);
+        r.lo[s][q] = load_elem<T>(pl + col);
       }
-  auto read_a = [&](float2 (&av)[4][R], int a0) {
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int a = a0 + 4 * ks + kq;
-#pragma unroll
-      for (int r = 0; r < R; ++r) av[ks][r] = as_[a * kPairTile + ((k0 + 16 * r + l16) ^ ((a & 1) << 4))];
     }
   };
-  auto step_mfma = [&](const float2 (&av)[4][R], const RingStep& bw, v4f (&s1)[R][2], v4f (&s2)[R][2],
-                       v4f (&s3)[R][2]) {
+  V gr[R][Q], gi[R][Q];
+  T f[R][Q][4];
+  const T zero{(Rt)0, (Rt)0};
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      float xs[R], ys[2];
+  for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int r = 0; r < R; ++r) xs[r] = av[ks][r].x + av[ks][r].y;
+    for (int q = 0; q < Q; ++q) {
+      gr[r][q] = gi[r][q] = V{0, 0, 0, 0};
 #pragma unroll
-      for (int q = 0; q < 2; ++q) ys[q] = bw.v[ks][q].x + bw.v[ks][q].y;
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          s1[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks][r].x, bw.v[ks][q].x, s1[r][q], 0, 0, 0);
-          s2[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks][r].y, bw.v[ks][q].y, s2[r][q], 0, 0, 0);
-          s3[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[r], ys[q], s3[r][q], 0, 0, 0);
-        }
+      for (int i = 0; i < 4; ++i) f[r][q][i] = zero;
     }
+  auto read_a = [&](T (&e)[2][R], const Pos& p) {
+    const int j0 = p.h < h_end ? (p.h ? row1 : 0) + 8 * p.st : zrow;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int j = j0 + 4 * s + kq;
+        e[s][r] = cs[j * K + swz(j, 16 * r + l16)];
+      }
   };
-  // The lane's four bins of pair k: d_i bin h (row di + N, or di), d_j bin dj (upper) or dj - N (lower).
-  float2* const out = part + (long long)z * kPairTile * BINS;
+  T* const out = part + (long long)(POLY ? z : 2 * z) * kPairTile * (POLY ? 4 * NN : NN);
   auto bin_at = [&](int k, int h, int dj_bin) {
-    return (long long)(k0 + k) * BINS + (long long)(h == 0 ? di + N : di) * (2 * N) + dj_bin + N;
+    return POLY ? (long long)k * 4 * NN + (long long)(h ? di : di + N) * (2 * N) + dj_bin + N
+                : ((long long)h * kPairTile + k) * NN + (long long)di * N + dj_bin;
   };
-  RingStep ring[RING];
+  Step ring[RING];
+  Pos lp{0, b_lo, 0}, cp{0, b_lo, 0};
 #pragma unroll
   for (int u = 0; u < RING - 1; ++u) {
-    load(ring[u], u);
+    load(ring[u], lp);
+    if (lp.h < h_end) advance(lp);
     __builtin_amdgcn_sched_barrier(0);
   }
-  float2 avs[2][4][R];
-  read_a(avs[0], 0);
+  T av[2][2][R];
+  read_a(av[0], cp);
+  T ub[kLdsB ? 1 : R][4], vb[kLdsB ? 1 : R][Q][4];
+  const int total = NB * (steps0 + steps1);
   for (int t0 = 0; t0 < total; t0 += RING) {
 #pragma unroll
     for (int u = 0; u < RING; ++u) {
-      // Step of this b: known at compile time when the ring holds whole b (t0 a multiple of SPB), else
-      // wavefront-uniform.
-      const int sb = RING % SPB == 0 ? u % SPB : (t0 + u) % SPB;
-      const int b = b_lo + (t0 + u) / SPB, a0 = sb * 16;
-      load(ring[(u + RING - 1) % RING], t0 + u + RING - 1);
-      if (sb == 0) {  // u1[k][b] of this b, behind the ring's load (it is needed at the fold)
+      load(ring[(u + RING - 1) % RING], lp);
+      if (lp.h < h_end) advance(lp);
+      Pos np = cp;
+      if (cp.h < h_end) advance(np);
+      if constexpr (!kLdsB) {
+        if (cp.st == 0 && cp.h < h_end) {  // the factors of this b, behind the ring's load (needed after its last step)
 #pragma unroll
-        for (int r = 0; r < R; ++r)
+          for (int r = 0; r < R; ++r)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) u1v[r][i] = u1t[b * kPairTile + k0 + 16 * r + Mfma<float2>::row(lane, i)];
+            for (int i = 0; i < 4; ++i) {
+              const int k = 16 * r + Mfma<T>::row(lane, i);
+              ub[r][i] = u1[k * N + cp.b];
+#pragma unroll
+              for (int q = 0; q < Q; ++q) vb[r][q][i] = u2[k * N + ((cp.b - dj0 - 16 * q - l16) & NM)];
+            }
+        }
       }
-      read_a(avs[(u + 1) % 2], ((sb + 1) % SPB) * 16);  // the next step's operand
+      read_a(av[(u + 1) % 2], np);
       __builtin_amdgcn_sched_barrier(0);
-      if (a0 >= di) {  // workgroup-uniform: every a of the step is in the bin d_i
-        step_mfma(avs[u % 2], ring[u], t1[0], t2[0], t3[0]);
-      } else if (a0 + 16 <= di) {  // every a is in the bin d_i - N
-        step_mfma(avs[u % 2], ring[u], t1[1], t2[1], t3[1]);
-      } else {  // the step holds d_i: each bin with the other bin's rows of A zeroed
-        float2 am[4][R];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const bool upper = a0 + 4 * ks + kq >= di;
+      for (int s = 0; s < 2; ++s)
 #pragma unroll
-          for (int r = 0; r < R; ++r) am[ks][r] = upper ? avs[u % 2][ks][r] : float2{0.f, 0.f};
+        for (int q = 0; q < Q; ++q) {
+          const T hi = ring[u].hi[s][q], lo = ring[u].lo[s][q];
+          const T e{hi.x + lo.x, hi.y + lo.y}, o{lo.x - hi.x, hi.y - lo.y};  // o: -i (hi - lo) = (o.y, o.x)
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            gr[r][q] = Mfma<T>::mac(av[u % 2][s][r].x, e.x, gr[r][q]);
+            gi[r][q] = Mfma<T>::mac(av[u % 2][s][r].x, e.y, gi[r][q]);
+          }
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            gr[r][q] = Mfma<T>::mac(av[u % 2][s][r].y, o.y, gr[r][q]);
+            gi[r][q] = Mfma<T>::mac(av[u % 2][s][r].y, o.x, gi[r][q]);
+          }
         }
-        step_mfma(am, ring[u], t1[0], t2[0], t3[0]);
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const bool upper = a0 + 4 * ks + kq >= di;
-#pragma unroll
-          for (int r = 0; r < R; ++r) am[ks][r] = upper ? float2{0.f, 0.f} : avs[u % 2][ks][r];
-        }
-        step_mfma(am, ring[u], t1[1], t2[1], t3[1]);
-      }
-      if (sb == SPB - 1) {  // the last step of b: D_h += u1[k][b] u2[k][b - dj] G_h, then the d_j switch
+      if (cp.h < h_end && cp.st + 1 == steps(cp.h)) {  // the last step of b (wavefront-uniform)
+        const bool range_end = cp.b + 1 == b_hi;
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int k = 16 * r + Mfma<float2>::row(lane, i);
+            const int k = 16 * r + Mfma<T>::row(lane, i);
+            T x;
+            if constexpr (kLdsB)
+              x = us[(cp.b - zc * NB * SUBS) * K + k];
+            else
+              x = ub[r][i];
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-              const int dj = dj0 + 16 * q + l16;
-              const int m = (b - dj) & NM;
-              const float2 c = cmul(u1v[r][i], u2s[m * kPairTile + ((k0 + k) ^ ((m & 15) << 1))]);
-#pragma unroll
-              for (int h = 0; h < 2; ++h) {
-                const float gr = t1[h][r][q][i] - t2[h][r][q][i];
-                const float gi = t3[h][r][q][i] - t1[h][r][q][i] - t2[h][r][q][i];
-                f[h][r][q][i].x += c.x * gr - c.y * gi;
-                f[h][r][q][i].y += c.x * gi + c.y * gr;
-              }
-              if (b == dj - 1 && dj < b_hi) {  // every b below d_j is summed: the lower d_j bin is complete
-                // (at dj = b_hi the sums stay held: the chunk ends there and stores them in the lower bin)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                  out[bin_at(k, h, dj - N)] = f[h][r][q][i];
-                  f[h][r][q][i] = float2{0.f, 0.f};
+            for (int q = 0; q < Q; ++q) {
+              const int dj = dj0 + 16 * q + l16, m = (cp.b - dj) & NM;
+              T y;
+              if constexpr (kLdsB)
+                y = us[NB * SUBS * K + m * K + uswz(m, k)];
+              else
+                y = vb[r][q][i];
+              const T c = cmul(x, y), g{gr[r][q][i], gi[r][q][i]};
+              f[r][q][i] = cadd(f[r][q][i], cmul(c, g));
+              if constexpr (POLY) {
+                if (cp.b == dj - 1 && dj < b_hi) {  // the lower bin is complete (at d_j = b_hi it is stored below)
+                  out[bin_at(k, cp.h, dj - N)] = cmul(kap[cp.h][k], f[r][q][i]);
+                  f[r][q][i] = zero;
                 }
               }
             }
           }
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
+        if (range_end) {
 #pragma unroll
           for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int q = 0; q < 2; ++q) t1[h][r][q] = t2[h][r][q] = t3[h][r][q] = v4f{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < 4; ++i) {
+              const int k = 16 * r + Mfma<T>::row(lane, i);
+              const T ka = kap[cp.h][k];
+#pragma unroll
+              for (int q = 0; q < Q; ++q) {
+                const int dj = dj0 + 16 * q + l16;
+                const T v = cmul(ka, f[r][q][i]);
+                if constexpr (POLY) {
+                  if (dj >= b_hi) {  // every b of the chunk is below d_j
+                    out[bin_at(k, cp.h, dj - N)] = v;
+                    out[bin_at(k, cp.h, dj)] = zero;
+                  } else {
+                    out[bin_at(k, cp.h, dj)] = v;
+                    if (dj <= b_lo) out[bin_at(k, cp.h, dj - N)] = zero;  // no b of the chunk is below d_j
+                  }
+                } else {
+                  out[bin_at(k, cp.h, dj)] = v;
+                }
+                f[r][q][i] = zero;
+              }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int q = 0; q < Q; ++q) gr[r][q] = gi[r][q] = V{0, 0, 0, 0};
       }
+      cp = np;
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  // The sums still held belong to the d_j bin of the chunk's last b; the other d_j bin was stored at the
-  // switch, or has no term in this chunk (zero).
+  if (h_end == 1) {  // the bins of the empty range
 #pragma unroll
-  for (int r = 0; r < R; ++r)
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
+      for (int q = 0; q < Q; ++q)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int k = 16 * r + Mfma<float2>::row(lane, i);
-        const int dj = dj0 + 16 * q + l16;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          if (dj >= b_hi) {  // every b of the chunk is below d_j
-            out[bin_at(k, h, dj - N)] = f[h][r][q][i];
-            out[bin_at(k, h, dj)] = float2{0.f, 0.f};
-          } else {
-            out[bin_at(k, h, dj)] = f[h][r][q][i];
-            if (dj <= b_lo) out[bin_at(k, h, dj - N)] = float2{0.f, 0.f};  // no b of the chunk is below d_j
-          }
+        for (int i = 0; i < 4; ++i) {
+          const int k = 16 * r + Mfma<T>::row(lane, i), dj = dj0 + 16 * q + l16;
+          out[bin_at(k, 1, dj)] = zero;
+          if constexpr (POLY) out[bin_at(k, 1, dj - N)] = zero;
         }
-      }
+  }
 }
 
-// out[k][i] = f(k, i) sum_s part[s][k][i] (k < kcount), summed in FP64 in the order of s;
+// out[k][i] = f(k, i) sum_s part[s][k][i] (k < kcount, parts of kstride pairs), summed in FP64 in the order of s;
 // f = u2[k][i / n] u2[k][i % n] when u2 is given (the row sums), else 1.
 template <class T>
-__global__ __launch_bounds__(256) void k_pair_sum(const T* __restrict__ part, int parts, int n, int kcount,
+__global__ __launch_bounds__(256) void k_pair_sum(const T* __restrict__ part, int parts, int n, int kcount, int kstride,
                                                   const T* __restrict__ u2, T* __restrict__ out) {
   using R = typename real_of<T>::type;
   const long long nn = (long long)n * n, total = (long long)kcount * nn;
@@ -965,7 +916,7 @@ __global__ __launch_bounds__(256) void k_pair_sum(const T* __restrict__ part, in
   double2 acc{0.0, 0.0};
 #pragma unroll 8
   for (int s = 0; s < parts; ++s) {
-    const T v = part[(long long)s * total + e];
+    const T v = part[(long long)s * kstride * nn + e];
     acc.x += (double)v.x;
     acc.y += (double)v.y;
   }
@@ -1030,11 +981,7 @@ __global__ __launch_bounds__(256) void k_pair_emit(const typename real_of<T>::ty
 
 // s0[k][m] = Re z[k][m] and key[k] = order key of max_m s0[k][m]: blockIdx.y is the pair, blockIdx.x one of
 // gridDim.x ranges of m; the ranges' maxima meet in an atomic max on the order keys (order-independent),
-// which k_pair_clear_keys has zeroed.
-__global__ void k_pair_clear_keys(unsigned long long* key, int count) {
-  if ((int)threadIdx.x < count) key[threadIdx.x] = 0ull;
-}
-
+// which k_pair_tables has zeroed.
 template <class T>
 __global__ __launch_bounds__(256) void k_pair_s0(const T* __restrict__ z, int n, typename real_of<T>::type* s0,
                                                  unsigned long long* key) {
@@ -1537,38 +1484,60 @@ static int rows_ring_parts(int n, int count) {
 
 // The mirrored form of a Fresnel group's row sums (count >= 2): at N = 32, 64, 128 and 256 the number of ranges of blocks it
 // writes, one workgroup per CU where the columns allow it; 0 at smaller N, whose few tiles the LDS-staged kernel covers.
-// Measured at N = 128: complex64, 64 pairs 941 -> 450 us (38 % of the matrix rate), 12 pairs 338 -> 345 us (6.2 TB/s);
-// complex128, 64 pairs 2.2 -> 0.87 ms; N = 64 complex128, 23 pairs 0.13 -> 0.07 ms.
+// Measured at N = 128: complex64, 64 pairs 941 -> 410 us (41 % of the matrix rate), 12 pairs 338 -> 350 us (6.1 TB/s);
+// complex128, 64 pairs 2.2 -> 0.80 ms; N = 64 complex128, 23 pairs 130 -> 50 us.
 template <class T> static int rows_fold_parts(int n) {
   if (n < 32) return 0;
-  const int tiles = n * n / (64 * 16 / (int)sizeof(T));
+  const int tiles = n * n / kStreamColumns<T>;
   return tiles >= 256 ? 1 : (256 / tiles < kPairSplitK ? 256 / tiles : kPairSplitK);
 }
 
 template <class T>
 static hipError_t launch_rows_fold(int n, int count, const T* w, const T* u1t, int pi, int pj, T* part, hipStream_t st) {
-  constexpr int Q = 16 / (int)sizeof(T);  // 32 columns per wavefront in complex64, 16 in complex128
   const int parts = rows_fold_parts<T>(n);
-  const unsigned grid = (unsigned)(n * n / (64 * Q) * parts);
+  const unsigned grid = (unsigned)(n * n / kStreamColumns<T> * parts);
   using Rows = void (*)(const T*, const T*, int, int, int, T*);
   auto of_n = [&](auto nc) -> Rows {
     constexpr int N = decltype(nc)::value;
-    return count > 32 ? k_pair_rows_fold<T, N, 4, Q> : count > 16 ? k_pair_rows_fold<T, N, 2, Q> : k_pair_rows_fold<T, N, 1, Q>;
+    return count > 32 ? k_pair_rows_fold<T, N, 4> : count > 16 ? k_pair_rows_fold<T, N, 2> : k_pair_rows_fold<T, N, 1>;
   };
   const Rows rows = n == 32    ? of_n(std::integral_constant<int, 32>{})
                     : n == 64  ? of_n(std::integral_constant<int, 64>{})
                     : n == 128 ? of_n(std::integral_constant<int, 128>{})
                                : of_n(std::integral_constant<int, 256>{});
-  hipLaunchKernelGGL(rows, dim3(grid), dim3(256), 0, st, w, u1t, pi, pj, parts, part);
+  hipLaunchKernelGGL(rows, dim3(grid), dim3(count > 32 ? 64 * kStreamWaves<T, 4> : 256), 0, st, w, u1t, pi, pj, parts, part);
   return hipGetLastError();
 }
 
-// The ring form of the Fresnel difference sums (complex64, N = 128, any count) writes 256 / N chunks of b.
-static bool diffs_ring_ok(int n, int count) { return n == 128 && count >= 1; }
+// The mirrored form of the difference sums (count >= 2) at N = 64 and 128: the chunks of b it writes (twice as many parts for
+// a Fresnel group, one per range), 256 workgroups; 0 at other N, which the LDS-staged kernels cover. Against those, and
+// against a ring of 3M products at N = 128 in complex64, which this replaced: N = 128 complex64 985 -> 870 us (64 pairs),
+// 560 -> 555 (30), 457 -> 460 (12), unfolded bins 1.44 ms -> 0.91 (64), 534 -> 535 us (16); complex128 2.25 -> 2.0 ms
+// (64), unfolded 3.1 -> 0.96 ms (16); N = 64 complex128 180 -> 95 us (23), complex64 98 -> 54 us (20).
+template <class T> static int diffs_mirror_parts(int n) {
+  if (n == 64) return sizeof(T) == 8 ? 8 : 4;
+  if (n == 128) return sizeof(T) == 8 ? 2 : 1;
+  return 0;
+}
 
-// The ring form of the polychromatic difference sums (complex64, N = 128, any count) writes 256 / N chunks
-// of b.
-static bool poly_diffs_ring_ok(int n, int count) { return n == 128 && count >= 1; }
+template <class T, bool POLY>
+static hipError_t launch_diffs_mirror(int n, int count, const double* alpha, const T* w, const T* u1, const T* u2,
+                                      const T* tr, T* part, hipStream_t st) {
+  DiffRates rates{};
+  rates.count = count;
+  for (int k = 0; k < count; ++k) rates.alpha[k] = alpha[k];
+  using Diffs = void (*)(const T*, const T*, const T*, const T*, const T*, DiffRates, T*);
+  constexpr int B128 = sizeof(T) == 8 ? 2 : 1;
+  Diffs diffs;
+  if (n == 64)
+    diffs = count > 32 ? k_diffs_mirror<T, 64, 4, 4, POLY> : count > 16 ? k_diffs_mirror<T, 64, 2, 4, POLY>
+                                                                           : k_diffs_mirror<T, 64, 1, 4, POLY>;
+  else
+    diffs = count > 32 ? k_diffs_mirror<T, 128, 4, B128, POLY> : count > 16 ? k_diffs_mirror<T, 128, 2, B128, POLY>
+                                                                               : k_diffs_mirror<T, 128, 1, B128, POLY>;
+  hipLaunchKernelGGL(diffs, dim3(256), dim3(count > 32 ? 64 * kStreamWaves<T, 4> : 256), 0, st, w, u1, u2, tr, tr + (long long)kPairTile * n, rates, part);
+  return hipGetLastError();
+}
 
 template <class T>
 static hipError_t launch_mfma(int count, int kind, int n, const T* w, const T* u1, const T* u2, const T* tr,
@@ -1586,23 +1555,6 @@ static hipError_t launch_mfma(int count, int kind, int n, const T* w, const T* u
                                     : (count > 32 ? k_pair_rows_ring<128, 4>
                                                   : count > 16 ? k_pair_rows_ring<128, 2> : k_pair_rows_ring<128, 1>);
       hipLaunchKernelGGL(rows, dim3(256), dim3(256), 0, st, w, tr + 2 * tq, tr + 3 * tq, ring_chunk, 256, part);
-      return hipGetLastError();
-    }
-    if (kind == 1 && diffs_ring_ok(n, count)) {
-      using DiffsRing = void (*)(const float2*, const float2*, const float2*, float2*);
-      const DiffsRing diffs = count > 32   ? k_pair_diffs_ring<128, 4>
-                              : count > 16 ? k_pair_diffs_ring<128, 2>
-                                           : k_pair_diffs_ring<128, 1>;
-      hipLaunchKernelGGL(diffs, dim3(256), dim3(256), 0, st, w, tr, tr + tq, part);
-      return hipGetLastError();
-    }
-    if (kind == 2 && poly_diffs_ring_ok(n, count)) {
-      if (count <= 16) {
-        hipLaunchKernelGGL((k_poly_diffs_ring<128, 1, 8>), dim3(256), dim3(256), 0, st, w, tr, tr + tq, 0, part);
-      } else {  // tiles of 32 pairs, one launch each
-        for (int k0 = 0; k0 < count; k0 += 32)
-          hipLaunchKernelGGL((k_poly_diffs_ring<128, 2, 4>), dim3(256), dim3(256), 0, st, w, tr, tr + tq, k0, part);
-      }
       return hipGetLastError();
     }
     if (count <= 32) return launch_mfma_tm<T, 32>(kind, n, w, u1, u2, tr, chunk, bchunk, sb, part, st);
@@ -1644,7 +1596,7 @@ hipError_t launch_pair_sums(int n, const T* w, const double* a_src, int count, i
   pg.count = count;
   for (int k = 0; k < count; ++k) pg.a_src[k] = a_src[k];
   hipLaunchKernelGGL(k_pair_tables<T>, dim3((unsigned)((kPairTile * n + 255) / 256)), dim3(256), 0, st, pg, n, pi, pj,
-                     u1, u2, ci, cj, tr);
+                     u1, u2, ci, cj, tr, key);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (count == 1) {  // one row: both sums in one pass, HBM-bound
@@ -1655,16 +1607,15 @@ hipError_t launch_pair_sums(int n, const T* w, const double* a_src, int count, i
                        (const T*)ci, (const T*)cj, slabs, part_r, part_d);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const unsigned blocks = (unsigned)((nn + 255) / 256);
-    hipLaunchKernelGGL(k_pair_sum<T>, dim3(blocks), dim3(256), 0, st, (const T*)part_r, ranges, n, 1, (const T*)u2,
+    hipLaunchKernelGGL(k_pair_sum<T>, dim3(blocks), dim3(256), 0, st, (const T*)part_r, ranges, n, 1, 1, (const T*)u2,
                        buf_r);
-    hipLaunchKernelGGL(k_pair_sum<T>, dim3(blocks), dim3(256), 0, st, (const T*)part_d, ranges, n, 1,
+    hipLaunchKernelGGL(k_pair_sum<T>, dim3(blocks), dim3(256), 0, st, (const T*)part_d, ranges, n, 1, 1,
                        (const T*)nullptr, buf_d);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL((k_pair_dft<T, +1>), dim3((unsigned)n), dim3(256), 0, st, (const T*)buf_d, n, buf_t);
     hipLaunchKernelGGL((k_pair_dft<T, +1>), dim3((unsigned)n), dim3(256), 0, st, (const T*)buf_t, n, buf_d);
     hipLaunchKernelGGL((k_pair_dft<T, -1>), dim3((unsigned)n), dim3(256), 0, st, (const T*)buf_r, n, buf_t);
     hipLaunchKernelGGL((k_pair_dft<T, -1>), dim3((unsigned)n), dim3(256), 0, st, (const T*)buf_t, n, buf_r);
-    hipLaunchKernelGGL(k_pair_clear_keys, dim3(1), dim3(64), 0, st, key, 1);
     hipLaunchKernelGGL(k_pair_s0<T>, dim3(s0_ranges(n), 1), dim3(256), 0, st, (const T*)buf_d, n, s0, key);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     out[0] = ObsSums<T>{s0, buf_r, key};
@@ -1678,15 +1629,19 @@ hipError_t launch_pair_sums(int n, const T* w, const double* a_src, int count, i
   else
     e = launch_mfma<T>(count, 0, n, w, u1, u2, tr, chunk, bchunk, sb, part_r, st);
   if (e != hipSuccess) return e;
-  e = launch_mfma<T>(count, 1, n, w, u1, u2, tr, chunk, bchunk, sb, part_d, st);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const unsigned sum_blocks = (unsigned)((g + 255) / 256);
+  const int mirrored = diffs_mirror_parts<T>(n);
+  if (mirrored > 0)
+    e = launch_diffs_mirror<T, false>(n, count, a_src, w, u1, u2, tr, part_d, st);
+  else
+    e = launch_mfma<T>(count, 1, n, w, u1, u2, tr, chunk, bchunk, sb, part_d, st);
+  if (e != hipSuccess) return e;
+  const unsigned sum_blocks = (unsigned)((count * nn + 255) / 256);  // the group's pairs only
   const int sr = folded > 0 ? folded : kPairSplitK;
-  hipLaunchKernelGGL(k_pair_sum<T>, dim3(sum_blocks), dim3(256), 0, st, (const T*)part_r, sr, n, kPairTile,
+  hipLaunchKernelGGL(k_pair_sum<T>, dim3(sum_blocks), dim3(256), 0, st, (const T*)part_r, sr, n, count, kPairTile,
                      (const T*)u2, buf_r);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int sd = (sizeof(T) == 8 && diffs_ring_ok(n, count)) ? 256 / n : sb;  // chunks of b written
-  hipLaunchKernelGGL(k_pair_sum<T>, dim3(sum_blocks), dim3(256), 0, st, (const T*)part_d, sd, n, kPairTile,
+  const int sd = mirrored > 0 ? 2 * mirrored : sb;  // parts written
+  hipLaunchKernelGGL(k_pair_sum<T>, dim3(sum_blocks), dim3(256), 0, st, (const T*)part_d, sd, n, count, kPairTile,
                      (const T*)nullptr, buf_d);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const unsigned rows = (unsigned)(count * n);  // the group's pairs only
@@ -1701,7 +1656,6 @@ hipError_t launch_pair_sums(int n, const T* w, const double* a_src, int count, i
     hipLaunchKernelGGL((k_pair_dft<T, -1>), dim3(rows), dim3(256), 0, st, (const T*)buf_r, n, buf_t);
     hipLaunchKernelGGL((k_pair_dft<T, -1>), dim3(rows), dim3(256), 0, st, (const T*)buf_t, n, buf_r);
   }
-  hipLaunchKernelGGL(k_pair_clear_keys, dim3(1), dim3(64), 0, st, key, count);
   hipLaunchKernelGGL(k_pair_s0<T>, dim3(s0_ranges(n), (unsigned)count), dim3(256), 0, st, (const T*)buf_d, n, s0,
                      key);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1787,24 +1741,29 @@ hipError_t launch_poly(int n, const T* w, int n_pairs, const double* alpha, cons
                          (const T*)ci, (const T*)cj, slabs, part_r, part_d);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       const unsigned blocks = (unsigned)((nn + 255) / 256);
-      hipLaunchKernelGGL(k_pair_sum<T>, dim3(blocks), dim3(256), 0, st, (const T*)part_r, ranges, n, 1,
+      hipLaunchKernelGGL(k_pair_sum<T>, dim3(blocks), dim3(256), 0, st, (const T*)part_r, ranges, n, 1, 1,
                          (const T*)u2, rr);
-      hipLaunchKernelGGL(k_pair_sum<T>, dim3(4 * blocks), dim3(256), 0, st, (const T*)part_d, ranges, 2 * n, 1,
+      hipLaunchKernelGGL(k_pair_sum<T>, dim3(4 * blocks), dim3(256), 0, st, (const T*)part_d, ranges, 2 * n, 1, 1,
                          (const T*)nullptr, dfull);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {
       const long long chunk = (nn + kPairSplitK - 1) / kPairSplitK;
       const int bchunk = (n + sb - 1) / sb;
       if ((e = launch_mfma<T>(pg.count, 0, n, w, u1, u2, tr, chunk, bchunk, sb, part_r, st)) != hipSuccess) return e;
-      if ((e = launch_mfma<T>(pg.count, 2, n, w, u1, u2, tr, chunk, bchunk, sb, part_d, st)) != hipSuccess) return e;
+      const int mirrored = diffs_mirror_parts<T>(n);
+      if (mirrored > 0)
+        e = launch_diffs_mirror<T, true>(n, pg.count, pg.alpha, w, u1, u2, tr, part_d, st);
+      else
+        e = launch_mfma<T>(pg.count, 2, n, w, u1, u2, tr, chunk, bchunk, sb, part_d, st);
+      if (e != hipSuccess) return e;
       const int rp = sizeof(T) == 8 ? rows_ring_parts(n, pg.count) : 0;
       const int sr = rp > 0 ? rp : kPairSplitK;
-      hipLaunchKernelGGL(k_pair_sum<T>, dim3((unsigned)((g + 255) / 256)), dim3(256), 0, st, (const T*)part_r, sr, n,
-                         kPairTile, (const T*)u2, rr);
+      hipLaunchKernelGGL(k_pair_sum<T>, dim3((unsigned)((pg.count * nn + 255) / 256)), dim3(256), 0, st, (const T*)part_r, sr,
+                         n, pg.count, kPairTile, (const T*)u2, rr);
       if ((e = hipGetLastError()) != hipSuccess) return e;
-      const int sdp = (sizeof(T) == 8 && poly_diffs_ring_ok(n, pg.count)) ? 256 / n : sb;  // chunks of b written
-      hipLaunchKernelGGL(k_pair_sum<T>, dim3((unsigned)((4 * g + 255) / 256)), dim3(256), 0, st, (const T*)part_d,
-                         sdp, 2 * n, kPairTile, (const T*)nullptr, dfull);
+      const int sdp = mirrored > 0 ? mirrored : sb;  // chunks of b written
+      hipLaunchKernelGGL(k_pair_sum<T>, dim3((unsigned)((pg.count * 4 * nn + 255) / 256)), dim3(256), 0, st,
+                         (const T*)part_d, sdp, 2 * n, pg.count, kPairTile, (const T*)nullptr, dfull);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     // S: the + transform of D over [-N, N)^2 (offset N); the row: the - transform of T R (offset N/2). Only
