@@ -86,6 +86,57 @@ __global__ __launch_bounds__(256) void k_mu_slice(const T* __restrict__ w, int n
   mu[m] = out;
 }
 
+// The same slice in one launch for N <= 64, where a call is bound by its launches: one workgroup gathers S, takes its
+// maximum and divides the row (the same operations on the same values, so the same bits). N = 16: three launches cost the
+// host 7.5 us more than one; at N = 128 one workgroup's gather (16384 lines) would take longer than three launches.
+constexpr int kMuOneThreads = 1024, kMuOneMaxN = 64;
+template <class T>
+__global__ __launch_bounds__(kMuOneThreads) void k_mu_slice_one(const T* __restrict__ w, int n, int p1, double floor_rel,
+                                                                T* __restrict__ mu) {
+  using R = typename real_of<T>::type;
+  constexpr int V = kMuOneMaxN * kMuOneMaxN / kMuOneThreads;
+  __shared__ unsigned long long red[kMuOneThreads];
+  __shared__ R s_p1;
+  const int nn = n * n, tid = threadIdx.x;
+  const long long step = nn + 1;
+  R s2[V];
+  T v[V];
+  unsigned long long k = 0ull;
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    const int m = tid + i * kMuOneThreads;
+    s2[i] = load_or_first(w, m < nn, m * step).x;
+    v[i] = load_or_first(w, m < nn, (long long)p1 * nn + m);
+  }
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    const int m = tid + i * kMuOneThreads;
+    if (m >= nn) continue;
+    const unsigned long long q = order_key((double)s2[i]);
+    k = q > k ? q : k;
+    if (m == p1) s_p1 = s2[i];
+  }
+  red[tid] = k;
+  __syncthreads();
+  for (int h = kMuOneThreads / 2; h > 0; h >>= 1) {
+    if (tid < h && red[tid + h] > red[tid]) red[tid] = red[tid + h];
+    __syncthreads();
+  }
+  const R tau = (R)(floor_rel * key_value(red[0]));
+  const R s1 = s_p1;
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    const int m = tid + i * kMuOneThreads;
+    if (m >= nn) continue;
+    T out{(R)0, (R)0};
+    if (s1 > tau && s2[i] > tau) {
+      const R d = sqrt(s1) * sqrt(s2[i]);
+      out = T{v[i].x / d, v[i].y / d};
+    }
+    mu[m] = out;
+  }
+}
+
 template <class T>
 __global__ __launch_bounds__(256) void k_mu_full(const T* __restrict__ w, int n, double floor_rel,
                                                  const typename real_of<T>::type* __restrict__ s,
@@ -125,6 +176,10 @@ hipError_t launch_coherence(int n, const T* w, int ip, int jp, double floor_rel,
   const long long nn = (long long)n * n;
   auto* key = reinterpret_cast<unsigned long long*>(scratch);
   auto* s = reinterpret_cast<R*>(reinterpret_cast<char*>(scratch) + 256);
+  if (ip >= 0 && n <= kMuOneMaxN) {
+    hipLaunchKernelGGL(k_mu_slice_one<T>, dim3(1), dim3(kMuOneThreads), 0, st, w, n, ip * n + jp, floor_rel, mu);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_clear_key, dim3(1), dim3(1), 0, st, key);
   hipLaunchKernelGGL(k_sdiag_max<T>, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, st, w, n, s, key);
   if (ip >= 0) {
