@@ -123,7 +123,9 @@ def _check(status: int, where: str) -> None:
 
 
 def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current HIP stream of the current device. The raw handle costs 0.4 us; a torch.cuda.Stream object
+    costs 2.8 us, a third of a small call (N = 16: build + propagation + S + mu 50 -> 41 us)."""
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _code(dtype: torch.dtype) -> int:
