@@ -99,6 +99,124 @@ __global__ __launch_bounds__(Split<N>::N2 * C) void k_axis_fft(const T* src, T* 
   }
 }
 
+// Job ja's input is the second-point transform of diag(g), formed here instead of read (see launch_operator_diag):
+// its plane wave is separable into a factor of the tile's outer index and the column, fixed for a thread, and one
+// of the axis index and the column. Job jb reads the array, as in k_axis_fft. Against a kernel that writes the
+// array and a pass that reads it back, the operator on diag(g): N = 64 complex64 109 -> 72 us, complex128 240 -> 141;
+// N = 128 complex64 1.97 -> 1.77 ms, complex128 3.95 -> 2.59; N = 256 34.5 -> 24.4 and 67.5 -> 45.0 ms. Bound by
+// the writes of this pass and by the sweep of the i1 pass that follows.
+template <class T> struct DiagInput {
+  const typename real_of<T>::type* g;
+  Chirp pre1, pre2, post2;
+  int sign2;
+};
+
+// a b with its fused products written out (re: a.x b.x, im: a.x b.y), so that every kernel that forms the plane
+// waves of diag(g) gives the same bits.
+template <class T> __device__ __forceinline__ T cmul_fixed(T a, T b) {
+  return T{fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x)};
+}
+
+template <class T, int N, int C, int SIGN>
+__global__ __launch_bounds__(Split<N>::N2 * C) void k_axis_fft_diag(T* dst, AxisJob ja, AxisJob jb, DiagInput<T> in) {
+  using S = Split<N>;
+  constexpr int N1 = S::N1, N2 = S::N2, Q = S::Q;
+  constexpr int NT = N2 * C;
+  __shared__ T xch[N * C];
+  __shared__ T tpre[N], tpost[N], tw[N];
+
+  // Two independent jobs may share one launch (the j1 pass of one column chunk and the i1 pass of
+  // the previous one). With equal sizes they interleave block by block.
+  long long bid = blockIdx.x;
+  bool second;
+  if (jb.blocks == ja.blocks) {
+    second = (bid & 1) != 0;
+    bid >>= 1;
+  } else {
+    second = bid >= ja.blocks;
+    if (second) bid -= ja.blocks;
+  }
+  const AxisJob& j = second ? jb : ja;
+
+  for (int i = threadIdx.x; i < N; i += NT) {
+    if (second) tpre[i] = chirp_entry<T>(j.pre, i, N);
+    tpost[i] = chirp_entry<T>(j.post, i, N);
+    tw[i] = twiddle_entry<T, SIGN>(i, N);
+  }
+  __syncthreads();
+
+  const int c = threadIdx.x % C;
+  const int t = threadIdx.x / C;
+  const long long o = bid / j.tiles_per_outer;
+  const long long c0 = (bid - o * j.tiles_per_outer) * C;
+  const long long base = o * j.outer_stride + j.inner_offset + c0 + c;
+  const long long as = j.axis_stride;
+
+  T v[N1];
+  if (!second) {  // uniform over the workgroup
+    using R = typename real_of<T>::type;
+    __shared__ T tw2[N], ts[N], q1[N], q2[N];  // ts[b]: the scalar of slab (o, b)
+    T* tp = tpre;                              // not used by this job otherwise
+    for (int e = threadIdx.x; e < 4 * N; e += NT) {  // one kind of entry per wavefront where N >= 64
+      const int i = e % N;
+      switch (e / N) {
+        case 0: tp[i] = chirp_entry<T>(in.post2, i, N); break;
+        case 1: q1[i] = chirp_entry<T>(in.pre1, i, N); break;
+        case 2: q2[i] = chirp_entry<T>(in.pre2, i, N); break;
+        default: tw2[i] = in.sign2 < 0 ? twiddle_entry<T, -1>(i, N) : twiddle_entry<T, +1>(i, N);
+      }
+    }
+    __syncthreads();
+    const int a1 = (int)o;
+    for (int i = threadIdx.x; i < N; i += NT)
+      ts[i] = cscale(cmul_fixed(cmul_fixed(q1[a1], q1[i]), cmul_fixed(q2[a1], q2[i])), (R)in.g[o * N + i]);
+    __syncthreads();
+    const int m2 = (int)(j.inner_offset + c0) + c, p = m2 / N, q = m2 % N;
+    const T row = cmul_fixed(tp[p], tw2[(a1 * p) & (N - 1)]);
+    const T tq = tp[q];
+#pragma unroll
+    for (int a = 0; a < N1; ++a) {
+      const int b = N2 * a + t;
+      v[a] = cmul_fixed(ts[b], cmul_fixed(row, cmul_fixed(tq, tw2[(b * q) & (N - 1)])));
+      asm("" : "+v"(v[a].x), "+v"(v[a].y));  // rounded here, as when it was stored: no fused sum with the DFT's adds
+    }
+  } else {
+#pragma unroll
+    for (int a = 0; a < N1; ++a) {
+      const int n = N2 * a + t;
+      if constexpr (sizeof(T) == 16) {
+        typedef typename real_of<T>::type R;
+        typedef R r2 __attribute__((ext_vector_type(2)));
+        const r2 x = __builtin_nontemporal_load(reinterpret_cast<const r2*>(dst + base + (long long)n * as));
+        v[a] = cmul(T{x.x, x.y}, tpre[n]);
+      } else {
+        v[a] = cmul(dst[base + (long long)n * as], tpre[n]);
+      }
+    }
+  }
+  dft_reg<N1, SIGN>(v);
+#pragma unroll
+  for (int k1 = 0; k1 < N1; ++k1) xch[(k1 * N2 + t) * C + c] = cmul(v[k1], tw[(t * k1) & (N - 1)]);
+  __syncthreads();
+  T u[N1];
+#pragma unroll
+  for (int r = 0; r < Q; ++r) {
+    const int k1 = t + N2 * r;
+#pragma unroll
+    for (int n2 = 0; n2 < N2; ++n2) u[r * N2 + n2] = xch[(k1 * N2 + n2) * C + c];
+    dft_reg<N2, SIGN>(&u[r * N2]);
+  }
+#pragma unroll
+  for (int r = 0; r < Q; ++r) {
+    const int k1 = t + N2 * r;
+#pragma unroll
+    for (int k2 = 0; k2 < N2; ++k2) {
+      const int k = k1 + N1 * k2;
+      dst[base + (long long)k * as] = cmul(u[r * N2 + k2], tpost[k]);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Contiguous axis (rows of N elements). A workgroup takes B consecutive rows.
 // GEN > 0 (B <= N, so that the rows of a workgroup lie in one slab p1 = (i1, j1)): the input rows are
@@ -630,14 +748,17 @@ static bool make_job(const AxisRange& ar, const Chirp& pre, const Chirp& post, A
 template <class T, int N, int SIGN>
 static hipError_t launch_axis_n(const T* src, T* dst, const AxisRange& a, const Chirp& pre_a, const Chirp& post_a,
                                 const AxisRange* b, const Chirp& pre_b, const Chirp& post_b, bool nt_loads,
-                                hipStream_t st) {
+                                hipStream_t st, const DiagInput<T>* diag) {
   constexpr int C = axis_cols<T, N>();
   AxisJob ja{}, jb{};
   if (!make_job<T, N>(a, pre_a, post_a, &ja)) return hipErrorInvalidValue;
   if (b != nullptr && !make_job<T, N>(*b, pre_b, post_b, &jb)) return hipErrorInvalidValue;
   const long long blocks = ja.blocks + jb.blocks;
   if (blocks > 0x7fffffffll) return hipErrorInvalidValue;
-  if (nt_loads)
+  if (diag)
+    hipLaunchKernelGGL((k_axis_fft_diag<T, N, C, SIGN>), dim3((unsigned)blocks), dim3(Split<N>::N2 * C), 0, st, dst, ja,
+                       jb, *diag);
+  else if (nt_loads)
     hipLaunchKernelGGL((k_axis_fft<T, N, C, SIGN, true>), dim3((unsigned)blocks), dim3(Split<N>::N2 * C), 0, st, src,
                        dst, ja, jb);
   else
@@ -733,11 +854,11 @@ static hipError_t launch_slab_n(const T* src, T* dst, long long slab0, long long
 template <class T>
 hipError_t launch_axis_range(int n, const T* src, T* dst, int sign, const AxisRange& a, const Chirp& pre_a,
                              const Chirp& post_a, const AxisRange* b, const Chirp& pre_b, const Chirp& post_b,
-                             hipStream_t st, bool nt_loads = sizeof(T) == 16) {
+                             hipStream_t st, bool nt_loads = sizeof(T) == 16, const DiagInput<T>* diag = nullptr) {
   if (sign < 0) {
-    WOLF_DISPATCH_N(n, (launch_axis_n<T, NN, -1>(src, dst, a, pre_a, post_a, b, pre_b, post_b, nt_loads, st)))
+    WOLF_DISPATCH_N(n, (launch_axis_n<T, NN, -1>(src, dst, a, pre_a, post_a, b, pre_b, post_b, nt_loads, st, diag)))
   }
-  WOLF_DISPATCH_N(n, (launch_axis_n<T, NN, +1>(src, dst, a, pre_a, post_a, b, pre_b, post_b, nt_loads, st)))
+  WOLF_DISPATCH_N(n, (launch_axis_n<T, NN, +1>(src, dst, a, pre_a, post_a, b, pre_b, post_b, nt_loads, st, diag)))
 }
 
 template <class T>
@@ -960,7 +1081,8 @@ hipError_t launch_operator(int n, const T* in, T* out, const OperatorTables& op,
 
 // ---------------------------------------------------------------------------------------------
 // Operator applied to a diagonal input diag(g) (e.g. the gradient of a loss of S = Re diag W).
-// The second-point 2D DFT of row m1 = (a, b) of diag(g) is a plane wave:
+// The second-point 2D DFT of row m1 = (a, b) of diag(g) is a plane wave, formed by the j1 pass itself
+// (k_axis_fft_diag), or written for the cooperative first-point pass, which reads its input:
 //   Y[m1; (p, q)] = g(m1) pre1[a] pre1[b] pre2[a] pre2[b] w^{a p} w^{b q} post2[p] post2[q],
 // with w = e^{sign2 2 pi i / N}. A write-only kernel makes it without reading an N^4 input.
 // ---------------------------------------------------------------------------------------------
@@ -998,15 +1120,20 @@ hipError_t launch_operator_diag(int n, const typename real_of<T>::type* g, T* ou
                                 const Plan& plan, void* counters, hipStream_t st) {
   const long long N = n, NN = N * N, NNN = NN * N;
   const Chirp ident{0.0, 1.0, +1, 0};
-  if (op.sign2 < 0)
-    hipLaunchKernelGGL((k_slab_from_diag<T, -1>), dim3((unsigned)NN), dim3(256), 0, st, g, out, n, op.pre1, op.pre2,
-                       op.post2);
-  else
-    hipLaunchKernelGGL((k_slab_from_diag<T, +1>), dim3((unsigned)NN), dim3(256), 0, st, g, out, n, op.pre1, op.pre2,
-                       op.post2);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (plan.coop) return launch_first_point_coop<T>(n, out, op, ident, plan.coop_cols, plan.coop_lookahead, counters, st);
+  hipError_t e;
+  if (plan.coop) {  // the cooperative first-point pass reads the array
+    if (op.sign2 < 0)
+      hipLaunchKernelGGL((k_slab_from_diag<T, -1>), dim3((unsigned)NN), dim3(256), 0, st, g, out, n, op.pre1, op.pre2,
+                         op.post2);
+    else
+      hipLaunchKernelGGL((k_slab_from_diag<T, +1>), dim3((unsigned)NN), dim3(256), 0, st, g, out, n, op.pre1, op.pre2,
+                         op.post2);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_first_point_coop<T>(n, out, op, ident, plan.coop_cols, plan.coop_lookahead, counters, st);
+  }
+  const DiagInput<T> diag{g, op.pre1, op.pre2, op.post2, op.sign2};
+  const bool nt = sizeof(T) == 16;
   const long long m = plan.col_chunk > 0 ? plan.col_chunk : NN;
   Chirp post_last = op.post1;
   post_last.scale = op.scale;
@@ -1017,9 +1144,9 @@ hipError_t launch_operator_diag(int n, const typename real_of<T>::type* g, T* ou
     const AxisRange aj{N, NNN, NN, cj, has_j ? ((cj + m <= NN) ? m : NN - cj) : 0};
     const AxisRange ai{N, NN, NNN, ci, has_i ? ((ci + m <= NN) ? m : NN - ci) : 0};
     if (has_j && has_i)
-      e = launch_axis_range<T>(n, out, out, op.sign1, aj, ident, op.post1, &ai, ident, post_last, st);
+      e = launch_axis_range<T>(n, out, out, op.sign1, aj, ident, op.post1, &ai, ident, post_last, st, nt, &diag);
     else if (has_j)
-      e = launch_axis_range<T>(n, out, out, op.sign1, aj, ident, op.post1, nullptr, ident, ident, st);
+      e = launch_axis_range<T>(n, out, out, op.sign1, aj, ident, op.post1, nullptr, ident, ident, st, nt, &diag);
     else
       e = launch_axis_range<T>(n, out, out, op.sign1, ai, ident, post_last, nullptr, ident, ident, st);
     if (e != hipSuccess) return e;
