@@ -1279,37 +1279,73 @@ __global__ __launch_bounds__(kOneThreads) void k_one_poly_sums(const T* __restri
 }
 
 // One axis of a chirp-z transform of every pair's array, stored transposed:
-// out[k][m][i] = sum_{p < len} e^{SIGN 2 pi i beta_k (m - c)(p - off)} in[k][i][p], m < N, i < rows. The
-// factors come from an FP64 recurrence along p (one FP64 product per term); sums in FP64.
+// out[k][m][i] = sum_{p < 2 off} e^{SIGN 2 pi i beta_k (m - c)(p - off)} in[k][i][p], m < N = 2 c, i < rows, in FP64.
+// Both indices are centred, so outputs c +- t share their sums and mirrored inputs meet first, with real factors:
+//   E(t) = sum_q cos(2 pi beta t q) (x[q] + x[-q]),  O(t) = sum_q sin(2 pi beta t q) (x[q] - x[-q]),  out(+-t) = E +- SIGN i O,
+// q = 1 .. off - 1 beside x[0] and x[-off], which have no mirror. The factors come from an FP64 recurrence in q: four
+// multiply-adds for them and four for the sums, for two inputs and two outputs (32 without the mirror). A row takes
+// min(c, 64) threads of one wavefront, a thread the outputs +-t; t = 0 is a sum of the row's entries, by butterfly.
+// Bound: FP64 FMA and the LDS reads of the two combinations. N = 128, 16 pairs: 2 x 57.6 + 2 x 21.2 us -> 2 x 17.0 + 2 x 9.3 (the 16-wavelength sum 1061 -> 968 us).
 template <class T, int SIGN>
-__global__ __launch_bounds__(256) void k_poly_czt(const T* __restrict__ in, int n, int rows, int len, int off,
+__global__ __launch_bounds__(256) void k_poly_czt(const T* __restrict__ in, int n, int rows, int off, int total,
                                                   PolyGroup g, T* __restrict__ out) {
   using R = typename real_of<T>::type;
-  __shared__ T row[512];
-  const int k = blockIdx.x / rows, i = blockIdx.x % rows, c = n / 2;
-  const long long inb = ((long long)k * rows + i) * len;
-  for (int p = threadIdx.x; p < len; p += blockDim.x) row[p] = in[inb + p];
-  __syncthreads();
-  const double beta = k < g.count ? g.beta[k] : 0.0;
-  for (int m = threadIdx.x; m < n; m += blockDim.x) {
-    double f0 = (double)SIGN * beta * (double)(m - c) * (double)(0 - off);
-    double fs = (double)SIGN * beta * (double)(m - c);
-    f0 -= rint(f0);
-    fs -= rint(fs);
-    double s0, c0, s1, c1;
-    sincospi(2.0 * f0, &s0, &c0);
-    sincospi(2.0 * fs, &s1, &c1);
-    double2 wv{c0, s0};
-    const double2 rot{c1, s1};
-    double2 acc{0.0, 0.0};
-    for (int p = 0; p < len; ++p) {
-      const T v = row[p];
-      acc.x += wv.x * (double)v.x - wv.y * (double)v.y;
-      acc.y += wv.x * (double)v.y + wv.y * (double)v.x;
-      wv = cmul(wv, rot);
+  __shared__ double2 se[1024], so[1024];  // rows of a workgroup x off: 512 up to N = 128, 4 x 256 at N = 256
+  const int c = n / 2, per = c < 64 ? c : 64;
+  const int r = threadIdx.x / per, lane = threadIdx.x % per;
+  const int gi = blockIdx.x * (256 / per) + r;
+  const bool ok = gi < total;
+  const T* x = in + (ok ? (long long)gi * 2 * off : 0);
+  double2* e = se + r * off;  // e[0] = x[0], o[0] = x[-off]
+  double2* o = so + r * off;
+  if (ok) {
+    for (int q = lane; q < off; q += per) {
+      const T a = x[off + q], b = x[q == 0 ? 0 : off - q];
+      const double2 ad{(double)a.x, (double)a.y}, bd{(double)b.x, (double)b.y};
+      e[q] = q == 0 ? ad : cadd(ad, bd);
+      o[q] = q == 0 ? bd : csub(ad, bd);
     }
-    out[((long long)k * n + m) * rows + i] = T{(R)acc.x, (R)acc.y};
   }
+  __syncthreads();
+  if (!ok) return;
+  const int k = gi / rows, i = gi % rows;
+  T* col = out + (long long)k * n * rows + i;
+  double2 z = lane == 0 ? o[0] : double2{0.0, 0.0};
+  for (int q = lane; q < off; q += per) z = cadd(z, e[q]);
+  for (int h = per / 2; h > 0; h >>= 1) z = cadd(z, double2{__shfl_xor(z.x, h), __shfl_xor(z.y, h)});
+  if (lane == 0) col[(long long)c * rows] = T{(R)z.x, (R)z.y};
+  const double beta = g.beta[k];
+  for (int t = lane + 1; t <= c; t += per) {
+    double fs = beta * (double)t;
+    fs -= rint(fs);
+    double2 rot;
+    sincospi(2.0 * fs, &rot.y, &rot.x);
+    double2 w = rot, ev = e[0], od{0.0, 0.0};
+#pragma unroll 4
+    for (int q = 1; q < off; ++q) {
+      const double2 a = e[q], b = o[q];
+      ev.x += w.x * a.x;
+      ev.y += w.x * a.y;
+      od.x += w.y * b.x;
+      od.y += w.y * b.y;
+      w = cmul(w, rot);
+    }
+    const double2 l = o[0];  // x[-off]: cos and -sin of q = off
+    ev.x += w.x * l.x;
+    ev.y += w.x * l.y;
+    od.x -= w.y * l.x;
+    od.y -= w.y * l.y;
+    const double sg = (double)SIGN;
+    col[(long long)(c - t) * rows] = T{(R)(ev.x + sg * od.y), (R)(ev.y - sg * od.x)};
+    if (t < c) col[(long long)(c + t) * rows] = T{(R)(ev.x - sg * od.y), (R)(ev.y + sg * od.x)};
+  }
+}
+
+template <class T, int SIGN>
+static void launch_poly_czt(const T* in, int n, int rows, int off, const PolyGroup& g, T* out, hipStream_t st) {
+  const int per = n / 2 < 64 ? n / 2 : 64, rb = 256 / per, total = g.count * rows;
+  hipLaunchKernelGGL((k_poly_czt<T, SIGN>), dim3((unsigned)((total + rb - 1) / rb)), dim3(256), 0, st, in, n, rows, off,
+                     total, g, out);
 }
 
 // S(m) (+)= sum_k c_k Re zd_k[m]; W(m) (+)= sum_k c_k conj(tau_k(P)) tau_k(m) zr_k[m], in FP64, pairs in order.
@@ -1768,14 +1804,10 @@ hipError_t launch_poly(int n, const T* w, int n_pairs, const double* alpha, cons
     }
     // S: the + transform of D over [-N, N)^2 (offset N); the row: the - transform of T R (offset N/2). Only
     // the group's pairs are transformed.
-    hipLaunchKernelGGL((k_poly_czt<T, +1>), dim3((unsigned)(pg.count * 2 * n)), dim3(256), 0, st, (const T*)dfull, n,
-                       2 * n, 2 * n, n, pg, tmp);
-    hipLaunchKernelGGL((k_poly_czt<T, +1>), dim3((unsigned)(pg.count * n)), dim3(256), 0, st, (const T*)tmp, n, n,
-                       2 * n, n, pg, zd);
-    hipLaunchKernelGGL((k_poly_czt<T, -1>), dim3((unsigned)(pg.count * n)), dim3(256), 0, st, (const T*)rr, n, n, n,
-                       n / 2, pg, tmp);
-    hipLaunchKernelGGL((k_poly_czt<T, -1>), dim3((unsigned)(pg.count * n)), dim3(256), 0, st, (const T*)tmp, n, n, n,
-                       n / 2, pg, zr);
+    launch_poly_czt<T, +1>((const T*)dfull, n, 2 * n, n, pg, tmp, st);
+    launch_poly_czt<T, +1>((const T*)tmp, n, n, n, pg, zd, st);
+    launch_poly_czt<T, -1>((const T*)rr, n, n, n / 2, pg, tmp, st);
+    launch_poly_czt<T, -1>((const T*)tmp, n, n, n / 2, pg, zr, st);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(k_poly_combine<T>, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, st, (const T*)zd,
                        (const T*)zr, n, pi, pj, pg, k0 == 0 ? 1 : 0, s_acc, w_acc);
