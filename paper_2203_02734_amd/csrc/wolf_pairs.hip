@@ -1285,7 +1285,8 @@ __global__ __launch_bounds__(kOneThreads) void k_one_poly_sums(const T* __restri
 // q = 1 .. off - 1 beside x[0] and x[-off], which have no mirror. The factors come from an FP64 recurrence in q: four
 // multiply-adds for them and four for the sums, for two inputs and two outputs (32 without the mirror). A row takes
 // min(c, 64) threads of one wavefront, a thread the outputs +-t; t = 0 is a sum of the row's entries, by butterfly.
-// Bound: FP64 FMA and the LDS reads of the two combinations. N = 128, 16 pairs: 2 x 57.6 + 2 x 21.2 us -> 2 x 17.0 + 2 x 9.3 (the 16-wavelength sum 1061 -> 968 us).
+// Bound: FP64 FMA and the LDS reads of the two combinations. N = 128, 16 pairs: 2 x 57.6 + 2 x 21.2 us -> 2 x 17.0 +
+// 2 x 9.3 (the 16-wavelength sum 1061 -> 968 us).
 template <class T, int SIGN>
 __global__ __launch_bounds__(256) void k_poly_czt(const T* __restrict__ in, int n, int rows, int off, int total,
                                                   PolyGroup g, T* __restrict__ out) {
