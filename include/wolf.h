@@ -238,6 +238,16 @@ WOLF_API wolf_status wolf_propagate_adjoint_diag(const void* g_diag, void* g_in,
                                                  int32_t dtype, void* stream);
 
 /*
+ * wolf_propagate_density -- S of the propagated CSD, as wolf_propagate_fresnel (or _farfield) in place and
+ * wolf_spectral_density give it, bit for bit, without the rest of the propagated array: after the second-point passes
+ * only the entries that S needs are kept.
+ *   w        device, N^4 complex, the source; its contents are undefined after the call.
+ *   s_out    device, N*N real, must not overlap w.   farfield: 0 Fresnel, 1 far field.
+ */
+WOLF_API wolf_status wolf_propagate_density(void* w, int32_t n, double pitch_m, double wavelength_m, double z_m,
+                                            int32_t farfield, int32_t kind, int32_t dtype, void* s_out, void* stream);
+
+/*
  * wolf_spectral_density -- S[i][j] = Re W[i][j; i][j] (Sec. 3.5, Algorithm 4, eq. defS).
  *   s_out   device, N*N real (float32 for WOLF_C64, float64 for WOLF_C128).
  */

@@ -34,7 +34,7 @@ EXPORTED = ["wolf_build_source", "wolf_propagate_fresnel", "wolf_propagate_farfi
             "wolf_propagate_lens", "wolf_propagate_direct", "wolf_direct_work_bytes",
             "wolf_propagate_padded", "wolf_propagate_polychromatic", "wolf_polychromatic_work_bytes",
             "wolf_propagate_source", "wolf_memory_ceiling", "wolf_degree_of_coherence_noalloc",
-            "wolf_fit_forward", "wolf_fit_backward", "wolf_fit_sums_work_bytes"]
+            "wolf_fit_forward", "wolf_fit_backward", "wolf_fit_sums_work_bytes", "wolf_propagate_density"]
 
 
 class WolfError(RuntimeError):
@@ -74,6 +74,7 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
         "wolf_propagate_adjoint": [vp, vp, i32, f64, f64, f64, i32, i32, i32, vp],
         "wolf_propagate_adjoint_diag": [vp, vp, i32, f64, f64, f64, i32, i32, i32, vp],
         "wolf_spectral_density": [vp, i32, i32, vp, vp],
+        "wolf_propagate_density": [vp, i32, f64, f64, f64, i32, i32, i32, vp, vp],
         "wolf_degree_of_coherence": [vp, i32, i32, i32, i32, f64, vp, vp],
         "wolf_degree_of_coherence_noalloc": [vp, i32, i32, i32, i32, f64, vp, vp],
         "wolf_propagate_batch": [vp, i32, f64, i32, pd, pd, pd, i32, i32, i32, i32, i32, f64, vp, vp, vp, vp],
@@ -390,6 +391,16 @@ def spectral_density(w: torch.Tensor, out: Optional[torch.Tensor] = None) -> tor
         _out(out, (n, n), _real(w.dtype), w.device)
     _check(lib.wolf_spectral_density(_ptr(w), n, _code(w.dtype), _ptr(out), _stream()), "wolf_spectral_density")
     return out
+
+
+def propagate_density(w: torch.Tensor, pitch: float, wavelength: float, z: float, farfield: bool = False,
+                      kind: int = SECONDARY) -> torch.Tensor:
+    """S of the propagated w, as propagate(w, ..., out=w) and spectral_density(w) give it; w is overwritten (scratch)."""
+    n = _csd(w)
+    s = torch.empty((n, n), dtype=_real(w.dtype), device=w.device)
+    _check(load().wolf_propagate_density(_ptr(w), n, pitch, wavelength, z, int(bool(farfield)), kind, _code(w.dtype),
+                                         _ptr(s), _stream()), "wolf_propagate_density")
+    return s
 
 
 def degree_of_coherence(w: torch.Tensor, ip: int = -1, jp: int = -1, floor_rel: float = 1e-12,

@@ -15,8 +15,8 @@ from types import SimpleNamespace
 
 import torch
 
-from . import (GEO_NONE, MODEL_MAP, build_source, fit_backward, fit_forward, fit_gradient, propagate,
-               propagate_adjoint_diag, spectral_density)
+from . import (GEO_NONE, MODEL_MAP, build_source, fit_backward, fit_forward, fit_gradient, propagate_adjoint_diag,
+               propagate_density)
 
 
 def _map_source(imap: torch.Tensor, sigma_g: float):
@@ -42,8 +42,7 @@ class PropagatedSpectralDensity(torch.autograd.Function):
             ctx.save_for_backward(imap_c, corr)
         else:
             w = build_source(_map_source(imap_c, sg), n, pitch, dtype, device=imap.device)
-            propagate(w, pitch, wavelength, z, farfield, out=w)
-            s = spectral_density(w)
+            s = propagate_density(w, pitch, wavelength, z, farfield)
             ctx.save_for_backward(imap_c)
         ctx.cfg = (pitch, wavelength, z, farfield, dtype, sg, sigma_g.device, sigma_g.dtype)
         return s

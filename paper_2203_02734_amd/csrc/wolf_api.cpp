@@ -322,14 +322,15 @@ wolf::Plan plan_for(int32_t n, int32_t dtype) {
 
 template <class T>
 wolf_status run_operator(const T* in, T* out, int32_t n, int32_t dtype, const wolf::OperatorTables& op,
-                         hipStream_t st) {
+                         hipStream_t st, typename wolf::real_of<T>::type* s_out = nullptr) {
   const wolf::Plan plan = plan_for(n, dtype);
   void* scratch = nullptr;
   if (plan.coop) {
     const wolf_status s = stream_scratch(st, &scratch);
     if (s != WOLF_OK) return s;
   }
-  const hipError_t e = wolf::launch_operator<T>(n, in, out, op, plan, scratch, st);
+  hipError_t e = wolf::launch_operator<T>(n, in, out, op, plan, scratch, st, nullptr, plan.coop ? nullptr : s_out);
+  if (e == hipSuccess && s_out && plan.coop) e = wolf::launch_spectral_density<T>(n, out, s_out, st);
   if (e != hipSuccess) return fail(WOLF_EDEVICE, "propagation launch: %s", hipGetErrorString(e));
   g_last_error.clear();
   return WOLF_OK;
@@ -337,7 +338,7 @@ wolf_status run_operator(const T* in, T* out, int32_t n, int32_t dtype, const wo
 
 wolf_status propagate_common(const void* w_in, void* w_out, int32_t n, double pitch, double lam, double z,
                              bool farfield, int32_t kind, int32_t dtype, bool adjoint, double* out_pitch,
-                             void* stream, const char* who, const LensSpec* lens = nullptr) {
+                             void* stream, const char* who, const LensSpec* lens = nullptr, void* s_out = nullptr) {
   if (!supported_n(n)) return fail(WOLF_EUNSUPPORTED, "%s: N=%d is not a power of two in [2, 256]", who, n);
   if (dtype != WOLF_C64 && dtype != WOLF_C128) return fail(WOLF_EINVAL, "%s: bad dtype %d", who, dtype);
   if (!pos_finite(pitch) || !pos_finite(lam) || !pos_finite(z))
@@ -372,8 +373,10 @@ wolf_status propagate_common(const void* w_in, void* w_out, int32_t n, double pi
   if (out_pitch) *out_pitch = lam * z / ((double)n * pitch);
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (dtype == WOLF_C64)
-    return run_operator<float2>(static_cast<const float2*>(w_in), static_cast<float2*>(w_out), n, dtype, op, st);
-  return run_operator<double2>(static_cast<const double2*>(w_in), static_cast<double2*>(w_out), n, dtype, op, st);
+    return run_operator<float2>(static_cast<const float2*>(w_in), static_cast<float2*>(w_out), n, dtype, op, st,
+                                static_cast<float*>(s_out));
+  return run_operator<double2>(static_cast<const double2*>(w_in), static_cast<double2*>(w_out), n, dtype, op, st,
+                               static_cast<double*>(s_out));
 }
 
 // Validates a source description and converts it to pixel units (shared by the builder and the
@@ -493,6 +496,20 @@ WOLF_API wolf_status wolf_propagate_farfield(const void* w_in, void* w_out, int3
                                              double* out_pitch_m, void* stream) {
   return propagate_common(w_in, w_out, n, pitch_m, wavelength_m, z_m, true, kind, dtype, false, out_pitch_m,
                           stream, "wolf_propagate_farfield");
+}
+
+WOLF_API wolf_status wolf_propagate_density(void* w, int32_t n, double pitch_m, double wavelength_m, double z_m,
+                                            int32_t farfield, int32_t kind, int32_t dtype, void* s_out, void* stream) {
+  const char* who = "wolf_propagate_density";
+  if (farfield != 0 && farfield != 1) return fail(WOLF_EINVAL, "%s: farfield must be 0 or 1", who);
+  if (!supported_n(n)) return fail(WOLF_EUNSUPPORTED, "%s: N=%d is not a power of two in [2, 256]", who, n);
+  if (dtype != WOLF_C64 && dtype != WOLF_C128) return fail(WOLF_EINVAL, "%s: bad dtype %d", who, dtype);
+  wolf_status s;
+  if ((s = check_buf(s_out, (size_t)n * n * real_bytes(dtype), "s_out")) != WOLF_OK) return s;
+  if (intervals_overlap(s_out, (size_t)n * n * real_bytes(dtype), w, n4(n) * elem_bytes(dtype)))
+    return fail(WOLF_EINVAL, "%s: s_out overlaps w", who);
+  return propagate_common(w, w, n, pitch_m, wavelength_m, z_m, farfield == 1, kind, dtype, false, nullptr, stream, who,
+                          nullptr, s_out);
 }
 
 WOLF_API wolf_status wolf_propagate_lens(const void* w_in, void* w_out, int32_t n, double pitch_m,

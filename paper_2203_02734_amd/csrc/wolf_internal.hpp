@@ -64,9 +64,11 @@ struct SourceParams;
 // `counters`: per-stream device scratch of at least coop_counter_bytes(n) (used when plan.coop).
 // `gen` (plan.fused_slab == 3, or 0 at N >= 64 with no input pupil): the input is the source
 // described by *gen, formed inside the first pass; `in` is not read.
+// `s_out` (no plan.coop): only S = Re diag of the result is wanted, N^2; `out` is then scratch.
 template <class T>
 hipError_t launch_operator(int n, const T* in, T* out, const OperatorTables& op, const Plan& plan, void* counters,
-                           hipStream_t st, const SourceParams* gen = nullptr);
+                           hipStream_t st, const SourceParams* gen = nullptr,
+                           typename real_of<T>::type* s_out = nullptr);
 // The operator applied to diag(g), g an N*N real array (no N^4 input is read).
 template <class T>
 hipError_t launch_operator_diag(int n, const typename real_of<T>::type* g, T* out, const OperatorTables& op,
