@@ -304,7 +304,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
 }
 
-// Wavefronts of a workgroup of the two streaming contractions below (one workgroup per CU) and blocks of 16 columns per
+// Wavefronts of a workgroup of the mirrored row sums below (one workgroup per CU) and blocks of 16 columns per
 // wavefront, for R tiles of 16 pairs. With four tiles complex64 takes two wavefronts per SIMD over one block each, so that
 // one's vector work runs beside the other's products; with fewer the read of W bounds the pass, and one wavefront over two
 // blocks has the longer runs. N = 128 complex64, row and difference sums: 64 pairs 450 and 980 us with one wavefront, 410 and
@@ -630,50 +630,385 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
       }
 }
 
-// Difference sums by the mirror symmetry of their weights. For an unfolded offset delta (d_i for a >= d_i, d_i - N for
-// a < d_i) the weight u1[a] u2[a - delta] is a linear phase in a: with s = a - a_mid over the range of a (its middle),
+// Difference sums of a complex64 group at N = 128, with the W stream kept deep
+// in flight (the ring of k_pair_rows_ring): part[z][k][di N + dj] = sum_{b in chunk z} B_k^{dj}[b] G_b[k][dj],
+// G_b[k][dj] = sum_a A^{di}[a][k] W[a, b; a - di, b - dj], A^{di}[a][k] = u1[k][a] u2[k][a - di],
+// B_k^{dj}[b] = u1[k][b] u2[k][b - dj] (indices mod N). A workgroup owns one di and 256 / N chunks of b
+// (z = blockIdx.x % (256 / N)), the first 16 R pairs (R = 4, 2, 1 for groups of more than 32, 17-32 and
+// up to 16 pairs; the other pairs' sums are not written) and all N values of dj (a wavefront: 32 of them). A^{di}
+// (formed once) and u2 sit in LDS; u1[k][b] is loaded at the start of each b. Each step is 16 values of a
+// (24 R MFMAs into G); after the N / 16 steps of one b, G is folded into the sums. Only N = 128 fills the
+// four wavefronts' 128 columns; at N = 64 wavefronts 2 and 3 hold no columns and stay idle.
+template <int N, int R>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_pair_diffs_ring(
+    const float2* __restrict__ w, const float2* __restrict__ u1t, const float2* __restrict__ u2t,
+    float2* __restrict__ part) {
+  constexpr long long NN = (long long)N * N;
+  constexpr int SPB = N / 16;  // steps per b
+  constexpr int RING = 8, BSPLIT = 256 / N, BCH = N / BSPLIT;
+  constexpr int NM = N - 1;
+  static_assert(SPB <= RING && RING % SPB == 0, "ring of whole b");
+  static_assert(R >= 1 && 16 * R <= kPairTile, "tiles of 16 pairs");
+  __shared__ float2 as_[N * kPairTile], u2s[N * kPairTile];
+  const int tid = threadIdx.x, lane = tid % 64, l16 = lane % 16, kq = lane / 16;
+  const int wv = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int di = (int)blockIdx.x / BSPLIT, z = (int)blockIdx.x % BSPLIT;
+  const int b_lo = z * BCH;
+  // A^{di}[a][k] at a 64 + (k ^ 16 (a & 1)); u2[m][k] at m 64 + (k ^ 2 (m & 15)) (the fold's 16 lanes of one
+  // k read 16 consecutive m).
+  for (int e = tid; e < N * kPairTile; e += 256) {
+    const int m = e / kPairTile, k = e % kPairTile;
+    as_[m * kPairTile + (k ^ ((m & 1) << 4))] = cmul(u1t[e], u2t[((m - di) & NM) * kPairTile + k]);
+    u2s[m * kPairTile + (k ^ ((m & 15) << 1))] = u2t[e];
+  }
+  __syncthreads();
+  if (wv * 32 >= N) return;  // no columns for this wavefront (N = 64); no barrier follows
+  const int dj0 = 32 * wv;
+  constexpr int total = BCH * SPB;
+  auto load = [&](RingStep& r, int t) {
+    const int tc = t < total ? t : total - 1;
+    const int b = b_lo + tc / SPB, a0 = (tc % SPB) * 16;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const int a = a0 + 4 * ks + kq;
+      const float2* row = w + ((long long)a * N + b) * NN + (long long)((a - di) & NM) * N;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) r.v[ks][q] = row[(b - dj0 - 16 * q - l16) & NM];
+    }
+  };
+  v4f t1[R][2], t2[R][2], t3[R][2];
+  float2 f[R][2][4], u1v[R][4];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      t1[r][q] = t2[r][q] = t3[r][q] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) f[r][q][i] = float2{0.f, 0.f};
+    }
+  auto read_a = [&](float2 (&av)[4][R], int a0) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const int a = a0 + 4 * ks + kq;
+#pragma unroll
+      for (int r = 0; r < R; ++r) av[ks][r] = as_[a * kPairTile + ((16 * r + l16) ^ ((a & 1) << 4))];
+    }
+  };
+  auto step_mfma = [&](const float2 (&av)[4][R], const RingStep& bw) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      float xs[R], ys[2];
+#pragma unroll
+      for (int r = 0; r < R; ++r) xs[r] = av[ks][r].x + av[ks][r].y;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) ys[q] = bw.v[ks][q].x + bw.v[ks][q].y;
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          t1[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks][r].x, bw.v[ks][q].x, t1[r][q], 0, 0, 0);
+          t2[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks][r].y, bw.v[ks][q].y, t2[r][q], 0, 0, 0);
+          t3[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[r], ys[q], t3[r][q], 0, 0, 0);
+        }
+    }
+  };
+  RingStep ring[RING];
+#pragma unroll
+  for (int u = 0; u < RING - 1; ++u) {
+    load(ring[u], u);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  float2 avs[2][4][R];
+  read_a(avs[0], 0);
+  for (int t0 = 0; t0 < total; t0 += RING) {  // t0 is a multiple of SPB
+#pragma unroll
+    for (int u = 0; u < RING; ++u) {
+      const int b = b_lo + (t0 + u) / SPB;
+      load(ring[(u + RING - 1) % RING], t0 + u + RING - 1);
+      if (u % SPB == 0) {  // u1[k][b] of this b, behind the ring's load (it is needed at the fold)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) u1v[r][i] = u1t[b * kPairTile + 16 * r + Mfma<float2>::row(lane, i)];
+      }
+      read_a(avs[(u + 1) % 2], ((u + 1) % SPB) * 16);  // the next step's operand
+      __builtin_amdgcn_sched_barrier(0);
+      step_mfma(avs[u % 2], ring[u]);
+      if ((u + 1) % SPB == 0) {  // the last step of b: D += u1[k][b] u2[k][b - dj] G
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int k = 16 * r + Mfma<float2>::row(lane, i);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+              const int m = (b - dj0 - 16 * q - l16) & NM;
+              const float2 c = cmul(u1v[r][i], u2s[m * kPairTile + (k ^ ((m & 15) << 1))]);
+              const float gr = t1[r][q][i] - t2[r][q][i], gi = t3[r][q][i] - t1[r][q][i] - t2[r][q][i];
+              f[r][q][i].x += c.x * gr - c.y * gi;
+              f[r][q][i].y += c.x * gi + c.y * gr;
+            }
+          }
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) t1[r][q] = t2[r][q] = t3[r][q] = v4f{0.f, 0.f, 0.f, 0.f};
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  float2* out = part + (long long)z * kPairTile * NN;
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        out[(16 * r + Mfma<float2>::row(lane, i)) * NN + (long long)di * N + dj0 + 16 * q + l16] = f[r][q][i];
+}
+
+// The polychromatic difference sums without wrap (the bins of k_poly_diffs_mfma) on the register ring of
+// k_pair_diffs_ring, for the pairs k0 .. k0 + 16 R - 1 of a complex64 group at N = 128: one tile of 16 pairs
+// with eight steps of the source in flight (R = 1, RING = 8), or two tiles with four steps (R = 2, RING = 4:
+// with eight, the two bins' sums of two tiles exceed the registers of one wavefront per SIMD and spill). A
+// workgroup owns one folded d_i, 256 / N chunks of b (z = blockIdx.x % (256 / N)) and every a: a step of 16
+// values of a adds into the G of bin d_i (a >= d_i) or of bin d_i - N (a < d_i); the one step that holds d_i
+// runs twice, with the A rows of the other bin zeroed. After the N / 16 steps of one b both G are folded into
+// their sums. On the second point a lane's column d_j switches bin once as b rises, so the lane stores its
+// lower bin's sums when b passes d_j - 1 and writes each of its four bins (two of d_i, two of d_j) exactly once
+// per chunk of b, zeros where the chunk holds no term.
+template <int N, int R, int RING>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_poly_diffs_ring(
+    const float2* __restrict__ w, const float2* __restrict__ u1t, const float2* __restrict__ u2t, int k0,
+    float2* __restrict__ part) {
+  constexpr long long NN = (long long)N * N, BINS = 4 * NN;
+  constexpr int SPB = N / 16;  // steps per b
+  constexpr int BSPLIT = 256 / N, BCH = N / BSPLIT;
+  constexpr int NM = N - 1;
+  static_assert((SPB <= RING && RING % SPB == 0) || (RING < SPB && SPB % RING == 0), "ring and steps per b nest");
+  static_assert((R == 1 && RING == 8) || (R == 2 && RING == 4), "the register budgets measured");
+  __shared__ float2 as_[N * kPairTile], u2s[N * kPairTile];
+  const int tid = threadIdx.x, lane = tid % 64, l16 = lane % 16, kq = lane / 16;
+  const int wv = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int di = (int)blockIdx.x / BSPLIT, z = (int)blockIdx.x % BSPLIT;
+  const int b_lo = z * BCH, b_hi = b_lo + BCH;
+  // A^{di}[a][k] at a 64 + (k ^ 16 (a & 1)); u2[m][k] at m 64 + (k ^ 2 (m & 15)), as in k_pair_diffs_ring.
+  for (int e = tid; e < N * kPairTile; e += 256) {
+    const int m = e / kPairTile, k = e % kPairTile;
+    as_[m * kPairTile + (k ^ ((m & 1) << 4))] = cmul(u1t[e], u2t[((m - di) & NM) * kPairTile + k]);
+    u2s[m * kPairTile + (k ^ ((m & 15) << 1))] = u2t[e];
+  }
+  __syncthreads();
+  if (wv * 32 >= N) return;  // no columns for this wavefront; no barrier follows
+  const int dj0 = 32 * wv;
+  constexpr int total = BCH * SPB;
+  auto load = [&](RingStep& r, int t) {
+    const int tc = t < total ? t : total - 1;
+    const int b = b_lo + tc / SPB, a0 = (tc % SPB) * 16;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const int a = a0 + 4 * ks + kq;
+      const float2* row = w + ((long long)a * N + b) * NN + (long long)((a - di) & NM) * N;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) r.v[ks][q] = row[(b - dj0 - 16 * q - l16) & NM];
+    }
+  };
+  // [h]: h = 0 the bin d_i (a >= d_i), h = 1 the bin d_i - N (a < d_i).
+  v4f t1[2][R][2], t2[2][R][2], t3[2][R][2];
+  float2 f[2][R][2][4], u1v[R][4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        t1[h][r][q] = t2[h][r][q] = t3[h][r][q] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f[h][r][q][i] = float2{0.f, 0.f};
+      }
+  auto read_a = [&](float2 (&av)[4][R], int a0) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const int a = a0 + 4 * ks + kq;
+#pragma unroll
+      for (int r = 0; r < R; ++r) av[ks][r] = as_[a * kPairTile + ((k0 + 16 * r + l16) ^ ((a & 1) << 4))];
+    }
+  };
+  auto step_mfma = [&](const float2 (&av)[4][R], const RingStep& bw, v4f (&s1)[R][2], v4f (&s2)[R][2],
+                       v4f (&s3)[R][2]) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      float xs[R], ys[2];
+#pragma unroll
+      for (int r = 0; r < R; ++r) xs[r] = av[ks][r].x + av[ks][r].y;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) ys[q] = bw.v[ks][q].x + bw.v[ks][q].y;
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          s1[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks][r].x, bw.v[ks][q].x, s1[r][q], 0, 0, 0);
+          s2[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks][r].y, bw.v[ks][q].y, s2[r][q], 0, 0, 0);
+          s3[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[r], ys[q], s3[r][q], 0, 0, 0);
+        }
+    }
+  };
+  // The lane's four bins of pair k: d_i bin h (row di + N, or di), d_j bin dj (upper) or dj - N (lower).
+  float2* const out = part + (long long)z * kPairTile * BINS;
+  auto bin_at = [&](int k, int h, int dj_bin) {
+    return (long long)(k0 + k) * BINS + (long long)(h == 0 ? di + N : di) * (2 * N) + dj_bin + N;
+  };
+  RingStep ring[RING];
+#pragma unroll
+  for (int u = 0; u < RING - 1; ++u) {
+    load(ring[u], u);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  float2 avs[2][4][R];
+  read_a(avs[0], 0);
+  for (int t0 = 0; t0 < total; t0 += RING) {
+#pragma unroll
+    for (int u = 0; u < RING; ++u) {
+      // Step of this b: known at compile time when the ring holds whole b (t0 a multiple of SPB), else
+      // wavefront-uniform.
+      const int sb = RING % SPB == 0 ? u % SPB : (t0 + u) % SPB;
+      const int b = b_lo + (t0 + u) / SPB, a0 = sb * 16;
+      load(ring[(u + RING - 1) % RING], t0 + u + RING - 1);
+      if (sb == 0) {  // u1[k][b] of this b, behind the ring's load (it is needed at the fold)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) u1v[r][i] = u1t[b * kPairTile + k0 + 16 * r + Mfma<float2>::row(lane, i)];
+      }
+      read_a(avs[(u + 1) % 2], ((sb + 1) % SPB) * 16);  // the next step's operand
+      __builtin_amdgcn_sched_barrier(0);
+      if (a0 >= di) {  // workgroup-uniform: every a of the step is in the bin d_i
+        step_mfma(avs[u % 2], ring[u], t1[0], t2[0], t3[0]);
+      } else if (a0 + 16 <= di) {  // every a is in the bin d_i - N
+        step_mfma(avs[u % 2], ring[u], t1[1], t2[1], t3[1]);
+      } else {  // the step holds d_i: each bin with the other bin's rows of A zeroed
+        float2 am[4][R];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          const bool upper = a0 + 4 * ks + kq >= di;
+#pragma unroll
+          for (int r = 0; r < R; ++r) am[ks][r] = upper ? avs[u % 2][ks][r] : float2{0.f, 0.f};
+        }
+        step_mfma(am, ring[u], t1[0], t2[0], t3[0]);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          const bool upper = a0 + 4 * ks + kq >= di;
+#pragma unroll
+          for (int r = 0; r < R; ++r) am[ks][r] = upper ? float2{0.f, 0.f} : avs[u % 2][ks][r];
+        }
+        step_mfma(am, ring[u], t1[1], t2[1], t3[1]);
+      }
+      if (sb == SPB - 1) {  // the last step of b: D_h += u1[k][b] u2[k][b - dj] G_h, then the d_j switch
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int k = 16 * r + Mfma<float2>::row(lane, i);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+              const int dj = dj0 + 16 * q + l16;
+              const int m = (b - dj) & NM;
+              const float2 c = cmul(u1v[r][i], u2s[m * kPairTile + ((k0 + k) ^ ((m & 15) << 1))]);
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                const float gr = t1[h][r][q][i] - t2[h][r][q][i];
+                const float gi = t3[h][r][q][i] - t1[h][r][q][i] - t2[h][r][q][i];
+                f[h][r][q][i].x += c.x * gr - c.y * gi;
+                f[h][r][q][i].y += c.x * gi + c.y * gr;
+              }
+              if (b == dj - 1 && dj < b_hi) {  // every b below d_j is summed: the lower d_j bin is complete
+                // (at dj = b_hi the sums stay held: the chunk ends there and stores them in the lower bin)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                  out[bin_at(k, h, dj - N)] = f[h][r][q][i];
+                  f[h][r][q][i] = float2{0.f, 0.f};
+                }
+              }
+            }
+          }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) t1[h][r][q] = t2[h][r][q] = t3[h][r][q] = v4f{0.f, 0.f, 0.f, 0.f};
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  // The sums still held belong to the d_j bin of the chunk's last b; the other d_j bin was stored at the
+  // switch, or has no term in this chunk (zero).
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int k = 16 * r + Mfma<float2>::row(lane, i);
+        const int dj = dj0 + 16 * q + l16;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if (dj >= b_hi) {  // every b of the chunk is below d_j
+            out[bin_at(k, h, dj - N)] = f[h][r][q][i];
+            out[bin_at(k, h, dj)] = float2{0.f, 0.f};
+          } else {
+            out[bin_at(k, h, dj)] = f[h][r][q][i];
+            if (dj <= b_lo) out[bin_at(k, h, dj - N)] = float2{0.f, 0.f};  // no b of the chunk is below d_j
+          }
+        }
+      }
+}
+
+// Difference sums of a complex128 group at N = 64 and 128 by the mirror symmetry of their weights. For an unfolded offset
+// delta (d_i for a >= d_i, d_i - N for a < d_i) the weight u1[a] u2[a - delta] is a linear phase in a: with s = a - a_mid over
+// the range of a (its middle),
 //   u1[a] u2[a - delta] = kappa e^{-2 pi i alpha delta s},   kappa = +-e^{i pi alpha delta},
 // so mirrored rows W_hi (s) and W_lo (-s) give  kappa (cos(theta) (W_hi + W_lo) - i sin(theta) (W_hi - W_lo)): real weights
 // on complex data, four real products for two rows (the 3M form takes six), and no operand sums. For each range h
 // (delta = d_i, d_i - N) and b,
 //   G[k][dj] = sum over the pairs of rows of the range,   D_h[k][dj] = kappa sum_b u1[b] u2[b - dj] G.
-// A workgroup owns d_i, up to four blocks of 16 Q columns d_j (further waves take their own chunks of b) and a chunk of b; the
-// ranges run one after the other, b inside. A wavefront owns 16 R pairs x 16 Q columns; a step is eight pairs of rows of one
-// b, and RING steps sit in registers (one wavefront per SIMD). cos and sin stand in LDS (FP64-built, one row per pair of
-// rows; zero past a range's last pair, cos = 1/2 for a middle row that is its own mirror). Past the last b the loads re-read
-// it and the weights are zero.
+// A workgroup owns d_i, four blocks of 16 columns d_j (one per wavefront, one wavefront per SIMD) and a chunk of b; the
+// ranges run one after the other, b inside. A wavefront owns 16 R pairs x 16 columns; a step is eight pairs of rows of one
+// b, and RING steps sit in registers. cos and sin stand in LDS (FP64-built, one row per pair of rows; zero past a range's last
+// pair, cos = 1/2 for a middle row that is its own mirror). Past the last b the loads re-read it and the weights are zero.
 //   POLY 0 (Fresnel batch): part[2 z + h][k][d_i N + d_j] = D_h: the ranges are two of the parts that are summed.
 //   POLY 1 (unfolded bins): part[z][k][(delta + N) 2N + delta_j + N]: as b rises a lane's column switches from the bin
 //          d_j - N to d_j at b = d_j; each bin is written once per chunk of b.
-// Bound: the matrix cores and the folds at 64 pairs, the read of W at 16. Measured: see diffs_mirror_parts.
+// Bound: the matrix cores and the folds at 64 pairs, the read of W at 16. Measured: see diffs_mirror_parts. complex64 stays
+// with the rings and the LDS-staged kernels: mu is cut off where S <= floor_rel max S, so in FP32, where S is rounded at
+// 1e-7 of its maximum, every other order of these sums moves points across a floor of 1e-3 (one a call of 64 pairs at N = 128:
+// mu 1e-3 off in the 2-norm).
 struct DiffRates {
   double alpha[kPairTile];  // source chirp rate of each pair
   int count;
 };
 
-template <class T, int N, int R, int BCH, bool POLY>
-__global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_waves_per_eu((kStreamWaves<T, R> / 4), (kStreamWaves<T, R> / 4)))) void k_diffs_mirror(
-    const T* __restrict__ w, const T* __restrict__ u1, const T* __restrict__ u2, const T* __restrict__ u1t,
-    const T* __restrict__ u2t, DiffRates rates, T* __restrict__ part) {
+template <int N, int R, int BCH, bool POLY>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_diffs_mirror(
+    const double2* __restrict__ w, const double2* __restrict__ u1, const double2* __restrict__ u2,
+    const double2* __restrict__ u1t, const double2* __restrict__ u2t, DiffRates rates, double2* __restrict__ part) {
+  using T = double2;
   using V = typename Mfma<T>::V;
-  using Rt = typename real_of<T>::type;
   constexpr long long NN = (long long)N * N, NNN = NN * N;
-  constexpr int Q = kStreamBlocks<T, R>, W = kStreamWaves<T, R>, K = 16 * R, NM = N - 1;
-  constexpr int RING = sizeof(T) == 16 && R == 4 ? 4 : 8;  // eight would spill there
-  constexpr int CG = N / (16 * Q);                       // blocks of columns
-  constexpr int CT = CG > W ? CG / W : 1;                // workgroups over them
-  constexpr int CW = CG > W ? W : CG, SUBS = W / CW;     // blocks per workgroup, chunks of b per workgroup
-  constexpr int NB = N / (BCH * SUBS);                   // values of b per chunk
+  constexpr int K = 16 * R, NM = N - 1;
+  constexpr int RING = R == 4 ? 4 : 8;                   // eight would spill there
+  constexpr int CT = N / 64;                             // workgroups over the columns
+  constexpr int NB = N / BCH;                            // values of b per chunk
   constexpr int PS = N / 2 + 16;                         // pairs of rows of both ranges, whole steps, and a zero step
-  constexpr bool kLdsB = sizeof(T) == 8 || N == 64;      // the factors of b fit the LDS beside the weights
+  constexpr bool kLdsB = N == 64;                        // the factors of b fit the LDS beside the weights
   static_assert(NB >= 1, "chunks of b");
-  __shared__ T cs[(PS + 8) * K];                         // (cos, sin) of row j, pair k at j K + swz(j, k)
+  __shared__ T cs[(PS + 8) * K];                         // (cos, sin) of row j, pair k at j K + k
   __shared__ T kap[2][K];
-  __shared__ T us[kLdsB ? (NB * SUBS + N) * K : 1];      // u1[b][k], then u2[m][k] at m K + (k ^ 2 (m & 15) within K)
+  __shared__ T us[kLdsB ? (NB + N) * K : 1];             // u1[b][k], then u2[m][k] at m K + (k ^ 2 (m & 15) within K)
   const int tid = threadIdx.x, lane = tid % 64, l16 = lane % 16, kq = lane / 16;
   const int wv = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int bid = (int)blockIdx.x, di = bid / (CT * BCH), ct = bid % CT, zc = (bid / CT) % BCH;
-  const int dj0 = (ct * CW + wv % CW) * 16 * Q, z = zc * SUBS + wv / CW;
+  const int bid = (int)blockIdx.x, di = bid / (CT * BCH), ct = bid % CT, z = (bid / CT) % BCH;
+  const int dj0 = (ct * 4 + wv) * 16, dj = dj0 + l16;
   const int b_lo = z * NB, b_hi = b_lo + NB;
   // Range h: a0[h] + [0, len[h]); steps of eight pairs; its first row of cs.
   auto len = [&](int h) { return h ? di : N - di; };
@@ -682,9 +1017,8 @@ __global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_wa
   const int steps0 = ((N - di + 1) / 2 + 7) / 8, steps1 = ((di + 1) / 2 + 7) / 8;
   auto steps = [&](int h) { return h ? steps1 : steps0; };
   const int row1 = 8 * steps0, zrow = 8 * (steps0 + steps1);  // zrow is at most N/2 + 8: the zero step follows
-  auto swz = [](int j, int k) { return sizeof(T) == 8 && K >= 32 ? k ^ ((j & 1) << 4) : k; };
   auto uswz = [](int m, int k) { return k ^ ((2 * (m & 15)) & (K - 1)); };
-  for (int e = tid; e < (zrow + 8) * K; e += 64 * W) {
+  for (int e = tid; e < (zrow + 8) * K; e += 256) {
     const int j = e / K, k = e % K;
     const int h = j >= row1 ? 1 : 0, p = j - (h ? row1 : 0), n = len(h);
     double si = 0.0, co = 0.0;
@@ -695,9 +1029,9 @@ __global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_wa
       sincospi(2.0 * c, &si, &co);
       if (2 * p + 1 == n) co = 0.5;  // the middle row, met twice
     }
-    cs[j * K + swz(j, k)] = T{(Rt)co, (Rt)si};
+    cs[e] = T{co, si};
   }
-  for (int e = tid; e < 2 * K; e += 64 * W) {
+  for (int e = tid; e < 2 * K; e += 256) {
     const int h = e / K, k = e % K;
     double si = 0.0, co = 0.0;
     if (k < rates.count) {
@@ -705,19 +1039,19 @@ __global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_wa
       c -= rint(c);
       sincospi(2.0 * c, &si, &co);
     }
-    kap[h][k] = T{(Rt)co, (Rt)si};
+    kap[h][k] = T{co, si};
   }
   if constexpr (kLdsB) {
-    for (int e = tid; e < NB * SUBS * K; e += 64 * W) us[e] = u1t[(zc * NB * SUBS + e / K) * kPairTile + e % K];
-    for (int e = tid; e < N * K; e += 64 * W) {
+    for (int e = tid; e < NB * K; e += 256) us[e] = u1t[(b_lo + e / K) * kPairTile + e % K];
+    for (int e = tid; e < N * K; e += 256) {
       const int m = e / K, k = e % K;
-      us[NB * SUBS * K + m * K + uswz(m, k)] = u2t[m * kPairTile + k];
+      us[NB * K + m * K + uswz(m, k)] = u2t[m * kPairTile + k];
     }
   }
   __syncthreads();
   const GlobalPtr<T> w0 = (GlobalPtr<T>)const_cast<T*>(w);
   struct Step {
-    T hi[2][Q], lo[2][Q];
+    T hi[2], lo[2];
   };
   struct Pos {
     int h, b, st;
@@ -735,39 +1069,29 @@ __global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_wa
     const int h = in ? p.h : 0, b = in ? p.b : b_hi - 1, st = in ? p.st : 0;
     const int n = len(h), pairs = (n + 1) / 2, a0 = first(h);
     const GlobalPtr<T> wb = w0 + (long long)b * NN - (long long)delta(h) * N;
+    const int col = (b - dj) & NM;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       const int j = 8 * st + 4 * s + kq, jj = j < pairs ? j : pairs - 1;
-      const GlobalPtr<T> ph = wb + (long long)(a0 + n - 1 - jj) * (NNN + N);
-      const GlobalPtr<T> pl = wb + (long long)(a0 + jj) * (NNN + N);
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const int col = (b - dj0 - 16 * q - l16) & NM;
-        r.hi[s][q] = load_elem<T>(ph + col);
-        r.lo[s][q] = load_elem<T>(pl + col);
-      }
+      r.hi[s] = load_elem<T>(wb + (long long)(a0 + n - 1 - jj) * (NNN + N) + col);
+      r.lo[s] = load_elem<T>(wb + (long long)(a0 + jj) * (NNN + N) + col);
     }
   };
-  V gr[R][Q], gi[R][Q];
-  T f[R][Q][4];
-  const T zero{(Rt)0, (Rt)0};
+  V gr[R], gi[R];
+  T f[R][4];
+  const T zero{0.0, 0.0};
 #pragma unroll
-  for (int r = 0; r < R; ++r)
+  for (int r = 0; r < R; ++r) {
+    gr[r] = gi[r] = V{0, 0, 0, 0};
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      gr[r][q] = gi[r][q] = V{0, 0, 0, 0};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) f[r][q][i] = zero;
-    }
+    for (int i = 0; i < 4; ++i) f[r][i] = zero;
+  }
   auto read_a = [&](T (&e)[2][R], const Pos& p) {
     const int j0 = p.h < h_end ? (p.h ? row1 : 0) + 8 * p.st : zrow;
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int j = j0 + 4 * s + kq;
-        e[s][r] = cs[j * K + swz(j, 16 * r + l16)];
-      }
+      for (int r = 0; r < R; ++r) e[s][r] = cs[(j0 + 4 * s + kq) * K + 16 * r + l16];
   };
   T* const out = part + (long long)(POLY ? z : 2 * z) * kPairTile * (POLY ? 4 * NN : NN);
   auto bin_at = [&](int k, int h, int dj_bin) {
@@ -784,7 +1108,7 @@ __global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_wa
   }
   T av[2][2][R];
   read_a(av[0], cp);
-  T ub[kLdsB ? 1 : R][4], vb[kLdsB ? 1 : R][Q][4];
+  T ub[kLdsB ? 1 : R][4], vb[kLdsB ? 1 : R][4];
   const int total = NB * (steps0 + steps1);
   for (int t0 = 0; t0 < total; t0 += RING) {
 #pragma unroll
@@ -801,30 +1125,27 @@ __global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_wa
             for (int i = 0; i < 4; ++i) {
               const int k = 16 * r + Mfma<T>::row(lane, i);
               ub[r][i] = u1[k * N + cp.b];
-#pragma unroll
-              for (int q = 0; q < Q; ++q) vb[r][q][i] = u2[k * N + ((cp.b - dj0 - 16 * q - l16) & NM)];
+              vb[r][i] = u2[k * N + ((cp.b - dj) & NM)];
             }
         }
       }
       read_a(av[(u + 1) % 2], np);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int s = 0; s < 2; ++s)
+      for (int s = 0; s < 2; ++s) {
+        const T hi = ring[u].hi[s], lo = ring[u].lo[s];
+        const T e{hi.x + lo.x, hi.y + lo.y}, o{lo.x - hi.x, hi.y - lo.y};  // o: -i (hi - lo) = (o.y, o.x)
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-          const T hi = ring[u].hi[s][q], lo = ring[u].lo[s][q];
-          const T e{hi.x + lo.x, hi.y + lo.y}, o{lo.x - hi.x, hi.y - lo.y};  // o: -i (hi - lo) = (o.y, o.x)
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            gr[r][q] = Mfma<T>::mac(av[u % 2][s][r].x, e.x, gr[r][q]);
-            gi[r][q] = Mfma<T>::mac(av[u % 2][s][r].x, e.y, gi[r][q]);
-          }
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            gr[r][q] = Mfma<T>::mac(av[u % 2][s][r].y, o.y, gr[r][q]);
-            gi[r][q] = Mfma<T>::mac(av[u % 2][s][r].y, o.x, gi[r][q]);
-          }
+        for (int r = 0; r < R; ++r) {
+          gr[r] = Mfma<T>::mac(av[u % 2][s][r].x, e.x, gr[r]);
+          gi[r] = Mfma<T>::mac(av[u % 2][s][r].x, e.y, gi[r]);
         }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          gr[r] = Mfma<T>::mac(av[u % 2][s][r].y, o.y, gr[r]);
+          gi[r] = Mfma<T>::mac(av[u % 2][s][r].y, o.x, gi[r]);
+        }
+      }
       if (cp.h < h_end && cp.st + 1 == steps(cp.h)) {  // the last step of b (wavefront-uniform)
         const bool range_end = cp.b + 1 == b_hi;
 #pragma unroll
@@ -832,26 +1153,21 @@ __global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_wa
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int k = 16 * r + Mfma<T>::row(lane, i);
-            T x;
-            if constexpr (kLdsB)
-              x = us[(cp.b - zc * NB * SUBS) * K + k];
-            else
+            T x, y;
+            if constexpr (kLdsB) {
+              const int m = (cp.b - dj) & NM;
+              x = us[(cp.b - b_lo) * K + k];
+              y = us[NB * K + m * K + uswz(m, k)];
+            } else {
               x = ub[r][i];
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-              const int dj = dj0 + 16 * q + l16, m = (cp.b - dj) & NM;
-              T y;
-              if constexpr (kLdsB)
-                y = us[NB * SUBS * K + m * K + uswz(m, k)];
-              else
-                y = vb[r][q][i];
-              const T c = cmul(x, y), g{gr[r][q][i], gi[r][q][i]};
-              f[r][q][i] = cadd(f[r][q][i], cmul(c, g));
-              if constexpr (POLY) {
-                if (cp.b == dj - 1 && dj < b_hi) {  // the lower bin is complete (at d_j = b_hi it is stored below)
-                  out[bin_at(k, cp.h, dj - N)] = cmul(kap[cp.h][k], f[r][q][i]);
-                  f[r][q][i] = zero;
-                }
+              y = vb[r][i];
+            }
+            const T c = cmul(x, y), g{gr[r][i], gi[r][i]};
+            f[r][i] = cadd(f[r][i], cmul(c, g));
+            if constexpr (POLY) {
+              if (cp.b == dj - 1 && dj < b_hi) {  // the lower bin is complete (at d_j = b_hi it is stored below)
+                out[bin_at(k, cp.h, dj - N)] = cmul(kap[cp.h][k], f[r][i]);
+                f[r][i] = zero;
               }
             }
           }
@@ -861,30 +1177,23 @@ __global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_wa
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
               const int k = 16 * r + Mfma<T>::row(lane, i);
-              const T ka = kap[cp.h][k];
-#pragma unroll
-              for (int q = 0; q < Q; ++q) {
-                const int dj = dj0 + 16 * q + l16;
-                const T v = cmul(ka, f[r][q][i]);
-                if constexpr (POLY) {
-                  if (dj >= b_hi) {  // every b of the chunk is below d_j
-                    out[bin_at(k, cp.h, dj - N)] = v;
-                    out[bin_at(k, cp.h, dj)] = zero;
-                  } else {
-                    out[bin_at(k, cp.h, dj)] = v;
-                    if (dj <= b_lo) out[bin_at(k, cp.h, dj - N)] = zero;  // no b of the chunk is below d_j
-                  }
+              const T v = cmul(kap[cp.h][k], f[r][i]);
+              if constexpr (POLY) {
+                if (dj >= b_hi) {  // every b of the chunk is below d_j
+                  out[bin_at(k, cp.h, dj - N)] = v;
+                  out[bin_at(k, cp.h, dj)] = zero;
                 } else {
                   out[bin_at(k, cp.h, dj)] = v;
+                  if (dj <= b_lo) out[bin_at(k, cp.h, dj - N)] = zero;  // no b of the chunk is below d_j
                 }
-                f[r][q][i] = zero;
+              } else {
+                out[bin_at(k, cp.h, dj)] = v;
               }
+              f[r][i] = zero;
             }
         }
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-          for (int q = 0; q < Q; ++q) gr[r][q] = gi[r][q] = V{0, 0, 0, 0};
+        for (int r = 0; r < R; ++r) gr[r] = gi[r] = V{0, 0, 0, 0};
       }
       cp = np;
       __builtin_amdgcn_sched_barrier(0);
@@ -894,13 +1203,11 @@ __global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_wa
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int q = 0; q < Q; ++q)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int k = 16 * r + Mfma<T>::row(lane, i), dj = dj0 + 16 * q + l16;
-          out[bin_at(k, 1, dj)] = zero;
-          if constexpr (POLY) out[bin_at(k, 1, dj - N)] = zero;
-        }
+      for (int i = 0; i < 4; ++i) {
+        const int k = 16 * r + Mfma<T>::row(lane, i);
+        out[bin_at(k, 1, dj)] = zero;
+        if constexpr (POLY) out[bin_at(k, 1, dj - N)] = zero;
+      }
   }
 }
 
@@ -1546,35 +1853,36 @@ static hipError_t launch_rows_fold(int n, int count, const T* w, const T* u1t, i
   return hipGetLastError();
 }
 
-// The mirrored form of the difference sums (count >= 2) at N = 64 and 128: the chunks of b it writes (twice as many parts for
-// a Fresnel group, one per range), 256 workgroups; 0 at other N, which the LDS-staged kernels cover. Against those, and
-// against a ring of 3M products at N = 128 in complex64, which this replaced: N = 128 complex64 985 -> 870 us (64 pairs),
-// 560 -> 555 (30), 457 -> 460 (12), unfolded bins 1.44 ms -> 0.91 (64), 534 -> 535 us (16); complex128 2.25 -> 2.0 ms
-// (64), unfolded 3.1 -> 0.96 ms (16); N = 64 complex128 180 -> 95 us (23), complex64 98 -> 54 us (20).
-template <class T> static int diffs_mirror_parts(int n) {
-  if (n == 64) return sizeof(T) == 8 ? 8 : 4;
-  if (n == 128) return sizeof(T) == 8 ? 2 : 1;
-  return 0;
-}
+// The mirrored form of a complex128 group's difference sums (count >= 2) at N = 64 and 128: the chunks of b it writes (twice as
+// many parts for a Fresnel group, one per range), 256 workgroups; 0 at other N, which the LDS-staged kernels cover.
+// Against those: N = 128 2.25 -> 2.0 ms (64 pairs), unfolded bins 3.1 -> 0.96 ms (16); N = 64 180 -> 95 us (23).
+static int diffs_mirror_parts(int n) { return n == 64 ? 4 : n == 128 ? 1 : 0; }
 
-template <class T, bool POLY>
-static hipError_t launch_diffs_mirror(int n, int count, const double* alpha, const T* w, const T* u1, const T* u2,
-                                      const T* tr, T* part, hipStream_t st) {
+template <bool POLY>
+static hipError_t launch_diffs_mirror(int n, int count, const double* alpha, const double2* w, const double2* u1,
+                                      const double2* u2, const double2* tr, double2* part, hipStream_t st) {
   DiffRates rates{};
   rates.count = count;
   for (int k = 0; k < count; ++k) rates.alpha[k] = alpha[k];
-  using Diffs = void (*)(const T*, const T*, const T*, const T*, const T*, DiffRates, T*);
-  constexpr int B128 = sizeof(T) == 8 ? 2 : 1;
+  using Diffs = void (*)(const double2*, const double2*, const double2*, const double2*, const double2*, DiffRates,
+                         double2*);
   Diffs diffs;
   if (n == 64)
-    diffs = count > 32 ? k_diffs_mirror<T, 64, 4, 4, POLY> : count > 16 ? k_diffs_mirror<T, 64, 2, 4, POLY>
-                                                                           : k_diffs_mirror<T, 64, 1, 4, POLY>;
+    diffs = count > 32 ? k_diffs_mirror<64, 4, 4, POLY> : count > 16 ? k_diffs_mirror<64, 2, 4, POLY>
+                                                                     : k_diffs_mirror<64, 1, 4, POLY>;
   else
-    diffs = count > 32 ? k_diffs_mirror<T, 128, 4, B128, POLY> : count > 16 ? k_diffs_mirror<T, 128, 2, B128, POLY>
-                                                                               : k_diffs_mirror<T, 128, 1, B128, POLY>;
-  hipLaunchKernelGGL(diffs, dim3(256), dim3(count > 32 ? 64 * kStreamWaves<T, 4> : 256), 0, st, w, u1, u2, tr, tr + (long long)kPairTile * n, rates, part);
+    diffs = count > 32 ? k_diffs_mirror<128, 4, 1, POLY> : count > 16 ? k_diffs_mirror<128, 2, 1, POLY>
+                                                                      : k_diffs_mirror<128, 1, 1, POLY>;
+  hipLaunchKernelGGL(diffs, dim3(256), dim3(256), 0, st, w, u1, u2, tr, tr + (long long)kPairTile * n, rates, part);
   return hipGetLastError();
 }
+
+// The ring form of the Fresnel difference sums (complex64, N = 128, any count) writes 256 / N chunks of b.
+static bool diffs_ring_ok(int n, int count) { return n == 128 && count >= 1; }
+
+// The ring form of the polychromatic difference sums (complex64, N = 128, any count) writes 256 / N chunks
+// of b.
+static bool poly_diffs_ring_ok(int n, int count) { return n == 128 && count >= 1; }
 
 template <class T>
 static hipError_t launch_mfma(int count, int kind, int n, const T* w, const T* u1, const T* u2, const T* tr,
@@ -1592,6 +1900,23 @@ static hipError_t launch_mfma(int count, int kind, int n, const T* w, const T* u
                                     : (count > 32 ? k_pair_rows_ring<128, 4>
                                                   : count > 16 ? k_pair_rows_ring<128, 2> : k_pair_rows_ring<128, 1>);
       hipLaunchKernelGGL(rows, dim3(256), dim3(256), 0, st, w, tr + 2 * tq, tr + 3 * tq, ring_chunk, 256, part);
+      return hipGetLastError();
+    }
+    if (kind == 1 && diffs_ring_ok(n, count)) {
+      using DiffsRing = void (*)(const float2*, const float2*, const float2*, float2*);
+      const DiffsRing diffs = count > 32   ? k_pair_diffs_ring<128, 4>
+                              : count > 16 ? k_pair_diffs_ring<128, 2>
+                                           : k_pair_diffs_ring<128, 1>;
+      hipLaunchKernelGGL(diffs, dim3(256), dim3(256), 0, st, w, tr, tr + tq, part);
+      return hipGetLastError();
+    }
+    if (kind == 2 && poly_diffs_ring_ok(n, count)) {
+      if (count <= 16) {
+        hipLaunchKernelGGL((k_poly_diffs_ring<128, 1, 8>), dim3(256), dim3(256), 0, st, w, tr, tr + tq, 0, part);
+      } else {  // tiles of 32 pairs, one launch each
+        for (int k0 = 0; k0 < count; k0 += 32)
+          hipLaunchKernelGGL((k_poly_diffs_ring<128, 2, 4>), dim3(256), dim3(256), 0, st, w, tr, tr + tq, k0, part);
+      }
       return hipGetLastError();
     }
     if (count <= 32) return launch_mfma_tm<T, 32>(kind, n, w, u1, u2, tr, chunk, bchunk, sb, part, st);
@@ -1666,18 +1991,18 @@ hipError_t launch_pair_sums(int n, const T* w, const double* a_src, int count, i
   else
     e = launch_mfma<T>(count, 0, n, w, u1, u2, tr, chunk, bchunk, sb, part_r, st);
   if (e != hipSuccess) return e;
-  const int mirrored = diffs_mirror_parts<T>(n);
-  if (mirrored > 0)
-    e = launch_diffs_mirror<T, false>(n, count, a_src, w, u1, u2, tr, part_d, st);
-  else
-    e = launch_mfma<T>(count, 1, n, w, u1, u2, tr, chunk, bchunk, sb, part_d, st);
+  const int mirrored = sizeof(T) == 16 ? diffs_mirror_parts(n) : 0;
+  if constexpr (sizeof(T) == 16) {
+    if (mirrored > 0) e = launch_diffs_mirror<false>(n, count, a_src, w, u1, u2, tr, part_d, st);
+  }
+  if (mirrored == 0) e = launch_mfma<T>(count, 1, n, w, u1, u2, tr, chunk, bchunk, sb, part_d, st);
   if (e != hipSuccess) return e;
   const unsigned sum_blocks = (unsigned)((count * nn + 255) / 256);  // the group's pairs only
   const int sr = folded > 0 ? folded : kPairSplitK;
   hipLaunchKernelGGL(k_pair_sum<T>, dim3(sum_blocks), dim3(256), 0, st, (const T*)part_r, sr, n, count, kPairTile,
                      (const T*)u2, buf_r);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int sd = mirrored > 0 ? 2 * mirrored : sb;  // parts written
+  const int sd = mirrored > 0 ? 2 * mirrored : sizeof(T) == 8 && diffs_ring_ok(n, count) ? 256 / n : sb;  // parts written
   hipLaunchKernelGGL(k_pair_sum<T>, dim3(sum_blocks), dim3(256), 0, st, (const T*)part_d, sd, n, count, kPairTile,
                      (const T*)nullptr, buf_d);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1787,18 +2112,18 @@ hipError_t launch_poly(int n, const T* w, int n_pairs, const double* alpha, cons
       const long long chunk = (nn + kPairSplitK - 1) / kPairSplitK;
       const int bchunk = (n + sb - 1) / sb;
       if ((e = launch_mfma<T>(pg.count, 0, n, w, u1, u2, tr, chunk, bchunk, sb, part_r, st)) != hipSuccess) return e;
-      const int mirrored = diffs_mirror_parts<T>(n);
-      if (mirrored > 0)
-        e = launch_diffs_mirror<T, true>(n, pg.count, pg.alpha, w, u1, u2, tr, part_d, st);
-      else
-        e = launch_mfma<T>(pg.count, 2, n, w, u1, u2, tr, chunk, bchunk, sb, part_d, st);
+      const int mirrored = sizeof(T) == 16 ? diffs_mirror_parts(n) : 0;
+      if constexpr (sizeof(T) == 16) {
+        if (mirrored > 0) e = launch_diffs_mirror<true>(n, pg.count, pg.alpha, w, u1, u2, tr, part_d, st);
+      }
+      if (mirrored == 0) e = launch_mfma<T>(pg.count, 2, n, w, u1, u2, tr, chunk, bchunk, sb, part_d, st);
       if (e != hipSuccess) return e;
       const int rp = sizeof(T) == 8 ? rows_ring_parts(n, pg.count) : 0;
       const int sr = rp > 0 ? rp : kPairSplitK;
       hipLaunchKernelGGL(k_pair_sum<T>, dim3((unsigned)((pg.count * nn + 255) / 256)), dim3(256), 0, st, (const T*)part_r, sr,
                          n, pg.count, kPairTile, (const T*)u2, rr);
       if ((e = hipGetLastError()) != hipSuccess) return e;
-      const int sdp = mirrored > 0 ? mirrored : sb;  // chunks of b written
+      const int sdp = mirrored > 0 ? mirrored : sizeof(T) == 8 && poly_diffs_ring_ok(n, pg.count) ? 256 / n : sb;
       hipLaunchKernelGGL(k_pair_sum<T>, dim3((unsigned)((pg.count * 4 * nn + 255) / 256)), dim3(256), 0, st,
                          (const T*)part_d, sdp, 2 * n, pg.count, kPairTile, (const T*)nullptr, dfull);
       if ((e = hipGetLastError()) != hipSuccess) return e;
