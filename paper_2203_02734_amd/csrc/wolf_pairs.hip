@@ -304,66 +304,58 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
 }
 
-// Wavefronts of a workgroup of the mirrored row sums below (one workgroup per CU) and blocks of 16 columns per
-// wavefront, for R tiles of 16 pairs. With four tiles complex64 takes two wavefronts per SIMD over one block each, so that
-// one's vector work runs beside the other's products; with fewer the read of W bounds the pass, and one wavefront over two
-// blocks has the longer runs. N = 128 complex64, row and difference sums: 64 pairs 450 and 980 us with one wavefront, 410 and
-// 875 us with two; 12 pairs 350 and 457 us with one, 357 and 580 us with two. complex128 holds one block per wavefront.
-template <class T, int R> constexpr int kStreamWaves = sizeof(T) == 8 && R == 4 ? 8 : 4;
-template <class T, int R> constexpr int kStreamBlocks = sizeof(T) == 8 && R < 4 ? 2 : 1;
-// Columns of a workgroup: 128 in complex64, 64 in complex128.
-template <class T> constexpr int kStreamColumns = 1024 / (int)sizeof(T);
-
-// Row sums of a Fresnel batch group by the mirror symmetry of the source chirp: with c = N/2, u1[c + m] = u1[c - m] = v[m]
-// for every pair, and the phase e^{2 pi i P a / N} is the same for all pairs, so mirrored rows of W meet before the product:
+// Row sums of a complex128 Fresnel batch group by the mirror symmetry of the source chirp: with c = N/2,
+// u1[c + m] = u1[c - m] = v[m] for every pair, and the phase e^{2 pi i P a / N} is the same for all pairs, so mirrored
+// rows of W meet before the product:
 //   R[k][p2] = sum_{l, m = 0}^{c} v_k[l] v_k[m] Y_{l,m}[p2],
 //   Y_{l,m}  = sum over the signs of e^{2 pi i (P_i (c +- l) + P_j (c +- m)) / N} W[(c +- l) N + c +- m][p2]
-// (one sign at l or m = 0 and at c: the grid ends at c - 1). A quarter of the matrix-core work of k_pair_rows_ring, for 12
-// vector FMAs per element of W. The stream of W is kept in flight as there: a wavefront owns 16 R pairs and 16 Q columns, a
-// step is four values of m of one l (16 rows of W, 3 Q R MFMAs into G_l = sum_m v[m] Y) and RING steps sit in registers. Y of
-// a step is formed between the products of the step before (a wavefront alone on its SIMD overlaps the two only so). The
-// blocks are l = 0 .. c over m < c, each folded with v[l], and one for m = c, which sums over l < c and is folded with v[c];
-// the corner l = m = c is added at the end. So a block is N / 8 steps, whole turns of the ring, and the fold stands once
-// after them. Loads are unconditional (past the chunk's last block they re-read it). A workgroup takes one tile of 64 Q
-// columns and one of `chunks` ranges of blocks: part[chunk][k][p2].
-// Bound: the read of W (and the matrix cores at 64 pairs). Measured: see rows_fold_parts.
-template <class T, int N, int R>
-__global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_waves_per_eu((kStreamWaves<T, R> / 4), (kStreamWaves<T, R> / 4)))) void k_pair_rows_fold(
-    const T* __restrict__ w, const T* __restrict__ u1t, int pi, int pj, int chunks, T* __restrict__ part) {
+// (one sign at l or m = 0 and at c: the grid ends at c - 1). A quarter of the matrix-core work of k_pair_rows_mfma, for 12
+// vector FMAs per element of W. The stream of W is kept in flight as in k_pair_rows_ring: a wavefront owns 16 R pairs and 16
+// columns (four wavefronts and 64 columns a workgroup, one workgroup per CU), a step is four values of m of one l (16 rows of
+// W, 3 R MFMAs into G_l = sum_m v[m] Y) and RING steps sit in registers. Y of a step is formed between the products of the
+// step before (a wavefront alone on its SIMD overlaps the two only so). The blocks are l = 0 .. c over m < c, each folded with
+// v[l], and one for m = c, which sums over l < c and is folded with v[c]; the corner l = m = c is added at the end. So a block
+// is N / 8 steps, whole turns of the ring, and the fold stands once after them. Loads are unconditional (past the chunk's last
+// block they re-read it). A workgroup takes one tile of 64 columns and one of `chunks` ranges of blocks: part[chunk][k][p2].
+// Bound: the read of W (and the matrix cores at 64 pairs). Measured: see rows_fold_parts. complex64 stays with
+// k_pair_rows_ring: here the phase and the chirp are rounded to the type by themselves and W passes two vector roundings
+// before the product, which in FP32 made W(P, .) of a beam at N = 128 up to a quarter less exact (1.2e-7 -> 1.5e-7).
+template <int N, int R>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_pair_rows_fold(
+    const double2* __restrict__ w, const double2* __restrict__ u1t, int pi, int pj, int chunks,
+    double2* __restrict__ part) {
+  using T = double2;
   using V = typename Mfma<T>::V;
-  using Rt = typename real_of<T>::type;
-  constexpr int Q = kStreamBlocks<T, R>, W = kStreamWaves<T, R>, C = N / 2, MS = C / 4, RING = MS < 8 ? MS : 8;
+  constexpr int C = N / 2, MS = C / 4, RING = MS < 8 ? MS : 8;
   constexpr unsigned EB = sizeof(T);
   constexpr long long NN = (long long)N * N, NNN = NN * N;
-  constexpr int TILES = (int)(NN / (16 * Q * W));
+  constexpr int TILES = (int)(NN / 64);
   static_assert(MS % RING == 0, "blocks of whole turns");
-  __shared__ T vm[(C + 1) * kPairTile];        // v[m][k] at m 64 + swz(m, k)
+  __shared__ T vm[(C + 1) * kPairTile];        // v[m][k] at m 64 + k
   __shared__ T phj[2][C + 1], phi[2][C + 1];   // the phases of the two signs, zero where a sign has no row
   const int tid = threadIdx.x, lane = tid % 64, l16 = lane % 16, kq = lane / 16;
   const int wv = __builtin_amdgcn_readfirstlane(tid / 64);
-  // Two rows of 8-byte entries 512 B apart share their banks: odd rows are exchanged by 16 pairs.
-  auto swz = [](int m, int k) { return sizeof(T) == 8 ? k ^ ((m & 1) << 4) : k; };
-  for (int e = tid; e < (C + 1) * kPairTile; e += 64 * W) {
+  for (int e = tid; e < (C + 1) * kPairTile; e += 256) {
     const int m = e / kPairTile, k = e % kPairTile;
-    vm[m * kPairTile + swz(m, k)] = u1t[(C - m) * kPairTile + k];
+    vm[e] = u1t[(C - m) * kPairTile + k];
   }
   auto phase = [&](int P, int d, int sgn) {  // e^{2 pi i P (c + sgn d) / N}, zero where that is no row
     const bool row = !(sgn > 0 && d == C) && !(sgn < 0 && d == 0);
     double si, co;
     sincospi(2.0 * (double)((P * (C + sgn * d)) % N) / (double)N, &si, &co);
-    return T{(Rt)(row ? co : 0.0), (Rt)(row ? si : 0.0)};
+    return T{row ? co : 0.0, row ? si : 0.0};
   };
-  for (int e = tid; e < 4 * (C + 1); e += 64 * W) {
+  for (int e = tid; e < 4 * (C + 1); e += 256) {
     const int which = e / (C + 1), d = e % (C + 1), sgn = which % 2 ? -1 : 1;
     (which < 2 ? phj[which] : phi[which - 2])[d] = phase(which < 2 ? pj : pi, d, sgn);
   }
   __syncthreads();
   const int tile = (int)blockIdx.x % TILES, chunk = (int)blockIdx.x / TILES;
   const int b_lo = (C + 2) * chunk / chunks, b_hi = (C + 2) * (chunk + 1) / chunks;  // blocks; C + 1: the rows m = c
-  const int col = (tile * W + wv) * 16 * Q + l16;
+  const int col = (tile * 4 + wv) * 16 + l16;
   const GlobalPtr<T> w0 = (GlobalPtr<T>)const_cast<T*>(w);
   struct Step {
-    T v[4][Q];  // W at (c + l, c + m), (c + l, c - m), (c - l, c + m), (c - l, c - m); block m = c: (c + l, 0), (c - l, 0) twice
+    T v[4];  // W at (c + l, c + m), (c + l, c - m), (c - l, c + m), (c - l, c - m); block m = c: (c + l, 0), (c - l, 0) twice
   };
   // Steps in order (block, ms); the load's position runs RING - 1 steps ahead of the product's.
   struct Pos {
@@ -385,29 +377,24 @@ __global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_wa
     const long long dn = rim ? (long long)C * NNN : (long long)(C - l) * NNN + C * NN;
     const unsigned op = ((unsigned)kq * st + (unsigned)col) * EB, om = ((unsigned)(3 - kq) * st + (unsigned)col) * EB;
     const long long back = at + 3ll * st;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      r.v[0][q] = load_elem<T>(byte_at<T>(w0 + up + at + 16 * q, op));
-      r.v[1][q] = load_elem<T>(byte_at<T>(w0 + up - back + 16 * q, om));
-      r.v[2][q] = load_elem<T>(byte_at<T>(w0 + dn + at + 16 * q, op));
-      r.v[3][q] = load_elem<T>(byte_at<T>(w0 + dn - back + 16 * q, om));
-    }
+    r.v[0] = load_elem<T>(byte_at<T>(w0 + up + at, op));
+    r.v[1] = load_elem<T>(byte_at<T>(w0 + up - back, om));
+    r.v[2] = load_elem<T>(byte_at<T>(w0 + dn + at, op));
+    r.v[3] = load_elem<T>(byte_at<T>(w0 + dn - back, om));
   };
-  V t1[R][Q], t2[R][Q], t3[R][Q];
-  T f[R][Q][4];
+  V t1[R], t2[R], t3[R];
+  T f[R][4];
 #pragma unroll
-  for (int r = 0; r < R; ++r)
+  for (int r = 0; r < R; ++r) {
+    t1[r] = t2[r] = t3[r] = V{0, 0, 0, 0};
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      t1[r][q] = t2[r][q] = t3[r][q] = V{0, 0, 0, 0};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) f[r][q][i] = T{(Rt)0, (Rt)0};
-    }
-  T av[2][R], ph[2][4], y[2][Q];
+    for (int i = 0; i < 4; ++i) f[r][i] = T{0.0, 0.0};
+  }
+  T av[2][R], ph[2][4], y[2];
   auto read_a = [&](T (&e)[R], const Pos& p) {
     const int m = 4 * p.ms + kq;
 #pragma unroll
-    for (int r = 0; r < R; ++r) e[r] = vm[m * kPairTile + swz(m, 16 * r + l16)];
+    for (int r = 0; r < R; ++r) e[r] = vm[m * kPairTile + 16 * r + l16];
   };
   // (inner +, inner -, outer +, outer -); the rim's inner index is l and its outer phase that of c - c.
   auto read_phases = [&](T (&e)[4], const Pos& p) {
@@ -419,13 +406,10 @@ __global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_wa
     e[2] = (rim ? phj[0] : phi[0])[l];
     e[3] = (rim ? phj[1] : phi[1])[l];
   };
-  auto form = [&](T (&o)[Q], const Step& b, const T (&e)[4]) {
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const T xp = cadd(cmul(e[0], b.v[0][q]), cmul(e[1], b.v[1][q]));
-      const T xm = cadd(cmul(e[0], b.v[2][q]), cmul(e[1], b.v[3][q]));
-      o[q] = cadd(cmul(e[2], xp), cmul(e[3], xm));
-    }
+  auto form = [&](T& o, const Step& b, const T (&e)[4]) {
+    const T xp = cadd(cmul(e[0], b.v[0]), cmul(e[1], b.v[1]));
+    const T xm = cadd(cmul(e[0], b.v[2]), cmul(e[1], b.v[3]));
+    o = cadd(cmul(e[2], xp), cmul(e[3], xm));
   };
   Step ring[RING];
   Pos lp{b_lo, 0}, np{b_lo, 0}, np2{b_lo, 0};  // the load's, the next step's and the one after it
@@ -452,26 +436,21 @@ __global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_wa
         read_phases(ph[u % 2], np2);
         __builtin_amdgcn_sched_barrier(0);
         form(y[(u + 1) % 2], ring[(u + 1) % RING], ph[(u + 1) % 2]);
+        const T yq = y[u % 2];
+        const double ys = yq.x + yq.y;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-          const T yq = y[u % 2][q];
-          const Rt ys = yq.x + yq.y;
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            const T x = av[u % 2][r];
-            t1[r][q] = Mfma<T>::mac(x.x, yq.x, t1[r][q]);
-            t2[r][q] = Mfma<T>::mac(x.y, yq.y, t2[r][q]);
-            t3[r][q] = Mfma<T>::mac(x.x + x.y, ys, t3[r][q]);
-          }
+        for (int r = 0; r < R; ++r) {
+          const T x = av[u % 2][r];
+          t1[r] = Mfma<T>::mac(x.x, yq.x, t1[r]);
+          t2[r] = Mfma<T>::mac(x.y, yq.y, t2[r]);
+          t3[r] = Mfma<T>::mac(x.x + x.y, ys, t3[r]);
         }
 #pragma unroll
-        for (int i = 0; i < 3 * R * Q; ++i) {  // one product, then a few of the vector instructions
+        for (int i = 0; i < 3 * R; ++i) {  // one product, then a few of the vector instructions
           __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
           __builtin_amdgcn_sched_group_barrier(0x2, R == 4 ? 3 : R == 2 ? 5 : 10, 0);
         }
-#pragma unroll
-        for (int q = 0; q < Q; ++q)  // keeps the next Y among the products
-          asm volatile("" : "+v"(y[(u + 1) % 2][q].x), "+v"(y[(u + 1) % 2][q].y));
+        asm volatile("" : "+v"(y[(u + 1) % 2].x), "+v"(y[(u + 1) % 2].y));  // keeps the next Y among the products
         np = np2;
         advance(np2);
         __builtin_amdgcn_sched_barrier(0);
@@ -482,40 +461,29 @@ __global__ __launch_bounds__((64 * kStreamWaves<T, R>)) __attribute__((amdgpu_wa
     for (int r = 0; r < R; ++r)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const T c = vm[l * kPairTile + swz(l, 16 * r + Mfma<T>::row(lane, i))];
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-          const Rt gr = t1[r][q][i] - t2[r][q][i], gi = t3[r][q][i] - t1[r][q][i] - t2[r][q][i];
-          f[r][q][i].x += c.x * gr - c.y * gi;
-          f[r][q][i].y += c.x * gi + c.y * gr;
-        }
+        const T c = vm[l * kPairTile + 16 * r + Mfma<T>::row(lane, i)];
+        const double gr = t1[r][i] - t2[r][i], gi = t3[r][i] - t1[r][i] - t2[r][i];
+        f[r][i].x += c.x * gr - c.y * gi;
+        f[r][i].y += c.x * gi + c.y * gr;
       }
+#pragma unroll
+    for (int r = 0; r < R; ++r) t1[r] = t2[r] = t3[r] = V{0, 0, 0, 0};
+  }
+  if (b_hi == C + 2) {  // the corner l = m = c: row 0 of W
+    const T x = cmul(cmul(phi[1][C], phj[1][C]), w[col]);
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int q = 0; q < Q; ++q) t1[r][q] = t2[r][q] = t3[r][q] = V{0, 0, 0, 0};
-  }
-  if (b_hi == C + 2) {  // the corner l = m = c: row 0 of W
-    const T p0 = cmul(phi[1][C], phj[1][C]);
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const T x = cmul(p0, w[col + 16 * q]);
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const T c = vm[C * kPairTile + swz(C, 16 * r + Mfma<T>::row(lane, i))];
-          f[r][q][i] = cadd(f[r][q][i], cmul(cmul(c, c), x));
-        }
-    }
+      for (int i = 0; i < 4; ++i) {
+        const T c = vm[C * kPairTile + 16 * r + Mfma<T>::row(lane, i)];
+        f[r][i] = cadd(f[r][i], cmul(cmul(c, c), x));
+      }
   }
   T* const out = part + (long long)chunk * kPairTile * NN;
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int q = 0; q < Q; ++q)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) out[(16 * r + Mfma<T>::row(lane, i)) * NN + col + 16 * q] = f[r][q][i];
+    for (int i = 0; i < 4; ++i) out[(16 * r + Mfma<T>::row(lane, i)) * NN + col] = f[r][i];
 }
 
 // Difference sums: part[z][k][di N + dj] = sum_{b in chunk z} B_k^{dj}[b] sum_a A_k^{di}[a]
@@ -1826,30 +1794,30 @@ static int rows_ring_parts(int n, int count) {
   return 256 / (n * n / 128);
 }
 
-// The mirrored form of a Fresnel group's row sums (count >= 2): at N = 32, 64, 128 and 256 the number of ranges of blocks it
+// The mirrored form of a complex128 Fresnel group's row sums (count >= 2) at N = 32 to 256: the number of ranges of blocks it
 // writes, one workgroup per CU where the columns allow it; 0 at smaller N, whose few tiles the LDS-staged kernel covers.
-// Measured at N = 128: complex64, 64 pairs 941 -> 410 us (41 % of the matrix rate), 12 pairs 338 -> 350 us (6.1 TB/s);
-// complex128, 64 pairs 2.2 -> 0.80 ms; N = 64 complex128, 23 pairs 130 -> 50 us.
-template <class T> static int rows_fold_parts(int n) {
+// A whole call, LDS-staged -> mirrored: N = 32 12 pairs 80 -> 74 us, 64 pairs 87 -> 85 us; N = 64 23 pairs 272 -> 186 us, 64
+// pairs 358 -> 276 us; N = 128 12 pairs 2.81 -> 1.56 ms, 64 pairs 4.07 -> 2.84 ms (the sums alone 2.2 -> 0.80 ms); N = 256 12
+// pairs 63.5 -> 44.8 ms, 64 pairs 64.3 -> 47.5 ms.
+static int rows_fold_parts(int n) {
   if (n < 32) return 0;
-  const int tiles = n * n / kStreamColumns<T>;
+  const int tiles = n * n / 64;
   return tiles >= 256 ? 1 : (256 / tiles < kPairSplitK ? 256 / tiles : kPairSplitK);
 }
 
-template <class T>
-static hipError_t launch_rows_fold(int n, int count, const T* w, const T* u1t, int pi, int pj, T* part, hipStream_t st) {
-  const int parts = rows_fold_parts<T>(n);
-  const unsigned grid = (unsigned)(n * n / kStreamColumns<T> * parts);
-  using Rows = void (*)(const T*, const T*, int, int, int, T*);
+static hipError_t launch_rows_fold(int n, int count, const double2* w, const double2* u1t, int pi, int pj, double2* part,
+                                   hipStream_t st) {
+  const int parts = rows_fold_parts(n);
+  using Rows = void (*)(const double2*, const double2*, int, int, int, double2*);
   auto of_n = [&](auto nc) -> Rows {
     constexpr int N = decltype(nc)::value;
-    return count > 32 ? k_pair_rows_fold<T, N, 4> : count > 16 ? k_pair_rows_fold<T, N, 2> : k_pair_rows_fold<T, N, 1>;
+    return count > 32 ? k_pair_rows_fold<N, 4> : count > 16 ? k_pair_rows_fold<N, 2> : k_pair_rows_fold<N, 1>;
   };
   const Rows rows = n == 32    ? of_n(std::integral_constant<int, 32>{})
                     : n == 64  ? of_n(std::integral_constant<int, 64>{})
                     : n == 128 ? of_n(std::integral_constant<int, 128>{})
                                : of_n(std::integral_constant<int, 256>{});
-  hipLaunchKernelGGL(rows, dim3(grid), dim3(count > 32 ? 64 * kStreamWaves<T, 4> : 256), 0, st, w, u1t, pi, pj, parts, part);
+  hipLaunchKernelGGL(rows, dim3((unsigned)(n * n / 64 * parts)), dim3(256), 0, st, w, u1t, pi, pj, parts, part);
   return hipGetLastError();
 }
 
@@ -1985,11 +1953,11 @@ hipError_t launch_pair_sums(int n, const T* w, const double* a_src, int count, i
   }
   const long long chunk = (nn + kPairSplitK - 1) / kPairSplitK;
   const int bchunk = (n + sb - 1) / sb;
-  const int folded = rows_fold_parts<T>(n);
-  if (folded > 0)
-    e = launch_rows_fold<T>(n, count, w, tr, pi, pj, part_r, st);
-  else
-    e = launch_mfma<T>(count, 0, n, w, u1, u2, tr, chunk, bchunk, sb, part_r, st);
+  const int folded = sizeof(T) == 16 ? rows_fold_parts(n) : 0;
+  if constexpr (sizeof(T) == 16) {
+    if (folded > 0) e = launch_rows_fold(n, count, w, tr, pi, pj, part_r, st);
+  }
+  if (folded == 0) e = launch_mfma<T>(count, 0, n, w, u1, u2, tr, chunk, bchunk, sb, part_r, st);
   if (e != hipSuccess) return e;
   const int mirrored = sizeof(T) == 16 ? diffs_mirror_parts(n) : 0;
   if constexpr (sizeof(T) == 16) {
@@ -1998,7 +1966,8 @@ hipError_t launch_pair_sums(int n, const T* w, const double* a_src, int count, i
   if (mirrored == 0) e = launch_mfma<T>(count, 1, n, w, u1, u2, tr, chunk, bchunk, sb, part_d, st);
   if (e != hipSuccess) return e;
   const unsigned sum_blocks = (unsigned)((count * nn + 255) / 256);  // the group's pairs only
-  const int sr = folded > 0 ? folded : kPairSplitK;
+  const int ringed = sizeof(T) == 8 ? rows_ring_parts(n, count) : 0;
+  const int sr = folded > 0 ? folded : ringed > 0 ? ringed : kPairSplitK;
   hipLaunchKernelGGL(k_pair_sum<T>, dim3(sum_blocks), dim3(256), 0, st, (const T*)part_r, sr, n, count, kPairTile,
                      (const T*)u2, buf_r);
   if ((e = hipGetLastError()) != hipSuccess) return e;
