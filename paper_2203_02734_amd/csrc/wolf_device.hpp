@@ -37,6 +37,12 @@ template <class T> __device__ __forceinline__ T cmul(T a, T b) {
   return T{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
 }
 template <class T> __device__ __forceinline__ T cconj(T a) { return T{a.x, -a.y}; }
+// sum += x, the rounding of the addition carried to the next in `lost` (Kahan): the error of a chain no longer grows with it.
+template <class T> __device__ __forceinline__ void add_compensated(T& sum, T& lost, T x) {
+  const T y = csub(x, lost), t = cadd(sum, y);
+  lost = csub(csub(t, sum), y);
+  sum = t;
+}
 // a b with each real product rounded before its sum (no fused multiply-add). A pass that either loads
 // its input or forms it (the source) applies its first factor with this, so that both forms give the
 // same bits: a contraction may fuse either product of a sum, and the compiler chooses per call site.

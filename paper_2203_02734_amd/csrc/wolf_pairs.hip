@@ -969,6 +969,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   constexpr int NB = N / BCH;                            // values of b per chunk
   constexpr int PS = N / 2 + 16;                         // pairs of rows of both ranges, whole steps, and a zero step
   constexpr bool kLdsB = N == 64;                        // the factors of b fit the LDS beside the weights
+  // A D of N = 128 is one chain over b (N = 64: four). Without the carried rounding S of a beam was 3.9e-16 off in the 2-norm
+  // (the LDS-staged sums, in twelve chunks: 2.4e-16), with it 2.3e-16. The unfolded bins' chains are shorter: S of the
+  // common-grid sum is 1.8e-16 off (LDS-staged: 1.1e-15).
+  constexpr bool kCompensated = !POLY && N == 128;
   static_assert(NB >= 1, "chunks of b");
   __shared__ T cs[(PS + 8) * K];                         // (cos, sin) of row j, pair k at j K + k
   __shared__ T kap[2][K];
@@ -1046,13 +1050,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
   };
   V gr[R], gi[R];
-  T f[R][4];
+  T f[R][4], lost[kCompensated ? R : 1][4];
   const T zero{0.0, 0.0};
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     gr[r] = gi[r] = V{0, 0, 0, 0};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) f[r][i] = zero;
+    for (int i = 0; i < 4; ++i) {
+      f[r][i] = zero;
+      if constexpr (kCompensated) lost[r][i] = zero;
+    }
   }
   auto read_a = [&](T (&e)[2][R], const Pos& p) {
     const int j0 = p.h < h_end ? (p.h ? row1 : 0) + 8 * p.st : zrow;
@@ -1131,7 +1138,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
               y = vb[r][i];
             }
             const T c = cmul(x, y), g{gr[r][i], gi[r][i]};
-            f[r][i] = cadd(f[r][i], cmul(c, g));
+            if constexpr (kCompensated)
+              add_compensated(f[r][i], lost[r][i], cmul(c, g));
+            else
+              f[r][i] = cadd(f[r][i], cmul(c, g));
             if constexpr (POLY) {
               if (cp.b == dj - 1 && dj < b_hi) {  // the lower bin is complete (at d_j = b_hi it is stored below)
                 out[bin_at(k, cp.h, dj - N)] = cmul(kap[cp.h][k], f[r][i]);
@@ -1158,6 +1168,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 out[bin_at(k, cp.h, dj)] = v;
               }
               f[r][i] = zero;
+              if constexpr (kCompensated) lost[r][i] = zero;
             }
         }
 #pragma unroll
@@ -1823,26 +1834,40 @@ static hipError_t launch_rows_fold(int n, int count, const double2* w, const dou
 
 // The mirrored form of a complex128 group's difference sums (count >= 2) at N = 64 and 128: the chunks of b it writes (twice as
 // many parts for a Fresnel group, one per range), 256 workgroups; 0 at other N, which the LDS-staged kernels cover.
-// Against those: N = 128 2.25 -> 2.0 ms (64 pairs), unfolded bins 3.1 -> 0.96 ms (16); N = 64 180 -> 95 us (23).
+// Against those: unfolded bins at N = 128 3.1 -> 0.96 ms (16 pairs); N = 64 180 -> 95 us (23 pairs). A Fresnel call of 64 pairs at
+// N = 128, LDS-staged difference sums -> mirrored: 4.33 -> 3.20 ms with the row sums', 32 pairs 4.29 -> 1.94 ms.
 static int diffs_mirror_parts(int n) { return n == 64 ? 4 : n == 128 ? 1 : 0; }
 
 template <bool POLY>
 static hipError_t launch_diffs_mirror(int n, int count, const double* alpha, const double2* w, const double2* u1,
                                       const double2* u2, const double2* tr, double2* part, hipStream_t st) {
-  DiffRates rates{};
-  rates.count = count;
-  for (int k = 0; k < count; ++k) rates.alpha[k] = alpha[k];
   using Diffs = void (*)(const double2*, const double2*, const double2*, const double2*, const double2*, DiffRates,
                          double2*);
-  Diffs diffs;
-  if (n == 64)
-    diffs = count > 32 ? k_diffs_mirror<64, 4, 4, POLY> : count > 16 ? k_diffs_mirror<64, 2, 4, POLY>
-                                                                     : k_diffs_mirror<64, 1, 4, POLY>;
-  else
-    diffs = count > 32 ? k_diffs_mirror<128, 4, 1, POLY> : count > 16 ? k_diffs_mirror<128, 2, 1, POLY>
-                                                                      : k_diffs_mirror<128, 1, 1, POLY>;
-  hipLaunchKernelGGL(diffs, dim3(256), dim3(256), 0, st, w, u1, u2, tr, tr + (long long)kPairTile * n, rates, part);
-  return hipGetLastError();
+  // Pairs of a launch: all, but at most 32 (two tiles) where the sums carry their roundings: those of four tiles exceed the
+  // registers of a wavefront (64 pairs at N = 128: one launch 4.38 ms, two 3.20 ms).
+  const int most = n == 64 || POLY ? kPairTile : 32;
+  const long long bins = (long long)n * n * (POLY ? 4 : 1);
+  hipError_t e = hipSuccess;
+  for (int k0 = 0; k0 < count && e == hipSuccess; k0 += most) {
+    DiffRates rates{};
+    rates.count = count - k0 < most ? count - k0 : most;
+    for (int k = 0; k < rates.count; ++k) rates.alpha[k] = alpha[k0 + k];
+    Diffs diffs;
+    if (n == 64)
+      diffs = rates.count > 32   ? k_diffs_mirror<64, 4, 4, POLY>
+              : rates.count > 16 ? k_diffs_mirror<64, 2, 4, POLY>
+                                 : k_diffs_mirror<64, 1, 4, POLY>;
+    else if constexpr (POLY)
+      diffs = rates.count > 32   ? k_diffs_mirror<128, 4, 1, true>
+              : rates.count > 16 ? k_diffs_mirror<128, 2, 1, true>
+                                 : k_diffs_mirror<128, 1, 1, true>;
+    else
+      diffs = rates.count > 16 ? k_diffs_mirror<128, 2, 1, false> : k_diffs_mirror<128, 1, 1, false>;
+    hipLaunchKernelGGL(diffs, dim3(256), dim3(256), 0, st, w, u1 + k0 * n, u2 + k0 * n, tr + k0,
+                       tr + (long long)kPairTile * n + k0, rates, part + k0 * bins);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 // The ring form of the Fresnel difference sums (complex64, N = 128, any count) writes 256 / N chunks of b.

@@ -1,0 +1,56 @@
+"""Rounding of the complex128 sums of the batch against long double."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+P, LAM = 20e-6, 600e-9
+L, CL = np.longdouble, np.clongdouble
+PI = L("3.14159265358979323846264338327950288")
+
+
+def cis(turns):
+    """e^{2 pi i turns} in long double."""
+    a = 2 * PI * (turns - np.rint(turns))
+    return np.cos(a) + 1j * np.sin(a)
+
+
+def beam_axis(n, width, coherence, curve):
+    """One axis of a partially coherent beam with a curved wavefront, rounded to 20 bits: products of two are exact."""
+    x, h = np.arange(n) - n / 2, n / 2
+    f = np.exp(-(x[:, None] ** 2 + x[None, :] ** 2) / (4 * (width * h) ** 2)
+               - (x[:, None] - x[None, :]) ** 2 / (2 * (coherence * h) ** 2)).astype(complex)
+    f *= np.exp(1j * np.pi * curve * (x[None, :] ** 2 - x[:, None] ** 2))
+    return (np.round(f.real * 2.0 ** 20) + 1j * np.round(f.imag * 2.0 ** 20)) / 2.0 ** 20
+
+
+# The register-tiled 3M sums (twelve chunks of b at N = 128) are 2.33e-16 to 2.43e-16 off on these inputs: a tenth above that.
+# A plain chain of N additions, near d = 0 all of one sign, is 3.7e-16 to 4.2e-16 off at N = 128.
+FORMER = 2.43e-16
+
+
+@pytest.mark.parametrize("n,k,probe", [(64, 5, (33, 30)), (64, 40, (34, 31)), (128, 5, (65, 62)), (128, 23, (3, 123)),
+                                       (128, 40, (66, 63))])
+def test_batch_s_of_a_beam(gpu_lib, n, k, probe):
+    """S in the 2-norm, root mean square over pairs of the group."""
+    fx, fy = beam_axis(n, 0.3, 0.1, 0.2 / n), beam_axis(n, 0.25, 0.13, -0.3 / n)
+    tx, ty = torch.from_numpy(fx).cuda(), torch.from_numpy(fy).cuda()
+    w = torch.empty((n,) * 4, dtype=torch.complex128, device="cuda")
+    for i in range(n):
+        w[i] = tx[i][None, :, None] * ty[:, None, :]
+    i = np.arange(k)
+    lam, z = LAM * (0.8 + 0.4 * ((7 * i) % 11) / 11), 0.1 + 0.8 * ((5 * i) % 13) / 13
+    s, _ = gpu_lib.propagate_batch(w, P, lam, z, np.ones(k), ip=probe[0], jp=probe[1], floor_rel=0.0)
+    s = s.cpu().numpy().astype(L)
+    d = (np.arange(n) - n // 2).astype(L)
+    sq = []
+    for q in range(0, k, max(1, k // 6)):
+        lz = lam[q] * z[q]
+        h = cis(-(d[:, None] * d[None, :]) / n) * cis(d * d * L(P * P / lz) / 2)[None, :]
+        bx, by = h.conj() @ fx.astype(CL) @ h.T, h.conj() @ fy.astype(CL) @ h.T
+        ref = L(1.0 / (lz * lz) * P * P * P * P) * np.outer(np.diag(bx).real, np.diag(by).real)
+        sq.append(float(((s[q] - ref) ** 2).sum() / (ref ** 2).sum()))
+    assert np.sqrt(np.mean(sq)) < 1.1 * FORMER
