@@ -43,6 +43,11 @@ template <class T> __device__ __forceinline__ void add_compensated(T& sum, T& lo
   lost = csub(csub(t, sum), y);
   sum = t;
 }
+__device__ __forceinline__ void add_compensated(double& sum, double& lost, double x) {
+  const double y = x - lost, t = sum + y;
+  lost = (t - sum) - y;
+  sum = t;
+}
 // a b with each real product rounded before its sum (no fused multiply-add). A pass that either loads
 // its input or forms it (the source) applies its first factor with this, so that both forms give the
 // same bits: a contraction may fuse either product of a sum, and the compiler chooses per call site.

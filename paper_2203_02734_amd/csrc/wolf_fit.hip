@@ -221,8 +221,8 @@ template hipError_t launch_fit_gradient<double2>(int, const double2*, const floa
 //   dL/dsg    = s pitch^2 / sg^3 sum_d Re( G[d] conj(D2[d]) ),  D2[d] = sum_{delta = d mod N} |delta|^2 mu_g(delta) C[delta].
 // N^4 / 2 and N^4 complex multiply-adds on N^2 operands in FP64, where the propagated array took three passes over N^4
 // elements each way. D and D2 obey X[-d] = conj(X[d]), so d_i runs over [0, N/2].
-// Bound: launches and LDS reads. One optimisation step in complex128: N = 64 0.74 -> 0.23 ms (63 us of it in these
-// kernels), N = 128 10.7 -> 0.35 ms (the sums 84 and 114 us).
+// Bound: launches and LDS reads. One optimisation step in complex128: N = 64 0.78 -> 0.23 ms (68 us of it in these
+// kernels), N = 128 10.8 -> 0.36 ms (245 us; the sums 84 and 114 us).
 // ---------------------------------------------------------------------------------------------
 constexpr int kFitThreads = 128;
 constexpr int kFitRows = 8;  // rows of one operand per workgroup
@@ -259,6 +259,8 @@ __device__ __forceinline__ void fit_roots(double2* w, int n) {
   }
 }
 
+// The two transforms and the sums over parts carry their roundings (add_compensated): they are the last chains before the results,
+// and plain ones left S_B 2.8e-16 to 4.4e-16 off in the 2-norm at N = 16 to 64, where the propagated array gave 1.1e-16 to 2.8e-16.
 __device__ __forceinline__ void cmac(double2& a, const double2& x, const double2& y) {
   a.x += x.x * y.x - x.y * y.y;
   a.y += x.x * y.y + x.y * y.x;
@@ -339,8 +341,8 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_corr(FitModel f, double2* _
       for (int k = 0; k < K; ++k) u[sub * n + dj0 + k] = which ? d2[k] : d1[k];
     __syncthreads();
     for (int j = threadIdx.x; j < n; j += kFitThreads) {
-      double2 a = u[j];
-      for (int q = 1; q < active; ++q) a = cadd(a, u[q * n + j]);
+      double2 a = u[j], lost{0.0, 0.0};
+      for (int q = 1; q < active; ++q) add_compensated(a, lost, u[q * n + j]);
       part[((long long)which * gridDim.y + blockIdx.y) * plane + (long long)di * n + j] = a;
     }
   }
@@ -357,9 +359,9 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_dft_rows(const double2* __r
   fit_roots(w, n);
   for (int j = threadIdx.x; j < 2 * n; j += kFitThreads) {
     const int which = j / n, jj = j % n;
-    double2 a{0.0, 0.0};
+    double2 a{0.0, 0.0}, lost{0.0, 0.0};
 #pragma unroll 8
-    for (int q = 0; q < chunks; ++q) a = cadd(a, part[((long long)which * chunks + q) * plane + at + jj]);
+    for (int q = 0; q < chunks; ++q) add_compensated(a, lost, part[((long long)which * chunks + q) * plane + at + jj]);
     if (which)
       corr[at + jj] = a;
     else
@@ -367,9 +369,9 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_dft_rows(const double2* __r
   }
   __syncthreads();
   for (int m = threadIdx.x; m < n; m += kFitThreads) {
-    double2 a{0.0, 0.0};
+    double2 a{0.0, 0.0}, lost{0.0, 0.0};
 #pragma unroll 4
-    for (int d = 0; d < n; ++d) cmac(a, w[((m - n / 2) * d) & (n - 1)], row[d]);
+    for (int d = 0; d < n; ++d) add_compensated(a, lost, cmul(w[((m - n / 2) * d) & (n - 1)], row[d]));
     e[at + m] = a;
   }
 }
@@ -383,11 +385,11 @@ __global__ __launch_bounds__(256) void k_fit_dft_s(const double2* __restrict__ e
   const int m = blockIdx.x * 256 + threadIdx.x;
   if (m >= n * n) return;
   const int mi = m / n, mj = m % n;
-  double a = 0.0;
+  double a = 0.0, lost = 0.0;
 #pragma unroll 8
   for (int d = 0; d <= n / 2; ++d) {
     const double2 x = fit_lds[((mi - n / 2) * d) & (n - 1)], y = e[(long long)d * n + mj];
-    a += (d == 0 || d == n / 2 ? 1.0 : 2.0) * (x.x * y.x - x.y * y.y);
+    add_compensated(a, lost, (d == 0 || d == n / 2 ? 1.0 : 2.0) * (x.x * y.x - x.y * y.y));
   }
   s[m] = scale * a;
 }
@@ -402,13 +404,9 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_g_rows(const double* __rest
   for (int j = threadIdx.x; j < n; j += kFitThreads) row[j] = g[(long long)blockIdx.x * n + j];
   __syncthreads();
   for (int d = threadIdx.x; d < n; d += kFitThreads) {
-    double2 t{0.0, 0.0};
+    double2 t{0.0, 0.0}, lost{0.0, 0.0};
 #pragma unroll 4
-    for (int m = 0; m < n; ++m) {
-      const double2 r = w[(-(m - n / 2) * d) & (n - 1)];
-      t.x += r.x * row[m];
-      t.y += r.y * row[m];
-    }
+    for (int m = 0; m < n; ++m) add_compensated(t, lost, cscale(w[(-(m - n / 2) * d) & (n - 1)], row[m]));
     a[(long long)blockIdx.x * n + d] = t;
   }
 }
@@ -421,9 +419,10 @@ __global__ __launch_bounds__(kFitThreads) void k_fit_g_cols(const double2* __res
   const int e = blockIdx.x * kFitThreads + threadIdx.x;
   if (e >= n * n) return;
   const int di = e / n, dj = e % n;
-  double2 t{0.0, 0.0};
+  double2 t{0.0, 0.0}, lost{0.0, 0.0};
 #pragma unroll 8
-  for (int m = 0; m < n; ++m) cmac(t, fit_lds[(-(m - n / 2) * di) & (n - 1)], a[(long long)m * n + dj]);
+  for (int m = 0; m < n; ++m)
+    add_compensated(t, lost, cmul(fit_lds[(-(m - n / 2) * di) & (n - 1)], a[(long long)m * n + dj]));
   gd[e] = t;
 }
 
@@ -493,11 +492,11 @@ __global__ __launch_bounds__(256) void k_fit_grad(FitModel f, const double* __re
   __shared__ double red[256];
   const int n = f.n, nn = n * n;
   if (blockIdx.x + 1 == gridDim.x) {
-    double a = 0.0;
+    double a = 0.0, lost = 0.0;
     for (int e = threadIdx.x; e < (n / 2 + 1) * n; e += 256) {
       const int di = e / n;
       const double2 x = gd[e], y = corr[e];
-      a += (di == 0 || di == n / 2 ? 1.0 : 2.0) * (x.x * y.x + x.y * y.y);
+      add_compensated(a, lost, (di == 0 || di == n / 2 ? 1.0 : 2.0) * (x.x * y.x + x.y * y.y));
     }
     red[threadIdx.x] = a;
     __syncthreads();
