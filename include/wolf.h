@@ -369,7 +369,7 @@ WOLF_API int64_t wolf_fit_work_bytes(int32_t n, int32_t dtype);
  *   imap     device N*N float32.   sigma_g_m > 0 (may be +inf).
  *   work     device scratch of wolf_fit_sums_work_bytes(n) bytes (overwritten).
  *   corr     device, 16 (N/2 + 1) N bytes, written: the sums that wolf_fit_backward needs for d_sigma.
- *   s_out    device, N*N float64.
+ *   s_out    device, N*N float64.   No two of the buffers may overlap.
  */
 WOLF_API wolf_status wolf_fit_forward(const float* imap, int32_t n, double pitch_m, double sigma_g_m,
                                       double wavelength_m, double z_m, int32_t farfield, void* work, void* corr,
@@ -379,7 +379,8 @@ WOLF_API wolf_status wolf_fit_forward(const float* imap, int32_t n, double pitch
  * wolf_fit_backward -- gradients of a loss of S_B with respect to the map and sigma_g, given g_s = dL/dS_B: what
  * wolf_propagate_adjoint_diag and wolf_fit_gradient give in WOLF_C128, without an N^4 array.
  *   g_s      device, N*N float64.   corr: as wolf_fit_forward wrote it for the same arguments.
- *   imap, d_imap, d_sigma   as wolf_fit_gradient.   work: wolf_fit_sums_work_bytes(n) bytes. N <= 128, sigma_g finite.
+ *   imap, d_imap, d_sigma   as wolf_fit_gradient.   work: wolf_fit_sums_work_bytes(n) bytes. No two of the buffers
+ *   may overlap. N <= 128, sigma_g finite.
  */
 WOLF_API wolf_status wolf_fit_backward(const double* g_s, const float* imap, int32_t n, double pitch_m,
                                        double sigma_g_m, double wavelength_m, double z_m, int32_t farfield,

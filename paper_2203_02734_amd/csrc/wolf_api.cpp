@@ -918,6 +918,22 @@ WOLF_API wolf_status wolf_fit_gradient(const void* ga, const float* imap, int32_
   return launched(e, who);
 }
 
+// One buffer of a call: its address, its bytes, its name.
+struct Buf {
+  const void* p;
+  size_t bytes;
+  const char* name;
+};
+
+// No two of a call's buffers share a byte.
+static wolf_status check_disjoint(const Buf* b, int count, const char* who) {
+  for (int i = 0; i < count; ++i)
+    for (int j = 0; j < i; ++j)
+      if (intervals_overlap(b[i].p, b[i].bytes, b[j].p, b[j].bytes))
+        return fail(WOLF_EINVAL, "%s: %s overlaps %s", who, b[i].name, b[j].name);
+  return WOLF_OK;
+}
+
 // Arguments shared by the two fit passes: validated, and the buffers both use checked.
 static wolf_status fit_args(const float* imap, int32_t n, double pitch_m, double sigma_g_m, double wavelength_m,
                             double z_m, int32_t farfield, const void* corr, const void* work, const char* who) {
@@ -939,6 +955,12 @@ WOLF_API wolf_status wolf_fit_forward(const float* imap, int32_t n, double pitch
   wolf_status s = fit_args(imap, n, pitch_m, sigma_g_m, wavelength_m, z_m, farfield, corr, work, who);
   if (s != WOLF_OK) return s;
   if ((s = check_buf(s_out, (size_t)n * n * 8, "s_out")) != WOLF_OK) return s;
+  const size_t nn = (size_t)n * n;
+  const Buf bufs[] = {{imap, 4 * nn, "imap"},
+                      {corr, 16 * (size_t)(n / 2 + 1) * n, "corr"},
+                      {work, wolf::fit_sums_work_bytes(n), "work"},
+                      {s_out, 8 * nn, "s_out"}};
+  if ((s = check_disjoint(bufs, 4, who)) != WOLF_OK) return s;
   const wolf::OperatorTables op = make_op(n, pitch_m, wavelength_m, z_m, farfield == 1, WOLF_SECONDARY, false);
   const double inv2g2_px = std::isinf(sigma_g_m) ? 0.0 : pitch_m * pitch_m / (2.0 * sigma_g_m * sigma_g_m);
   return launched(wolf::launch_fit_forward(n, imap, op.pre2.alpha, inv2g2_px, op.scale, work, (double2*)corr, s_out,
@@ -957,6 +979,14 @@ WOLF_API wolf_status wolf_fit_backward(const double* g_s, const float* imap, int
   if ((s = check_buf(g_s, (size_t)n * n * 8, "g_s")) != WOLF_OK) return s;
   if ((s = check_buf(d_imap, (size_t)n * n * 4, "d_imap")) != WOLF_OK) return s;
   if ((s = check_buf(d_sigma, 8, "d_sigma")) != WOLF_OK) return s;
+  const size_t nn = (size_t)n * n;
+  const Buf bufs[] = {{imap, 4 * nn, "imap"},
+                      {corr, 16 * (size_t)(n / 2 + 1) * n, "corr"},
+                      {work, wolf::fit_sums_work_bytes(n), "work"},
+                      {g_s, 8 * nn, "g_s"},
+                      {d_imap, 4 * nn, "d_imap"},
+                      {d_sigma, 8, "d_sigma"}};
+  if ((s = check_disjoint(bufs, 6, who)) != WOLF_OK) return s;
   const wolf::OperatorTables op = make_op(n, pitch_m, wavelength_m, z_m, farfield == 1, WOLF_SECONDARY, false);
   const double inv2g2_px = pitch_m * pitch_m / (2.0 * sigma_g_m * sigma_g_m);
   const double sg_scale = pitch_m * pitch_m / (sigma_g_m * sigma_g_m * sigma_g_m);

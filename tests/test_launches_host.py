@@ -1,0 +1,105 @@
+"""The built library against the host-only HIP stand-in (no GPU, no kernel runs): refusals before any launch, the status of
+every launch, and how many launches a call takes."""
+from __future__ import annotations
+
+import json
+import os
+import shutil
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+HOSTDIR = os.path.join(HERE, "host")
+CLANGXX = "/opt/rocm/llvm/bin/clang++"
+
+# Runs in a process of its own, with the stand-in's symbols ahead of the HIP runtime's.
+PRELUDE = """
+import ctypes, json, sys
+vp, i32, f64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_double
+lib, shim = ctypes.CDLL(sys.argv[1]), ctypes.CDLL(sys.argv[2])
+lib.wolf_fit_forward.argtypes = [vp, i32, f64, f64, f64, f64, i32, vp, vp, vp, vp]
+lib.wolf_fit_backward.argtypes = [vp, vp, i32, f64, f64, f64, f64, i32, vp, vp, vp, vp, vp]
+lib.wolf_fit_sums_work_bytes.restype = ctypes.c_int64
+lib.wolf_degree_of_coherence.argtypes = [vp, i32, i32, i32, i32, f64, vp, vp]
+lib.wolf_propagate_padded.argtypes = [vp, vp, i32, i32, f64, f64, f64, i32, i32, i32, vp, vp, vp]
+lib.wolf_last_error_message.restype = ctypes.c_char_p
+stub = ctypes.CDLL(sys.argv[3])
+stub.hipMalloc.argtypes = [ctypes.POINTER(vp), ctypes.c_size_t]
+def alloc(n):
+    p = vp()
+    assert stub.hipMalloc(ctypes.byref(p), n) == 0
+    return p.value
+def launches(f, fail_at=0):
+    shim.shim_reset(fail_at)
+    status = f()
+    return status, shim.shim_launches()
+out = {}
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    if not os.path.exists(CLANGXX):
+        pytest.skip("ROCm compilers not installed")
+    import paper_2203_02734_amd as wolf
+    if not os.path.exists(wolf.LIB_PATH):
+        from paper_2203_02734_amd import build
+        build.build()
+    d = tmp_path_factory.mktemp("stand_in")
+    libs = {}
+    for name in ("launch_shim", "hip_stub"):
+        libs[name] = str(d / f"lib{name}.so")
+        subprocess.run([CLANGXX, "-shared", "-fPIC", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", HOSTDIR,
+                        "-o", libs[name], os.path.join(HOSTDIR, name + ".cpp")], check=True)
+
+    def go(body):
+        code = PRELUDE + textwrap.dedent(body) + "\nprint(json.dumps(out))\n"
+        env = dict(os.environ, LD_PRELOAD=":".join([libs["launch_shim"], libs["hip_stub"]]))
+        r = subprocess.run([sys.executable, "-c", code, wolf.LIB_PATH, libs["launch_shim"], libs["hip_stub"]],
+                           capture_output=True, text=True, env=env, timeout=120)
+        assert r.returncode == 0, r.stderr[-2000:]
+        return json.loads(r.stdout)
+
+    return go
+
+
+FIT = """
+n, nn = 16, 256
+size = {"imap": 4 * nn, "corr": 16 * (n // 2 + 1) * n, "work": lib.wolf_fit_sums_work_bytes(n), "s": 8 * nn, "g": 8 * nn,
+        "d_imap": 4 * nn, "d_sigma": 8}
+def forward(b):
+    return lib.wolf_fit_forward(b["imap"], n, 1e-5, 1e-4, 6e-7, 0.3, 0, b["work"], b["corr"], b["s"], None)
+def backward(b):
+    return lib.wolf_fit_backward(b["g"], b["imap"], n, 1e-5, 1e-4, 6e-7, 0.3, 0, b["corr"], b["work"], b["d_imap"], b["d_sigma"],
+                                 None)
+calls = {"forward": (forward, ["imap", "work", "corr", "s"]),
+         "backward": (backward, ["g", "imap", "corr", "work", "d_imap", "d_sigma"])}
+"""
+
+
+def test_fit_refuses_overlapping_buffers(run):
+    """Each pair of buffers of a call, sharing their first or their last bytes, and side by side in one allocation."""
+    out = run(FIT + textwrap.dedent("""
+        for name, (call, used) in calls.items():
+            free = {k: alloc(size[k]) for k in used}
+            out[name + " apart"] = launches(lambda: call(free))
+            for i, x in enumerate(used):
+                for y in used[:i]:
+                    for how in ("first", "last", "beside"):
+                        a, b = max(size[x], size[y]), min(size[x], size[y])
+                        base = alloc(a + b)
+                        big, small = (x, y) if size[x] >= size[y] else (y, x)
+                        bufs = dict(free)
+                        bufs[big] = base
+                        bufs[small] = base + {"first": 0, "last": a - b, "beside": a}[how]
+                        out["%s %s %s %s" % (name, x, y, how)] = launches(lambda: call(bufs))
+    """))
+    for what, (status, count) in out.items():
+        if what.endswith(("apart", "beside")):
+            assert status == 0 and count in (3, 4), what
+        else:
+            assert status == -1 and count == 0, what
