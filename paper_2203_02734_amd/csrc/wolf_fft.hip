@@ -821,6 +821,8 @@ static hipError_t launch_first_point_s_n(T* w, typename real_of<T>::type* s, con
   constexpr int tiles = N * N / C;
   hipLaunchKernelGGL((k_axis_fft_s<T, N, C, SIGN, false>), dim3((unsigned)(tiles * N)), dim3(Split<N>::N2 * C), 0, st, w,
                      s, pre, post_j);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_axis_fft_s<T, N, C, SIGN, true>), dim3((unsigned)tiles), dim3(Split<N>::N2 * C), 0, st, w, s, pre,
                      post_i);
   return hipGetLastError();

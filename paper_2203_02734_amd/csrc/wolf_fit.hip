@@ -539,8 +539,11 @@ hipError_t launch_fit_forward(int n, const float* imap, double alpha, double inv
     hipLaunchKernelGGL(k_fit_corr<4>, grid, dim3(kFitThreads), lds, st, f, part);
   else
     hipLaunchKernelGGL(k_fit_corr<1>, grid, dim3(kFitThreads), lds, st, f, part);
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
   hipLaunchKernelGGL(k_fit_dft_rows, dim3((unsigned)half), dim3(kFitThreads), 2 * n * sizeof(double2), st, part, n,
                      chunks, e, corr);
+  if ((err = hipGetLastError()) != hipSuccess) return err;
   hipLaunchKernelGGL(k_fit_dft_s, dim3((unsigned)((n * n + 255) / 256)), dim3(256), n * sizeof(double2), st, e, n,
                      scale, s);
   return hipGetLastError();
@@ -557,14 +560,18 @@ hipError_t launch_fit_backward(int n, const double* g_s, const float* imap, doub
   double* part = reinterpret_cast<double*>(gd + nn);
   hipLaunchKernelGGL(k_fit_g_rows, dim3((unsigned)n), dim3(kFitThreads), n * (sizeof(double2) + sizeof(double)), st,
                      g_s, n, a);
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
   hipLaunchKernelGGL(k_fit_g_cols, dim3((unsigned)((nn + kFitThreads - 1) / kFitThreads)), dim3(kFitThreads),
                      n * sizeof(double2), st, a, n, gd);
+  if ((err = hipGetLastError()) != hipSuccess) return err;
   const size_t lds = (size_t)(3 * rows * n + n) * sizeof(double2) + (size_t)(n + 1) * sizeof(double);
   const dim3 grid((unsigned)n, (unsigned)chunks);
   if (fit_outputs(n) == 4)
     hipLaunchKernelGGL(k_fit_conv<4>, grid, dim3(kFitThreads), lds, st, f, gd, part);
   else
     hipLaunchKernelGGL(k_fit_conv<1>, grid, dim3(kFitThreads), lds, st, f, gd, part);
+  if ((err = hipGetLastError()) != hipSuccess) return err;
   hipLaunchKernelGGL(k_fit_grad, dim3((unsigned)((nn + 255) / 256 + 1)), dim3(256), 0, st, f, part, chunks, gd, corr,
                      sg_scale, d_imap, d_sigma);
   return hipGetLastError();

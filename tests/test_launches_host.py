@@ -103,3 +103,20 @@ def test_fit_refuses_overlapping_buffers(run):
             assert status == 0 and count in (3, 4), what
         else:
             assert status == -1 and count == 0, what
+
+
+def test_every_failed_launch_is_reported(run):
+    """The difference sums of the fit, and S alone of a propagated source."""
+    out = run(FIT + textwrap.dedent("""
+        lib.wolf_propagate_density.argtypes = [vp, i32, f64, f64, f64, i32, i32, i32, vp, vp]
+        size["w"] = 8 * nn * nn
+        calls["density"] = (lambda b: lib.wolf_propagate_density(b["w"], n, 1e-5, 6e-7, 0.3, 0, 0, 0, b["s"], None), ["w", "s"])
+        for name, (call, used) in calls.items():
+            bufs = {k: alloc(size[k]) for k in used}
+            count = launches(lambda: call(bufs))[1]
+            out[name] = [launches(lambda: call(bufs), k + 1) for k in range(count)]
+    """))
+    assert [len(out[k]) for k in ("forward", "backward", "density")] == [3, 4, 3]
+    for name, seen in out.items():
+        for k, (status, count) in enumerate(seen):
+            assert status == -4 and count == k + 1, (name, k)  # and nothing is launched after the failure
