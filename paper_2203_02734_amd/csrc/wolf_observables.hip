@@ -86,55 +86,38 @@ __global__ __launch_bounds__(256) void k_mu_slice(const T* __restrict__ w, int n
   mu[m] = out;
 }
 
-// The same slice in one launch for N <= 64, where a call is bound by its launches: one workgroup gathers S, takes its
-// maximum and divides the row (the same operations on the same values, so the same bits). N = 16: three launches cost the
-// host 7.5 us more than one; at N = 128 one workgroup's gather (16384 lines) would take longer than three launches.
-constexpr int kMuOneThreads = 1024, kMuOneMaxN = 64;
+// The same slice in one launch for N <= 32: one workgroup gathers S, takes its maximum and divides the row (the same operations
+// on the same values, so the same bits). A call costs the host 6.1 us instead of 13.5. On the device, between kernels that turn
+// the caches over, three launches and one take 6.7 and 3.6 us at N = 16, 7.2 and 5.3 at N = 32, but 7.7 and 8.9 at N = 48
+// and 7.8 and 12.8 at N = 64 (complex64; complex128 alike), where one workgroup's gather of N^2 lines is the longer: from N = 34 on
+// a full stream would wait for it.
+constexpr int kMuOneThreads = 1024, kMuOneMaxN = 32;
 template <class T>
 __global__ __launch_bounds__(kMuOneThreads) void k_mu_slice_one(const T* __restrict__ w, int n, int p1, double floor_rel,
                                                                 T* __restrict__ mu) {
   using R = typename real_of<T>::type;
-  constexpr int V = kMuOneMaxN * kMuOneMaxN / kMuOneThreads;
+  static_assert(kMuOneMaxN * kMuOneMaxN <= kMuOneThreads, "one point per thread");
   __shared__ unsigned long long red[kMuOneThreads];
   __shared__ R s_p1;
-  const int nn = n * n, tid = threadIdx.x;
-  const long long step = nn + 1;
-  R s2[V];
-  T v[V];
-  unsigned long long k = 0ull;
-#pragma unroll
-  for (int i = 0; i < V; ++i) {
-    const int m = tid + i * kMuOneThreads;
-    s2[i] = load_or_first(w, m < nn, m * step).x;
-    v[i] = load_or_first(w, m < nn, (long long)p1 * nn + m);
-  }
-#pragma unroll
-  for (int i = 0; i < V; ++i) {
-    const int m = tid + i * kMuOneThreads;
-    if (m >= nn) continue;
-    const unsigned long long q = order_key((double)s2[i]);
-    k = q > k ? q : k;
-    if (m == p1) s_p1 = s2[i];
-  }
-  red[tid] = k;
+  const int nn = n * n, m = threadIdx.x;
+  const R s2 = load_or_first(w, m < nn, (long long)m * (nn + 1)).x;
+  const T v = load_or_first(w, m < nn, (long long)p1 * nn + m);
+  red[m] = m < nn ? order_key((double)s2) : 0ull;
+  if (m == p1) s_p1 = s2;
   __syncthreads();
   for (int h = kMuOneThreads / 2; h > 0; h >>= 1) {
-    if (tid < h && red[tid + h] > red[tid]) red[tid] = red[tid + h];
+    if (m < h && red[m + h] > red[m]) red[m] = red[m + h];
     __syncthreads();
   }
+  if (m >= nn) return;
   const R tau = (R)(floor_rel * key_value(red[0]));
   const R s1 = s_p1;
-#pragma unroll
-  for (int i = 0; i < V; ++i) {
-    const int m = tid + i * kMuOneThreads;
-    if (m >= nn) continue;
-    T out{(R)0, (R)0};
-    if (s1 > tau && s2[i] > tau) {
-      const R d = sqrt(s1) * sqrt(s2[i]);
-      out = T{v[i].x / d, v[i].y / d};
-    }
-    mu[m] = out;
+  T out{(R)0, (R)0};
+  if (s1 > tau && s2 > tau) {
+    const R d = sqrt(s1) * sqrt(s2);
+    out = T{v.x / d, v.y / d};
   }
+  mu[m] = out;
 }
 
 template <class T>

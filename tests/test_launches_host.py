@@ -120,3 +120,15 @@ def test_every_failed_launch_is_reported(run):
     for name, seen in out.items():
         for k, (status, count) in enumerate(seen):
             assert status == -4 and count == k + 1, (name, k)  # and nothing is launched after the failure
+
+
+def test_mu_slice_in_one_launch_up_to_32(run):
+    """Above, one workgroup's gather of N^2 lines takes longer than three launches."""
+    out = run("""
+        w, mu = alloc(16 * 66 ** 4), alloc(16 * 66 ** 2)
+        for dtype in (0, 1):
+            for n in (2, 16, 30, 32, 34, 48, 64, 66):
+                out["%d %d" % (dtype, n)] = launches(lambda: lib.wolf_degree_of_coherence(w, n, dtype, 1, 1, 1e-3, mu, None))
+    """)
+    for what, (status, count) in out.items():
+        assert status == 0 and count == (1 if int(what.split()[1]) <= 32 else 3), what
