@@ -199,7 +199,9 @@ __global__ __launch_bounds__(256) void k_rs_fold(const T* in, T* out, T* extra, 
 // Bound: the matrix cores. N = 64: 1.13 and 1.24 ms in complex64 (97 and 91 TFLOP/s executed of 154), 2.04 and 2.28 ms in
 // complex128 (54 and 50 of 72); the plain products took 4.2 and 10.7 ms each. Stores of the operands that run along kk
 // are swizzled over the LDS banks (before: 3.45 and 3.18 ms in complex128).
-template <class T, bool FIRST>
+// !MIRRORED (N < 16): one class whose slots are its indices; a launch is one tile and a chain of at most four steps, which the
+// walk of the slots would lengthen (a call at N = 8: 23.8 us with it, 18.8 without in complex64, 30.3 and 24.4 in complex128).
+template <class T, bool FIRST, bool MIRRORED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 2))) void k_rs_gemm(
     const T* __restrict__ x, const T* __restrict__ h, T* __restrict__ y, T* __restrict__ extra, RsClasses cs,
     int panels, int per_xcd, double alpha) {
@@ -217,9 +219,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
   const int width = panels - first < per_xcd ? panels - first : per_xcd;
   const int panel = first + in_group % width, tile = in_group / width;
   RsClass cl = cs.c[0];
+  if constexpr (MIRRORED) {
 #pragma unroll
-  for (int q = 1; q < 4; ++q)
-    if (q < cs.count && tile >= cs.c[q].tile) cl = cs.c[q];
+    for (int q = 1; q < 4; ++q)
+      if (tile >= cs.c[q].tile) cl = cs.c[q];
+  }
   const int n = cs.n, nn = n * n, kk_n = cl.la * cl.lb, vs = cs.slots, vv = vs * vs;
   const int o0 = (tile - cl.tile) * 64, p0 = panel * 64;  // first output of the class, first line of the panel
   const int p_n = FIRST ? nn : vv;
@@ -232,11 +236,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
   // (kk e / 64, column e % 64), 64 consecutive columns. (mi, mj) of this thread's kk advance with the steps.
   constexpr int NI = FIRST ? 1 : 4;
   int mi[NI], mj[NI];
+  if constexpr (MIRRORED) {
 #pragma unroll
-  for (int q = 0; q < NI; ++q) {
-    const int kk = FIRST ? tid % TK : wv + 4 * q;
-    mi[q] = kk / cl.lb;
-    mj[q] = kk - mi[q] * cl.lb;
+    for (int q = 0; q < NI; ++q) {
+      const int kk = FIRST ? tid % TK : wv + 4 * q;
+      mi[q] = kk / cl.lb;
+      mj[q] = kk - mi[q] * cl.lb;
+    }
   }
   T rh[4], rx[4];
   auto fetch = [&](int k0) {  // called for k0 = 0, 16, 32, ... in turn
@@ -247,7 +253,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
       rh[q] = load_or_first(hm, o < kk_n && kh < kk_n, (long long)o * kk_n + kh);
     }
     if constexpr (FIRST) {
-      const int s = kh < kk_n ? slot(mi[0], mj[0]) : 0;
+      const int s = kh >= kk_n ? 0 : MIRRORED ? slot(mi[0], mj[0]) : kh;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int p = p0 + tid / TK + 16 * q;
@@ -257,16 +263,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
       const int v = p0 + lane;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int s = k0 + wv + 4 * q < kk_n ? slot(mi[q], mj[q]) : 0;
+        const int kx = k0 + wv + 4 * q, s = kx >= kk_n ? 0 : MIRRORED ? slot(mi[q], mj[q]) : kx;
         rx[q] = load_or_first(x, v < p_n, (long long)s * vv + v);
       }
     }
+    if constexpr (MIRRORED) {
 #pragma unroll
-    for (int q = 0; q < NI; ++q) {
-      mj[q] += TK;
-      while (mj[q] >= cl.lb) {
-        mj[q] -= cl.lb;
-        ++mi[q];
+      for (int q = 0; q < NI; ++q) {
+        mj[q] += TK;
+        while (mj[q] >= cl.lb) {
+          mj[q] -= cl.lb;
+          ++mi[q];
+        }
       }
     }
   };
@@ -316,6 +324,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
         const T v{(R)(alpha * acc.re(r, q, i)), (R)(alpha * acc.im(r, q, i))};
         const int o = o0 + (FIRST ? gj : gi), p = p0 + (FIRST ? gi : gj);
         if (o < kk_n && p < p_n) {
+          if constexpr (!MIRRORED) {
+            y[FIRST ? (long long)p * nn + o : (long long)o * nn + p] = v;
+            continue;
+          }
           const int oi = o / cl.lb, oj = o - oi * cl.lb;
           if constexpr (FIRST) {
             y[(long long)p * vv + (cl.sa + oi) * vs + cl.sb + oj] = v;
@@ -327,12 +339,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
       }
 }
 
-template <class T, bool FIRST>
+template <class T, bool FIRST, bool MIRRORED>
 static hipError_t launch_rs_gemm(const T* x, const T* h, T* y, T* extra, const RsClasses& cs, double alpha,
                                  hipStream_t st) {
   const int lines = FIRST ? cs.n * cs.n : cs.slots * cs.slots;
   const int panels = (lines + 63) / 64, per_xcd = (panels + 7) / 8;
-  hipLaunchKernelGGL((k_rs_gemm<T, FIRST>), dim3((unsigned)(8 * ((panels * cs.tiles + 7) / 8))), dim3(256), 0, st, x, h, y, extra,
+  hipLaunchKernelGGL((k_rs_gemm<T, FIRST, MIRRORED>), dim3((unsigned)(8 * ((panels * cs.tiles + 7) / 8))), dim3(256), 0, st, x, h, y, extra,
                      cs, panels, per_xcd, alpha);
   return hipGetLastError();
 }
@@ -360,8 +372,8 @@ hipError_t launch_direct(int n, const T* in, T* out, void* work, double pitch, d
     hipLaunchKernelGGL(k_rs_kernel<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, h, n, pitch, dx, z, lam,
                        primary);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = launch_rs_gemm<T, true>(in, h, t1, (T*)nullptr, cs, 1.0, st)) != hipSuccess) return e;
-    return launch_rs_gemm<T, false>(t1, h, out, (T*)nullptr, cs, s, st);
+    if ((e = launch_rs_gemm<T, true, false>(in, h, t1, (T*)nullptr, cs, 1.0, st)) != hipSuccess) return e;
+    return launch_rs_gemm<T, false, false>(t1, h, out, (T*)nullptr, cs, s, st);
   }
   const int c = n / 2, w = c + 1;
   const long long m = (long long)w * w + (long long)c * c;
@@ -373,8 +385,8 @@ hipError_t launch_direct(int n, const T* in, T* out, void* work, double pitch, d
   const dim3 orbits((unsigned)(((long long)w * w * w * w + 255) / 256));
   hipLaunchKernelGGL((k_rs_fold<T, false>), orbits, dim3(256), 0, st, in, out, extra, n);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = launch_rs_gemm<T, true>(out, h, t1, extra, cs, 1.0, st)) != hipSuccess) return e;
-  if ((e = launch_rs_gemm<T, false>(t1, h, out, extra, cs, s, st)) != hipSuccess) return e;
+  if ((e = launch_rs_gemm<T, true, true>(out, h, t1, extra, cs, 1.0, st)) != hipSuccess) return e;
+  if ((e = launch_rs_gemm<T, false, true>(t1, h, out, extra, cs, s, st)) != hipSuccess) return e;
   hipLaunchKernelGGL((k_rs_fold<T, true>), orbits, dim3(256), 0, st, (const T*)out, out, extra, n);
   return hipGetLastError();
 }
