@@ -1569,19 +1569,21 @@ __global__ __launch_bounds__(kOneThreads) void k_one_poly_sums(const T* __restri
 // Both indices are centred, so outputs c +- t share their sums and mirrored inputs meet first, with real factors:
 //   E(t) = sum_q cos(2 pi beta t q) (x[q] + x[-q]),  O(t) = sum_q sin(2 pi beta t q) (x[q] - x[-q]),  out(+-t) = E +- SIGN i O,
 // q = 1 .. off - 1 beside x[0] and x[-off], which have no mirror. The factors come from an FP64 recurrence in q: four
-// multiply-adds for them and four for the sums, for two inputs and two outputs (32 without the mirror). A row takes
-// min(c, 64) threads of one wavefront, a thread the outputs +-t; t = 0 is a sum of the row's entries, by butterfly.
+// multiply-adds for them and four for the sums, for two inputs and two outputs (32 without the mirror). A thread takes the
+// outputs +-t. Below N = 128 a row has c + 1 threads, t = 0 .. c; above, where one more would not fit a wavefront, 64 of one
+// wavefront, and t = 0 is a sum of the row's entries, by butterfly.
 // Bound: FP64 FMA and the LDS reads of the two combinations. N = 128, 16 pairs: 2 x 57.6 + 2 x 21.2 us -> 2 x 17.0 +
 // 2 x 9.3 (the 16-wavelength sum 1061 -> 968 us).
+__host__ __device__ __forceinline__ int czt_threads(int n) { return n / 2 < 64 ? n / 2 + 1 : 64; }
 template <class T, int SIGN>
 __global__ __launch_bounds__(256) void k_poly_czt(const T* __restrict__ in, int n, int rows, int off, int total,
                                                   PolyGroup g, T* __restrict__ out) {
   using R = typename real_of<T>::type;
   __shared__ double2 se[1024], so[1024];  // rows of a workgroup x off: 512 up to N = 128, 4 x 256 at N = 256
-  const int c = n / 2, per = c < 64 ? c : 64;
+  const int c = n / 2, per = czt_threads(n);
   const int r = threadIdx.x / per, lane = threadIdx.x % per;
   const int gi = blockIdx.x * (256 / per) + r;
-  const bool ok = gi < total;
+  const bool ok = gi < total && r < 256 / per;  // the threads past the last whole row have none
   const T* x = in + (ok ? (long long)gi * 2 * off : 0);
   double2* e = se + r * off;  // e[0] = x[0], o[0] = x[-off]
   double2* o = so + r * off;
@@ -1597,12 +1599,14 @@ __global__ __launch_bounds__(256) void k_poly_czt(const T* __restrict__ in, int 
   if (!ok) return;
   const int k = gi / rows, i = gi % rows;
   T* col = out + (long long)k * n * rows + i;
-  double2 z = lane == 0 ? o[0] : double2{0.0, 0.0};
-  for (int q = lane; q < off; q += per) z = cadd(z, e[q]);
-  for (int h = per / 2; h > 0; h >>= 1) z = cadd(z, double2{__shfl_xor(z.x, h), __shfl_xor(z.y, h)});
-  if (lane == 0) col[(long long)c * rows] = T{(R)z.x, (R)z.y};
+  if (c >= 64) {
+    double2 z = lane == 0 ? o[0] : double2{0.0, 0.0};
+    for (int q = lane; q < off; q += per) z = cadd(z, e[q]);
+    for (int h = per / 2; h > 0; h >>= 1) z = cadd(z, double2{__shfl_xor(z.x, h), __shfl_xor(z.y, h)});
+    if (lane == 0) col[(long long)c * rows] = T{(R)z.x, (R)z.y};
+  }
   const double beta = g.beta[k];
-  for (int t = lane + 1; t <= c; t += per) {
+  for (int t = c >= 64 ? lane + 1 : lane; t <= c; t += per) {
     double fs = beta * (double)t;
     fs -= rint(fs);
     double2 rot;
@@ -1624,13 +1628,13 @@ __global__ __launch_bounds__(256) void k_poly_czt(const T* __restrict__ in, int 
     od.y -= w.y * l.y;
     const double sg = (double)SIGN;
     col[(long long)(c - t) * rows] = T{(R)(ev.x + sg * od.y), (R)(ev.y - sg * od.x)};
-    if (t < c) col[(long long)(c + t) * rows] = T{(R)(ev.x - sg * od.y), (R)(ev.y + sg * od.x)};
+    if (t > 0 && t < c) col[(long long)(c + t) * rows] = T{(R)(ev.x - sg * od.y), (R)(ev.y + sg * od.x)};
   }
 }
 
 template <class T, int SIGN>
 static void launch_poly_czt(const T* in, int n, int rows, int off, const PolyGroup& g, T* out, hipStream_t st) {
-  const int per = n / 2 < 64 ? n / 2 : 64, rb = 256 / per, total = g.count * rows;
+  const int rb = 256 / czt_threads(n), total = g.count * rows;
   hipLaunchKernelGGL((k_poly_czt<T, SIGN>), dim3((unsigned)((total + rb - 1) / rb)), dim3(256), 0, st, in, n, rows, off,
                      total, g, out);
 }
