@@ -329,8 +329,10 @@ wolf_status run_operator(const T* in, T* out, int32_t n, int32_t dtype, const wo
     const wolf_status s = stream_scratch(st, &scratch);
     if (s != WOLF_OK) return s;
   }
-  hipError_t e = wolf::launch_operator<T>(n, in, out, op, plan, scratch, st, nullptr, plan.coop ? nullptr : s_out);
-  if (e == hipSuccess && s_out && plan.coop) e = wolf::launch_spectral_density<T>(n, out, s_out, st);
+  // S alone where its passes give the full ones' bits; else the whole array and its diagonal.
+  const bool s_alone = s_out && !plan.coop && wolf::density_pass_supported(n);
+  hipError_t e = wolf::launch_operator<T>(n, in, out, op, plan, scratch, st, nullptr, s_alone ? s_out : nullptr);
+  if (e == hipSuccess && s_out && !s_alone) e = wolf::launch_spectral_density<T>(n, out, s_out, st);
   if (e != hipSuccess) return fail(WOLF_EDEVICE, "propagation launch: %s", hipGetErrorString(e));
   g_last_error.clear();
   return WOLF_OK;

@@ -107,9 +107,12 @@ template <class T> __device__ __forceinline__ T cmul_fixed(T a, T b) {
 
 // The first-point passes when only S = Re diag W is wanted, over the array as the second-point passes left it. The j1 pass
 // (LAST = false) keeps of each transformed line the entry j1 = j2, in its place; the i1 pass reads those N^3 entries and
-// keeps i1 = i2: s[m2]. The sums are k_axis_fft's with the same bits (the fused products of the post-factor written out).
+// keeps i1 = i2: s[m2]. The sums are k_axis_fft's with the same bits (the fused products of the post-factor written out) up to
+// N = 128; at N = 256 the compiler fuses other products in k_axis_fft, a fifth of the points differ in the last bit, and S comes
+// from the whole array.
 // Bound: the one read of the array; the full passes read and write it twice. The complex64 fit step at N = 64:
 // 340 -> 286 us.
+constexpr int kDensityMaxN = 128;
 template <class T, int N, int C, int SIGN, bool LAST>
 __global__ __launch_bounds__(Split<N>::N2 * C) void k_axis_fft_s(T* w, typename real_of<T>::type* s, Chirp pre,
                                                                 Chirp post) {
@@ -817,6 +820,7 @@ static bool make_job(const AxisRange& ar, const Chirp& pre, const Chirp& post, A
 template <class T, int N, int SIGN>
 static hipError_t launch_first_point_s_n(T* w, typename real_of<T>::type* s, const Chirp& pre, const Chirp& post_j,
                                          const Chirp& post_i, hipStream_t st) {
+  if constexpr (N > kDensityMaxN) return hipErrorInvalidValue;
   constexpr int C = axis_cols<T, N>();
   constexpr int tiles = N * N / C;
   hipLaunchKernelGGL((k_axis_fft_s<T, N, C, SIGN, false>), dim3((unsigned)(tiles * N)), dim3(Split<N>::N2 * C), 0, st, w,
@@ -1171,6 +1175,8 @@ hipError_t launch_operator(int n, const T* in, T* out, const OperatorTables& op,
   }
   return hipSuccess;
 }
+
+bool density_pass_supported(int n) { return n <= kDensityMaxN; }
 
 // ---------------------------------------------------------------------------------------------
 // Operator applied to a diagonal input diag(g) (e.g. the gradient of a loss of S = Re diag W).

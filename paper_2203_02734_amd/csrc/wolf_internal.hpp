@@ -64,7 +64,8 @@ struct SourceParams;
 // `counters`: per-stream device scratch of at least coop_counter_bytes(n) (used when plan.coop).
 // `gen` (plan.fused_slab == 3, or 0 at N >= 64 with no input pupil): the input is the source
 // described by *gen, formed inside the first pass; `in` is not read.
-// `s_out` (no plan.coop): only S = Re diag of the result is wanted, N^2; `out` is then scratch.
+// `s_out` (no plan.coop, density_pass_supported): only S = Re diag of the result is wanted, N^2; `out` is then scratch.
+bool density_pass_supported(int n);
 template <class T>
 hipError_t launch_operator(int n, const T* in, T* out, const OperatorTables& op, const Plan& plan, void* counters,
                            hipStream_t st, const SourceParams* gen = nullptr,
