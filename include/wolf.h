@@ -201,8 +201,8 @@ WOLF_API int64_t wolf_direct_work_bytes(int32_t n, int32_t dtype);
  * e^{-+2 pi i (k - N/2)(n - N/2) / n_fft}, halved by its mirror symmetry (8 N real flops per element).
  *   n          even, 2..256.   n_fft   N..2048.
  *   w_in, w_out   device N^4 complex; w_in == w_out allowed (partial overlap is not).
- *   work       device N^4 complex of `dtype`, its contents undefined after the call; must not
- *              overlap w_in or w_out.
+ *   work       not used, may be NULL: every pass works in place on w_out. A buffer that is given must be
+ *              device N^4 complex of `dtype` that does not overlap w_in or w_out.
  *   farfield   0 Fresnel, 1 far field.   kind, dtype, out_pitch_m as wolf_propagate_fresnel.
  * The source builder and the observables accept any even N as well.
  */

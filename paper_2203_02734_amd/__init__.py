@@ -334,15 +334,14 @@ def propagate_padded(w: torch.Tensor, pitch: float, wavelength: float, z: float,
                      farfield: bool = False, kind: int = SECONDARY, out: Optional[torch.Tensor] = None,
                      work: Optional[torch.Tensor] = None) -> Tuple[torch.Tensor, float]:
     """Propagation for any even N, with zero padding of the transform to n_fft points and the result
-    cropped back to N (Sec. 3.3; n_fft = N by default). Returns (W_B, dx), dx = lambda z / (n_fft pitch)."""
+    cropped back to N (Sec. 3.3; n_fft = N by default). Returns (W_B, dx), dx = lambda z / (n_fft pitch).
+    `work` is checked if it is given and not used: every pass works in place on the result."""
     lib = load()
     n = _csd(w, "w")
     if out is None:
         out = torch.empty_like(w)
     else:
         _out(out, w.shape, w.dtype, w.device)
-    if work is None:
-        work = torch.empty_like(w)
     dx = ctypes.c_double(0.0)
     _check(lib.wolf_propagate_padded(_ptr(w), _ptr(out), n, n if n_fft is None else int(n_fft), pitch, wavelength, z,
                                      int(bool(farfield)), kind, _code(w.dtype), _ptr(work), ctypes.byref(dx),

@@ -572,9 +572,10 @@ WOLF_API wolf_status wolf_propagate_padded(const void* w_in, void* w_out, int32_
   wolf_status s;
   if ((s = check_buf(w_in, bytes, "w_in")) != WOLF_OK) return s;
   if ((s = check_buf(w_out, bytes, "w_out")) != WOLF_OK) return s;
-  if ((s = check_buf(work, bytes, "work")) != WOLF_OK) return s;
-  if (partial_overlap(w_in, w_out, bytes) || intervals_overlap(work, bytes, w_in, bytes) ||
-      intervals_overlap(work, bytes, w_out, bytes))
+  // No pass uses `work`; one that is given is checked as ever.
+  if (work != nullptr && (s = check_buf(work, bytes, "work")) != WOLF_OK) return s;
+  if (partial_overlap(w_in, w_out, bytes) ||
+      (work != nullptr && (intervals_overlap(work, bytes, w_in, bytes) || intervals_overlap(work, bytes, w_out, bytes))))
     return fail(WOLF_EINVAL, "%s: buffers overlap", who);
   // Chirps on the N-point grids, output pitch lambda z / (n_fft pitch).
   const double dx = wavelength_m * z_m / ((double)n_fft * pitch_m);

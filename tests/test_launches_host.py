@@ -132,3 +132,24 @@ def test_mu_slice_in_one_launch_up_to_32(run):
     """)
     for what, (status, count) in out.items():
         assert status == 0 and count == (1 if int(what.split()[1]) <= 32 else 3), what
+
+
+def test_padded_needs_no_work_buffer(run):
+    """Four passes in place on the output, for lengths with an FFT split and without; a buffer that is given is still checked."""
+    out = run("""
+        n = 12
+        size = 16 * n ** 4
+        w, o, k = alloc(size), alloc(size), alloc(size)
+        def call(w_in, w_out, work, nz, dtype):
+            return launches(lambda: lib.wolf_propagate_padded(w_in, w_out, n, nz, 1e-5, 6e-7, 0.3, 0, 0, dtype, work, None, None))
+        for dtype in (0, 1):
+            for nz in (12, 13, 24, 30):
+                out["%d %d none" % (dtype, nz)] = call(w, o, None, nz, dtype)
+                out["%d %d none in place" % (dtype, nz)] = call(w, w, None, nz, dtype)
+                out["%d %d given" % (dtype, nz)] = call(w, o, k, nz, dtype)
+                out["%d %d input: refused" % (dtype, nz)] = call(w, o, w, nz, dtype)
+                out["%d %d output: refused" % (dtype, nz)] = call(w, o, o, nz, dtype)
+                out["%d %d small: refused" % (dtype, nz)] = call(w, o, k + size - 64, nz, dtype)
+    """)
+    for what, (status, count) in out.items():
+        assert (status, count) == ((-1, 0) if "refused" in what else (0, 4)), what
