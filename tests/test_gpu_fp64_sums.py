@@ -56,8 +56,8 @@ def test_batch_s_of_a_beam(gpu_lib, n, k, probe):
     assert np.sqrt(np.mean(sq)) < 1.1 * FORMER
 
 
-def fit_reference(b, inv, scale):
-    """S_B = scale sum_d e^{2 pi i <m - c, d> / N} D[d] from the differences of b, in long double."""
+def fit_reference(b, inv, scale, moment=0):
+    """scale sum_d e^{2 pi i <m - c, d> / N} D[d] from the differences of b, in long double: S_B. moment = 2: with |d|^2 D[d]."""
     n = b.shape[0]
     dd = np.zeros((n, n), CL)
     for di in range(n):
@@ -66,6 +66,8 @@ def fit_reference(b, inv, scale):
                 continue
             j0, j1 = max(0, dj), min(n, n + dj)
             c = (b[di:, j0:j1].conj() * b[:n - di, j0 - dj:j1 - dj]).sum() * np.exp(-L(di * di + dj * dj) * L(inv))
+            if moment:
+                c *= di * di + dj * dj
             dd[di % n, dj % n] += c
             if di or dj:
                 dd[-di % n, -dj % n] += c.conj()
@@ -98,3 +100,31 @@ def test_fit_s(gpu_lib, n, seeds, farfield):
                             1.0 / ((lam * z) * (lam * z)) * P * P * P * P)
         sq.append(float(((s.cpu().numpy().astype(L) - ref) ** 2).sum() / (ref ** 2).sum()))
     assert np.sqrt(np.mean(sq)) < 1.1 * FORMER_FIT
+
+
+@pytest.mark.parametrize("farfield", [False, True])
+@pytest.mark.parametrize("n", [16, 32])
+def test_fit_dsigma(gpu_lib, n, farfield):
+    """dL/dsg = f sum_m g[m] T[m], T the transform of |d|^2 D[d], with random g. The library takes it as f sum_d Re G conj(D2):
+    G carries 2 u of its root mean square from two transforms, D2 4 u from table, product, weight and sums, the final sum u, against
+    the sum of the sizes |G D2|: 8 u of it."""
+    r = np.random.default_rng(n)
+    sg, z, lam = 0.1 * P * n / 2, 0.5, LAM
+    x = np.arange(n) - n / 2
+    a = np.round((0.2 + np.exp(-(x[:, None] ** 2 + x[None, :] ** 2) / (n / 2) ** 2)) * np.exp(
+        0.2 * r.standard_normal((n, n))) * 2 ** 11) / 2 ** 11
+    g = np.round(64 * r.standard_normal((n, n))) / 64
+    imap = torch.from_numpy((a * a).astype(np.float32)).cuda()
+    gs = torch.from_numpy(g).cuda()
+    s, corr = gpu_lib.fit_forward(imap, P, sg, lam, z, farfield)
+    _, ds = gpu_lib.fit_backward(gs, imap, corr, P, sg, lam, z, farfield)
+    d = np.arange(n) - n // 2
+    t = cis((d * d).astype(L) * L(0.0 if farfield else P * P / (lam * z)) / 2)
+    scale = 1.0 / ((lam * z) * (lam * z)) * P * P * P * P
+    tm = fit_reference(a.astype(L) * t[:, None] * t[None, :], P * P / (2.0 * sg * sg), scale, 2)
+    f = L(P * P / (sg * sg * sg))
+    k = np.arange(n)
+    w = cis(((k[:, None] - n // 2) * k[None, :]).astype(L) / n)
+    sizes = np.abs(w.conj().T @ g.astype(CL) @ w.conj()) * np.abs(w.conj().T @ tm.astype(CL) @ w.conj()) / (n * n)
+    ref = f * (g.astype(L) * tm).sum()
+    assert abs(float(L(float(ds)) - ref)) < 8 * 2.0 ** -53 * float(f * sizes.sum())
