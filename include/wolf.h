@@ -239,8 +239,8 @@ WOLF_API wolf_status wolf_propagate_adjoint_diag(const void* g_diag, void* g_in,
 
 /*
  * wolf_propagate_density -- S of the propagated CSD, as wolf_propagate_fresnel (or _farfield) in place and
- * wolf_spectral_density give it, bit for bit, without the rest of the propagated array: after the second-point passes
- * only the entries that S needs are kept.
+ * wolf_spectral_density give it, bit for bit. Up to N = 128 without the rest of the propagated array: after the second-point
+ * passes only the entries that S needs are kept.
  *   w        device, N^4 complex, the source; its contents are undefined after the call.
  *   s_out    device, N*N real, must not overlap w.   farfield: 0 Fresnel, 1 far field.
  */

@@ -5,7 +5,7 @@ Forward:  I, sigma_g -> W_A (custom map with a Gaussian degree of coherence; eq.
 Backward: dL/dS_B -> adjoint propagation of diag(dL/dS_B) -> dL/dI and dL/dsigma_g.
 Every step runs in libwolf kernels; this module only orders the calls. In complex128 both directions are FP64 sums
 over the difference of the two points (fit_forward, fit_backward: no N^4 array; a step at N = 64 takes 0.23 ms instead
-of 0.74, at N = 128 0.35 instead of 10.7). complex64 propagates its FP32 arrays: its gradient in sigma_g is an FP64
+of 0.78, at N = 128 0.36 instead of 10.8). complex64 propagates its FP32 arrays: its gradient in sigma_g is an FP64
 number of its own FP32 rounding, and stays what it was.
 """
 from __future__ import annotations

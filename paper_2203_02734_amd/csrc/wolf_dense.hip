@@ -60,8 +60,8 @@ __device__ __forceinline__ TileRange xcd_tiles(long long tiles) {
 //           the stores of a row are runs of 16 elements.
 //   CONTIG: the data is the A operand: a store is a run of 16 outputs along the line.
 // Bound: memory up to N of about 150 (without its products the N = 150 pass takes 2.2 ms, without its loads and stores
-// 1.4 ms), the FP32 matrix cores above. N = 150 unpadded, complex64: 29.9 -> 8.5 ms (3.8 TB/s moved), N = 200 to
-// 210: 126 -> 29.9 ms; error against FP64 5.0e-7 -> 3.2e-7 at N = 150. Before, a 64 x 64-tiled complex product
+// 1.4 ms), the FP32 matrix cores above. N = 150 unpadded, complex64: 29.8 -> 8.8 ms (3.7 TB/s moved), N = 200 to
+// 210: 126 -> 29.9 ms; error against FP64 4.8e-7 -> 3.0e-7 at N = 150 (a beam behind a circular aperture). Before, a 64 x 64-tiled complex product
 // generated its matrix tile by tile into LDS behind two barriers per 16 steps. Measured and not kept: the next
 // tile's loads issued ahead of the products (9.1 ms, half the wavefronts), 32 lines per wavefront with 16-byte
 // accesses (9.0 ms).
@@ -111,7 +111,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mirror_wave
     const int line0 = ((int)u * 4 + wv) * 16;
     if (line0 >= lines) continue;  // no barrier in the loop
     // Addresses: a uniform base (the wavefront's first line, at its middle row) and a 32-bit byte offset per lane.
-    // The lines of a wavefront may run into the next block; their offsets stay below outer_stride + 16 elements.
+    // The 16 lines of a wavefront may run over blocks (N < 16: up to eight); the offsets of its lines stay below
+    // ceil(16 / ncols) outer_stride + 16 col_stride elements, those of its rows 15 axis_stride: under 4 GiB for every N.
     const int o0 = line0 / ncols, col0 = line0 - o0 * ncols;
     const long long base0 = (long long)o0 * j.outer_stride + (long long)col0 * j.col_stride + (long long)c * as;
     const bool line_ok = line0 + l16 < lines;

@@ -222,7 +222,7 @@ template hipError_t launch_fit_gradient<double2>(int, const double2*, const floa
 // N^4 / 2 and N^4 complex multiply-adds on N^2 operands in FP64, where the propagated array took three passes over N^4
 // elements each way. D and D2 obey X[-d] = conj(X[d]), so d_i runs over [0, N/2].
 // Bound: launches and LDS reads. One optimisation step in complex128: N = 64 0.78 -> 0.23 ms (68 us of it in these
-// kernels), N = 128 10.8 -> 0.36 ms (245 us; the sums 84 and 114 us).
+// kernels), N = 128 10.8 -> 0.36 ms (245 us; the sums 72 and 114 us).
 // ---------------------------------------------------------------------------------------------
 constexpr int kFitThreads = 128;
 constexpr int kFitRows = 8;  // rows of one operand per workgroup
