@@ -61,7 +61,8 @@ __device__ __forceinline__ TileRange xcd_tiles(long long tiles) {
 //   CONTIG: the data is the A operand: a store is a run of 16 outputs along the line.
 // Bound: memory up to N of about 150 (without its products the N = 150 pass takes 2.2 ms, without its loads and stores
 // 1.4 ms), the FP32 matrix cores above. N = 150 unpadded, complex64: 29.8 -> 8.8 ms (3.7 TB/s moved), N = 200 to
-// 210: 126 -> 29.9 ms; error against FP64 4.8e-7 -> 3.0e-7 at N = 150 (a beam behind a circular aperture). Before, a 64 x 64-tiled complex product
+// 210: 126 -> 29.9 ms; error against FP64 4.8e-7 -> 3.0e-7 at N = 150 (a beam behind a circular aperture). Before, a
+// 64 x 64-tiled complex product
 // generated its matrix tile by tile into LDS behind two barriers per 16 steps. Measured and not kept: the next
 // tile's loads issued ahead of the products (9.1 ms, half the wavefronts), 32 lines per wavefront with 16-byte
 // accesses (9.0 ms).

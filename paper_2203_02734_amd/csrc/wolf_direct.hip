@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) void k_rs_fold(const T* in, T* out, T* extra, 
 // Workgroups: the pairs of a 64-wide panel of F (or T1) and a matrix tile are listed by groups of an eighth of the panels,
 // each group tile by tile, and each XCD takes an equal contiguous share of the list: it streams the matrices through its
 // L2 about once, and its consecutive workgroups share a matrix tile.
-// Bound: the matrix cores. N = 64: 1.13 and 1.24 ms in complex64 (97 and 91 TFLOP/s executed of 154), 2.04 and 2.28 ms in
+// Bound: the matrix cores. N = 64: 1.07 and 1.16 ms in complex64 (103 and 98 TFLOP/s executed of 154), 2.04 and 2.28 ms in
 // complex128 (54 and 50 of 72); the plain products took 4.2 and 10.7 ms each. Stores of the operands that run along kk
 // are swizzled over the LDS banks (before: 3.45 and 3.18 ms in complex128).
 // !MIRRORED (N < 16): one class whose slots are its indices; a launch is one tile and a chain of at most four steps, which the
